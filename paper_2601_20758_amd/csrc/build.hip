@@ -628,7 +628,8 @@ hipError_t launch_node_ih(const float4* pts, const float4* pparam, int32_t pp_mo
 // k-th nearest neighbour squared distance (per-point bandwidth).
 // One wavefront per leaf, one query particle per lane; each lane keeps its
 // KM smallest squared distances in a sorted register array whose last slot
-// is its current k-th smallest (the threshold). The lane's own leaf and its
+// is its current k-th smallest (the threshold); closer candidates wait in a
+// queue in LDS and are sorted in by networks. The lane's own leaf and its
 // nearest neighbours along the curve come first and bound every answer from above by
 // real distances. The box hierarchy is then walked with the wavefront's
 // largest threshold (a box farther than that cannot hold a closer
@@ -651,19 +652,6 @@ constexpr int kKnnBands = 5;                        // distance bands of the vis
 template <int KM>
 constexpr int knn_near() {
   return KM >= 32 ? 4 : KM >= 16 ? 2 : 1;
-}
-
-// Insert x into the ascending array a, dropping the largest entry. Each new
-// entry is the median of (old left neighbour, x, old entry), so the updates
-// are independent of each other.
-template <int KM>
-__device__ __forceinline__ void knn_insert(float (&a)[KM], float x) {
-#pragma unroll
-  for (int i = KM - 1; i >= 1; --i) a[i] = __builtin_amdgcn_fmed3f(a[i - 1], x, a[i]);
-  // min(a[0], x) as one operation: the bound -FLT_MAX lies below every
-  // distance, and a -inf entry (only ever read as a left neighbour of
-  // another -inf entry or of this one) may become -FLT_MAX harmlessly
-  a[0] = __builtin_amdgcn_fmed3f(a[0], x, -3.402823466e38f);
 }
 
 // Largest unsigned value over the wavefront (uniform result): DPP row
@@ -689,23 +677,27 @@ __device__ __forceinline__ float wave_max_nonneg(float v) {
   return __uint_as_float(wave_max_u32(__float_as_uint(v)));
 }
 
-// Ascending bitonic sorting network on a register array (N a power of two;
-// every index is a compile-time constant, so each compare-exchange is one
-// min and one max).
+// Ascending sorting network on a register array (Batcher's odd-even merge
+// sort, N a power of two; every index is a compile-time constant, so each
+// compare-exchange is one min and one max: 63 of them for 16 values, against
+// 80 of the bitonic network). The values are the bit patterns of non-negative
+// floats, whose order as integers is the floats' order: integer min and max
+// need no instruction that quiets a NaN first.
 template <int N>
-__device__ __forceinline__ void sort_net(float (&v)[N]) {
+__device__ __forceinline__ void sort_net(int (&v)[N]) {
 #pragma unroll
-  for (int size = 2; size <= N; size <<= 1) {
+  for (int p = 1; p < N; p <<= 1) {
 #pragma unroll
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
+    for (int k = p; k >= 1; k >>= 1) {
 #pragma unroll
-      for (int i = 0; i < N; ++i) {
-        const int j = i ^ stride;
-        if (j > i) {
-          const float lo = fminf(v[i], v[j]), hi = fmaxf(v[i], v[j]);
-          const bool up = (i & size) == 0 || size == N;
-          v[i] = up ? lo : hi;
-          v[j] = up ? hi : lo;
+      for (int j = k % p; j + k < N; j += 2 * k) {
+#pragma unroll
+        for (int i = 0; i < k; ++i) {
+          if (i + j + k < N && (i + j) / (2 * p) == (i + j + k) / (2 * p)) {
+            const int lo = min(v[i + j], v[i + j + k]), hi = max(v[i + j], v[i + j + k]);
+            v[i + j] = lo;
+            v[i + j + k] = hi;
+          }
         }
       }
     }
@@ -717,17 +709,17 @@ __device__ __forceinline__ void sort_net(float (&v)[N]) {
 // and reversed b holds exactly those N values as a bitonic sequence, which
 // one half-cleaner cascade sorts; the padding leaves a's first N - M alone.
 template <int N, int M>
-__device__ __forceinline__ void merge_low(float (&a)[N], const float (&b)[M]) {
+__device__ __forceinline__ void merge_low(int (&a)[N], const int (&b)[M]) {
   static_assert(M <= N, "merge a shorter run into a longer one");
 #pragma unroll
-  for (int i = 0; i < M; ++i) a[N - M + i] = fminf(a[N - M + i], b[M - 1 - i]);
+  for (int i = 0; i < M; ++i) a[N - M + i] = min(a[N - M + i], b[M - 1 - i]);
 #pragma unroll
   for (int stride = N >> 1; stride > 0; stride >>= 1) {
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       const int j = i ^ stride;
       if (j > i) {
-        const float lo = fminf(a[i], a[j]), hi = fmaxf(a[i], a[j]);
+        const int lo = min(a[i], a[j]), hi = max(a[i], a[j]);
         a[i] = lo;
         a[j] = hi;
       }
@@ -743,32 +735,31 @@ __device__ __forceinline__ float pt_box_d2(const float* b, float x, float y, flo
   return __fadd_rn(__fadd_rn(__fmul_rn(gx, gx), __fmul_rn(gy, gy)), __fmul_rn(gz, gz));
 }
 
-#ifndef SFK_KNN_WAVES
-#define SFK_KNN_WAVES 4
-#endif
-#ifndef SFK_KNN_RUN
-#define SFK_KNN_RUN 16
-#endif
+// Candidates a lane takes before they are sorted in, kKnnRun at a time, and
+// the rows of its column in the queue: a group of kKnnSub fits when kKnnRun
+// or fewer are waiting.
+constexpr int kKnnRun = 16;
+constexpr int kKnnRows = kKnnRun + kKnnSub + 1;
+static_assert(2 * kKnnList <= kKnnRows * 64, "the held leaves share the queue's LDS");
 
 template <int KM>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KM <= 32 ? SFK_KNN_WAVES : 2))) void k_knn(TreeView tv, const float* __restrict__ sub_box, int k,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KM <= 32 ? 4 : 2))) void k_knn(TreeView tv, const float* __restrict__ sub_box, int k,
                                              float* __restrict__ h2_sorted,
                                              const float* __restrict__ skip_if) {
   if (skip_if && *skip_if > 0.0f) return;  // the build fails: non-finite coordinates
   __shared__ float4 lds_pts[4][SFK_LEAF];
   __shared__ int32_t lds_stack[4][SFK_STACK];
-  __shared__ float lds_d2[4][kKnnSub * 64];
-  __shared__ int32_t lds_lid[4][kKnnList];
-  __shared__ float lds_lkey[4][kKnnList];
+  __shared__ float lds_queue[4][kKnnRows * 64];
   __shared__ int32_t lds_ord[4][kKnnList];
   __shared__ float4 lds_sb[4][2 * kKnnSubPerLeaf];
   const int lane = lane_id(), wave = threadIdx.x >> 6;
   float4* lp = lds_pts[wave];
   float4* lsb = lds_sb[wave];
-  float* ld2 = lds_d2[wave];
+  float* queue = lds_queue[wave];
   int32_t* stack = lds_stack[wave];
-  int32_t* lid = lds_lid[wave];
-  float* lkey = lds_lkey[wave];
+  // the leaves held by the walk live in the queue's LDS: it is empty then
+  float* lkey = queue;
+  int32_t* lid = reinterpret_cast<int32_t*>(queue + kKnnList);
   int32_t* ord = lds_ord[wave];
   const int nl = tv.n_leaves;
   const NodeBox* leaf_box = tv.nodes + tv.level_off[0];
@@ -776,27 +767,80 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KM <= 32 ? 
     const int64_t my = (int64_t)leaf * SFK_LEAF + lane;
     const float4 q = tv.pts[my];
     const bool real = my < tv.n;
-    // The first KM - k slots hold -inf and never move, so the last slot is
-    // always the k-th smallest distance seen (no runtime index into a).
-    float a[KM];
+    // Squared distances as bit patterns. The first KM - k slots hold the
+    // lowest integer and never move, so the last slot is always the k-th
+    // smallest distance sorted in (no runtime index into a).
+    constexpr int kInf = 0x7f800000;
+    int a[KM];
 #pragma unroll
-    for (int i = 0; i < KM; ++i) a[i] = i < KM - k ? -__builtin_huge_valf() : __builtin_huge_valf();
-    float thr = __builtin_huge_valf();
+    for (int i = 0; i < KM; ++i) a[i] = i < KM - k ? (int)0x80000000 : kInf;
+    // (padding lanes take no candidate)
+    float thr = real ? __builtin_huge_valf() : -1.0f;
+    int qn = 0;  // candidates in this lane's column of the queue
     const NodeBox qb = leaf_box[leaf];
+
+    auto merge_run = [&](int (&b)[kKnnRun]) {
+      if constexpr (KM < kKnnRun) {
+        // a short list: each half of the run by itself
+        int b0[KM], b1[KM];
+#pragma unroll
+        for (int i = 0; i < KM; ++i) {
+          b0[i] = b[i];
+          b1[i] = b[KM + i];
+        }
+        sort_net<KM>(b0);
+        merge_low<KM, KM>(a, b0);
+        sort_net<KM>(b1);
+        merge_low<KM, KM>(a, b1);
+      } else {
+        sort_net<kKnnRun>(b);
+        merge_low<KM, kKnnRun>(a, b);
+      }
+      if (real) thr = __int_as_float(a[KM - 1]);
+    };
+    // The last kKnnRun candidates (or fewer) of every lane's column. Rows
+    // past a column's end hold +inf, but for the first of them, which may
+    // hold a distance that was not taken.
+    auto flush = [&]() {
+      int* top = reinterpret_cast<int*>(queue) + lane;
+      top[qn * 64] = kInf;
+      qn = max(qn - kKnnRun, 0);
+      int* c = top + qn * 64;
+      int b[kKnnRun];
+#pragma unroll
+      for (int i = 0; i < kKnnRun; ++i) b[i] = c[i * 64];
+#pragma unroll
+      for (int i = 0; i < kKnnRun; ++i) c[i * 64] = kInf;
+      merge_run(b);
+    };
+    // rows [0, n) of the queue to +inf
+    auto clear_rows = [&](int n) {
+      for (int i = 0; i < n; ++i) reinterpret_cast<int*>(queue)[i * 64 + lane] = kInf;
+    };
 
     // One candidate leaf, its particle for this lane in pc and its eight
     // sub-block boxes over the lanes of sbv (8 floats per box). Lanes 0..7
     // first test one box each against the query leaf's box and the
     // wavefront's largest threshold (a box that fails cannot hold a particle
     // closer to any lane than its threshold); the boxes that pass are tested
-    // per lane. Per needed sub-block each lane marks the particles below its
-    // threshold; the insertion then runs in rounds, a round inserting every
-    // lane's next marked particle, until no lane has one left.
-    auto process = [&](int cl, const float4 pc, const float sbv) {
+    // per lane. Per needed sub-block each lane appends the distances below its
+    // threshold to its column of the queue (every distance is stored at the
+    // column's end, which advances past the accepted ones only).
+    //
+    // Bound by VALU issue (10M clustered points, k = 32: 6.2 ms, 8.35 ms with
+    // the insertion below). A leaf evaluates 103 groups and sorts 32 runs in:
+    // appending costs three instructions a candidate, and a run is read, sorted
+    // (63 compare-exchanges) and merged (16 minima, 80 compare-exchanges) for
+    // every lane at once, some 320 instructions. Inserting each group's
+    // candidates as they came, one median per list slot, took as many rounds
+    // of 40 instructions as the busiest lane had candidates, 440 a leaf. Runs
+    // of 8 were slower (27 instructions a value merged against 19), a queue of
+    // 8 more rows, with 3 wavefronts a SIMD, too.
+    auto process = [&](const float4 pc, const float sbv) {
       lp[lane] = pc;
       if (lane < kKnnBoxFloats) reinterpret_cast<float*>(lsb)[lane] = sbv;
       wave_sync();
-      const float tnow = wave_max_nonneg(real ? thr : 0.0f);
+      const float tnow = wave_max_nonneg(fmaxf(thr, 0.0f));
       bool cpass = false;
       if (lane < kKnnSubPerLeaf) {
         const float4 blo = lsb[2 * lane], bhi = lsb[2 * lane + 1];
@@ -810,34 +854,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KM <= 32 ? 
         if (cand & (1u << j)) {
           const float4 blo = lsb[2 * j], bhi = lsb[2 * j + 1];
           const float bx[6] = {blo.x, blo.y, blo.z, bhi.x, bhi.y, bhi.z};
-          if (ballot(real && pt_box_d2(bx, q.x, q.y, q.z) < thr)) need |= 1u << j;
+          if (ballot(pt_box_d2(bx, q.x, q.y, q.z) < thr)) need |= 1u << j;
         }
       }
-      const int self = cl == leaf ? lane : -1;
       while (need) {
         const int j = __ffs(need) - 1;
         need &= need - 1;
-        uint32_t mark = 0;
+        if (ballot(qn > kKnnRun)) flush();
 #pragma unroll
         for (int u = 0; u < kKnnSub; ++u) {
           const float4 p = lp[j * kKnnSub + u];
           const float x = canon_d2(q.x, q.y, q.z, p.x, p.y, p.z);
-          ld2[u * 64 + lane] = x;  // own column: no other lane reads it
-          if (x < thr) mark |= 1u << u;
-        }
-        // the query itself and padding lanes never insert
-        const int rel = self - j * kKnnSub;
-        if ((unsigned)rel < (unsigned)kKnnSub) mark &= ~(1u << rel);
-        if (!real) mark = 0;
-        const int rounds = (int)wave_max_u32((unsigned)__popc(mark));
-        for (int r = 0; r < rounds; ++r) {
-          // a lane without a mark reads any slot of its column and inserts +inf
-          const int u = (__ffs(mark) - 1) & (kKnnSub - 1);
-          const float x = mark ? ld2[u * 64 + lane] : __builtin_huge_valf();
-          mark &= mark - 1;
-          // lanes with x >= thr only touch entries past the k-th: harmless
-          knn_insert<KM>(a, x);
-          thr = a[KM - 1];
+          queue[qn * 64 + lane] = x;  // own column: no other lane reads it
+          qn += x < thr ? 1 : 0;
         }
       }
       wave_sync();
@@ -850,7 +879,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KM <= 32 ? 
       float4 pn = tv.pts[(int64_t)cl * SFK_LEAF + lane];
       float sn = lane < kKnnBoxFloats ? sub_box[(int64_t)cl * kKnnBoxFloats + lane] : 0.0f;
       for (int i = 0; i < count; ++i) {
-        const int cur = cl;
         const float4 pc = pn;
         const float sc = sn;
         if (i + 1 < count) {
@@ -858,8 +886,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KM <= 32 ? 
           pn = tv.pts[(int64_t)cl * SFK_LEAF + lane];
           sn = lane < kKnnBoxFloats ? sub_box[(int64_t)cl * kKnnBoxFloats + lane] : 0.0f;
         }
-        process(cur, pc, sc);
+        process(pc, sc);
       }
+      while (ballot(qn > 0)) flush();
     };
 
     // Depth-first walk of the box hierarchy that stops whenever the held
@@ -935,7 +964,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KM <= 32 ? 
             const float bx[6] = {readlane_f(bb.lo[0], b), readlane_f(bb.lo[1], b),
                                  readlane_f(bb.lo[2], b), readlane_f(bb.hi[0], b),
                                  readlane_f(bb.hi[1], b), readlane_f(bb.hi[2], b)};
-            if (ballot(real && pt_box_d2(bx, q.x, q.y, q.z) < thr)) {
+            if (ballot(pt_box_d2(bx, q.x, q.y, q.z) < thr)) {
               if (lane == 0) ord[no] = __builtin_amdgcn_readlane(id, b);
               ++no;
             }
@@ -945,6 +974,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KM <= 32 ? 
       }
       ln = 0;
       wave_sync();
+      clear_rows(2 * kKnnList / 64);  // the held leaves' share of the queue
       return no;
     };
 
@@ -957,40 +987,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KM <= 32 ? 
       if (phase == 0) {
         // the leaf, then its curve neighbours at distance 1, 2, ... knn_near
         no = 0;
-        if (k == KM) {
-          // The leaf's particles are the lanes' own queries. With no -inf
-          // slots, a lane's KM smallest distances to them come from sorting
-          // networks over KM of them at a time (the query itself and padding
-          // at +inf), merged keeping the lower half: the same values the
-          // insertion would keep, without its 64 rounds.
-          lp[lane] = q;
-          wave_sync();
-          auto own = [&](int u) {
-            const float4 p = lp[u];
-            return u == lane ? __builtin_huge_valf() : canon_d2(q.x, q.y, q.z, p.x, p.y, p.z);
-          };
+        // the leaf's particles are the lanes' own queries (a query is not its
+        // own neighbour)
+        clear_rows(kKnnRows);
+        lp[lane] = q;
+        wave_sync();
+#pragma unroll 1
+        for (int c0 = 0; c0 < SFK_LEAF; c0 += kKnnRun) {
+          int b[kKnnRun];
 #pragma unroll
-          for (int i = 0; i < KM; ++i) a[i] = own(i);
-          sort_net<KM>(a);
-          // the rest in sorted runs of at most 16, so both arrays stay in
-          // registers (10M points, k = 32: k-NN 9.09 -> 8.75 ms against the
-          // insertion; whole runs of 32: 8.79 ms; the first 32 sorted and the
-          // rest inserted: 8.90 ms)
-          constexpr int R = KM > SFK_KNN_RUN ? SFK_KNN_RUN : KM;
-#pragma unroll
-          for (int c0 = KM; c0 < SFK_LEAF; c0 += R) {
-            float b[R];
-#pragma unroll
-            for (int i = 0; i < R; ++i) b[i] = own(c0 + i);
-            sort_net<R>(b);
-            merge_low<KM, R>(a, b);
+          for (int i = 0; i < kKnnRun; ++i) {
+            const float4 p = lp[c0 + i];
+            const float x = canon_d2(q.x, q.y, q.z, p.x, p.y, p.z);
+            b[i] = c0 + i == lane ? kInf : __float_as_int(x);
           }
-          thr = a[KM - 1];
-          wave_sync();
-        } else {
-          if (lane == 0) ord[0] = leaf;
-          ++no;
+          merge_run(b);
         }
+        wave_sync();
         for (int d = 1; d <= knn_near<KM>(); ++d) {
           if (leaf - d >= 0) {
             if (lane == 0) ord[no] = leaf - d;
