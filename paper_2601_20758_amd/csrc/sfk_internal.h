@@ -281,26 +281,19 @@ hipError_t launch_sweep_eval(TreeView tv, const BatchHdr* hdr, const RoiDev* roi
                              int grid_blocks, int n_cu, int64_t max_tiles, hipStream_t s);
 
 // mbe.hip
-// leaves whose box meets the closed box [lo, hi]: flags[n_leaves]; their
-// indices, ascending, from the flags' exclusive scan
-hipError_t launch_leaf_overlap(const NodeBox* leaf_box, int32_t n_leaves, const double* lo,
-                               const double* hi, int32_t* flags, hipStream_t s);
-hipError_t launch_compact_leaves(const int32_t* flags, const int64_t* pos, int32_t n_leaves,
-                                 int32_t* cand, hipStream_t s);
-// particles in the closed box among n examined slots: every slot in order
-// (cand == nullptr, n = slots) or the 64 slots of each candidate leaf in
-// order (n = 64 * candidates); flags and positions index examined slots
-hipError_t launch_inbox_flags(const float4* pts, const int32_t* cand, int64_t n, const double* lo,
-                              const double* hi, int32_t* flags, hipStream_t s);
-hipError_t launch_compact(const float4* pts, const int32_t* perm, const int32_t* cand,
-                          const int32_t* flags, const int64_t* pos, int64_t n,
-                          int64_t n_slots_out, float4* out_pts, int32_t* out_perm,
-                          float* out_axes, int64_t n_b, hipStream_t s);
-hipError_t launch_axis_keys(const float* axes, int64_t n_b, uint64_t* keys, uint32_t* vals,
+// particles in the closed box [lo, hi]: their number in each leaf, then, from
+// the counts' exclusive scan, the particles themselves in the cloud's order
+hipError_t launch_box_count(const NodeBox* leaf_box, const float4* pts, int32_t n_leaves,
+                            const double* lo, const double* hi, int32_t* cnt,
                             hipStream_t s);
-hipError_t launch_mbe_ell(const uint64_t* sorted_keys_xyz, int64_t n_b, const double* lo,
-                          const double* hi, const int32_t* res, float* ell_out,
-                          int32_t* flags_out, hipStream_t s);
+hipError_t launch_box_write(const float4* pts, const int32_t* perm, const int32_t* cnt,
+                            const int64_t* pos, int32_t n_leaves, const double* lo,
+                            const double* hi, int64_t n_b, int64_t n_slots_out, float4* out_pts,
+                            int32_t* out_perm, float* out_axes, hipStream_t s);
+// Eq. 1's smoothing lengths; n_b < 2^32 particles, all in [lo, hi]
+size_t axis_select_tmp_bytes();
+hipError_t launch_axis_select(const float* axes, int64_t n_b, const double* lo, const double* hi,
+                              const int32_t* res, void* tmp, float* ell_out, hipStream_t s);
 hipError_t launch_trilinear_mean(const float4* pts, int64_t n_b, const float* grid,
                                  const double* lo, const double* hi, const int32_t* res,
                                  double* pden, double* block_sums, double* ave, hipStream_t s);

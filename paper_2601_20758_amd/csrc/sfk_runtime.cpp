@@ -1150,7 +1150,9 @@ struct SubCloud {
   int32_t n_leaves = 0, n_levels = 0, total_nodes = 0;
   int32_t off[SFK_MAX_LEVELS], cnt[SFK_MAX_LEVELS];
   TmpBuf pts, perm, nodes, node_ih, pparam, axes;
-  explicit SubCloud(sfk_ctx c) : pts(c), perm(c), nodes(c), node_ih(c), pparam(c), axes(c) {}
+  TmpBuf cnt_b, pos, stmp;  // per leaf of the cloud; live until the evaluation is done
+  explicit SubCloud(sfk_ctx c)
+      : pts(c), perm(c), nodes(c), node_ih(c), pparam(c), axes(c), cnt_b(c), pos(c), stmp(c) {}
   TreeView view(int pp) const {
     TreeView tv{};
     tv.pts = pts.as<const float4>();
@@ -1171,41 +1173,20 @@ struct SubCloud {
 
 sfk_status make_subcloud(sfk_ctx c, sfk_tree t, const sfk_roi* r, bool want_axes, SubCloud& sc,
                          hipStream_t s) {
-  // Only the leaves whose box meets B can hold particles in B: find them
-  // first, then examine their slots alone (in leaf order, so the particles
-  // come out in the tree's order as a scan of every slot would give them).
-  // Work and scratch then grow with the box's leaves, not with the cloud.
   const int32_t nl = t->n_leaves;
-  TmpBuf lflags(c), lpos(c), ltotal(c), cand(c), flags(c), pos(c), stmp(c), total(c);
-  SFK_TRY(lflags.get(sizeof(int32_t) * (size_t)std::max(nl, 1), "leaf flags"));
-  SFK_TRY(lpos.get(sizeof(int64_t) * (size_t)std::max(nl, 1), "leaf positions"));
-  SFK_TRY(ltotal.get(sizeof(int64_t), "leaf total"));
-  SFK_TRY(stmp.get(sfk::scan_tmp_bytes((int64_t)nl * SFK_LEAF), "scan scratch"));
-  int64_t n_cand = 0;
-  if (nl > 0) {
-    SFK_HIP(c, sfk::launch_leaf_overlap((const NodeBox*)t->nodes.p + t->level_off[0], nl, r->lo,
-                                         r->hi, lflags.as<int32_t>(), s));
-    SFK_HIP(c, sfk::scan_exclusive_i32_i64(lflags.as<int32_t>(), lpos.as<int64_t>(), nl,
-                                            ltotal.as<int64_t>(), stmp.b.p, stmp.b.bytes, s));
-    SFK_HIP(c, hipMemcpyAsync(&n_cand, ltotal.b.p, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    SFK_HIP(c, hipStreamSynchronize(s));
-  }
-  const int64_t n_slots = n_cand * SFK_LEAF;  // examined slots
-  SFK_TRY(cand.get(sizeof(int32_t) * (size_t)std::max<int64_t>(n_cand, 1), "candidate leaves"));
-  SFK_TRY(flags.get(sizeof(int32_t) * (size_t)std::max<int64_t>(n_slots, 1), "in-box flags"));
-  SFK_TRY(pos.get(sizeof(int64_t) * (size_t)std::max<int64_t>(n_slots, 1), "in-box positions"));
-  SFK_TRY(total.get(sizeof(int64_t), "in-box total"));
-  if (n_cand > 0) {
-    SFK_HIP(c, sfk::launch_compact_leaves(lflags.as<int32_t>(), lpos.as<int64_t>(), nl,
-                                           cand.as<int32_t>(), s));
-    SFK_HIP(c, sfk::launch_inbox_flags((const float4*)t->pts.p, cand.as<int32_t>(), n_slots,
-                                        r->lo, r->hi, flags.as<int32_t>(), s));
-    SFK_HIP(c, sfk::scan_exclusive_i32_i64(flags.as<int32_t>(), pos.as<int64_t>(), n_slots,
-                                            total.as<int64_t>(), stmp.b.p, stmp.b.bytes, s));
-  }
+  TmpBuf &cnt = sc.cnt_b, &pos = sc.pos, &stmp = sc.stmp;
+  SFK_TRY(cnt.get(sizeof(int32_t) * (size_t)std::max(nl, 1), "in-box counts"));
+  SFK_TRY(pos.get(sizeof(int64_t) * ((size_t)nl + 1), "in-box positions"));
+  SFK_TRY(stmp.get(sfk::scan_tmp_bytes(nl), "scan scratch"));
   int64_t n_b = 0;
-  if (n_cand > 0) {
-    SFK_HIP(c, hipMemcpyAsync(&n_b, total.b.p, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+  if (nl > 0) {
+    int64_t* total = pos.as<int64_t>() + nl;
+    SFK_HIP(c, sfk::launch_box_count((const NodeBox*)t->nodes.p + t->level_off[0],
+                                     (const float4*)t->pts.p, nl, r->lo, r->hi,
+                                     cnt.as<int32_t>(), s));
+    SFK_HIP(c, sfk::scan_exclusive_i32_i64(cnt.as<int32_t>(), pos.as<int64_t>(), nl, total,
+                                            stmp.b.p, stmp.b.bytes, s));
+    SFK_HIP(c, hipMemcpyAsync(&n_b, total, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     SFK_HIP(c, hipStreamSynchronize(s));
   }
   sc.n_b = n_b;
@@ -1219,16 +1200,12 @@ sfk_status make_subcloud(sfk_ctx c, sfk_tree t, const sfk_roi* r, bool want_axes
   if (want_axes)
     SFK_TRY(sc.axes.get(sizeof(float) * 3 * (size_t)std::max<int64_t>(n_b, 1), "in-box axes"));
   if (n_b == 0) return SFK_OK;
-  SFK_HIP(c, sfk::launch_compact((const float4*)t->pts.p, (const int32_t*)t->perm.p,
-                                  cand.as<int32_t>(), flags.as<int32_t>(), pos.as<int64_t>(),
-                                  n_slots, out_slots,
-                                  sc.pts.as<float4>(), sc.perm.as<int32_t>(),
-                                  want_axes ? sc.axes.as<float>() : nullptr, n_b, s));
-  SFK_TRY(build_boxes(c, sc.pts.as<float4>(), n_b, sc.n_leaves, sc.nodes.as<NodeBox>(), sc.off,
-                      sc.cnt, sc.n_levels, s));
-  // keep the temporaries alive until the kernels that read them are done
-  SFK_HIP(c, hipStreamSynchronize(s));
-  return SFK_OK;
+  SFK_HIP(c, sfk::launch_box_write((const float4*)t->pts.p, (const int32_t*)t->perm.p,
+                                   cnt.as<int32_t>(), pos.as<int64_t>(), nl, r->lo, r->hi, n_b,
+                                   out_slots, sc.pts.as<float4>(), sc.perm.as<int32_t>(),
+                                   want_axes ? sc.axes.as<float>() : nullptr, s));
+  return build_boxes(c, sc.pts.as<float4>(), n_b, sc.n_leaves, sc.nodes.as<NodeBox>(), sc.off,
+                     sc.cnt, sc.n_levels, s);
 }
 
 struct MbeDebug {
@@ -1311,25 +1288,12 @@ sfk_status eval_subcloud(sfk_ctx c, sfk_tree t, const sfk_roi* r, bool count_mod
   }
 
   // ---- MBE (Section 3.1) ----
-  // Eq. 1: exact order statistics from one radix sort of the three axes
-  TmpBuf keys(c), keys2(c), vals(c), vals2(c), stmp(c), ell_d(c), flag_d(c), pilot(c), pden(c),
-      bsum(c), ave_d(c), ellj_d(c);
-  const int64_t m3 = 3 * n_b;
-  SFK_TRY(keys.get(sizeof(uint64_t) * (size_t)m3, "axis keys"));
-  SFK_TRY(keys2.get(sizeof(uint64_t) * (size_t)m3, "axis keys"));
-  SFK_TRY(vals.get(sizeof(uint32_t) * (size_t)m3, "axis values"));
-  SFK_TRY(vals2.get(sizeof(uint32_t) * (size_t)m3, "axis values"));
-  SFK_TRY(stmp.get(sfk::radix_sort_tmp_bytes(m3), "sort scratch"));
+  // Eq. 1: exact order statistics of the three axes
+  TmpBuf stmp(c), ell_d(c), pilot(c), pden(c), bsum(c), ave_d(c), ellj_d(c);
+  SFK_TRY(stmp.get(sfk::axis_select_tmp_bytes(), "selection scratch"));
   SFK_TRY(ell_d.get(4 * sizeof(float), "smoothing lengths"));
-  SFK_TRY(flag_d.get(sizeof(int32_t), "flags"));
-  SFK_HIP(c, sfk::launch_axis_keys(sc.axes.as<float>(), n_b, keys.as<uint64_t>(),
-                                    vals.as<uint32_t>(), s));
-  int alt = 0;
-  SFK_HIP(c, sfk::radix_sort_pairs(keys.as<uint64_t>(), vals.as<uint32_t>(), keys2.as<uint64_t>(),
-                                    vals2.as<uint32_t>(), m3, 34, stmp.b.p, stmp.b.bytes, s, &alt));
-  const uint64_t* sorted = alt ? keys2.as<uint64_t>() : keys.as<uint64_t>();
-  SFK_HIP(c, sfk::launch_mbe_ell(sorted, n_b, r->lo, r->hi, r->res, ell_d.as<float>(),
-                                  flag_d.as<int32_t>(), s));
+  SFK_HIP(c, sfk::launch_axis_select(sc.axes.as<float>(), n_b, r->lo, r->hi, r->res, stmp.b.p,
+                                     ell_d.as<float>(), s));
   float ell0[3];
   SFK_HIP(c, hipMemcpyAsync(ell0, ell_d.b.p, 3 * sizeof(float), hipMemcpyDeviceToHost, s));
   SFK_HIP(c, hipStreamSynchronize(s));
