@@ -1091,6 +1091,8 @@ __global__ __launch_bounds__(256) void k_iso_params(float4* __restrict__ pts,
       }
       pts[i] = p;
       if (p.x < 1.0e29f) m = p.w;
+    } else {  // a padding slot: with w = 0 its support would be everywhere
+      pts[i].w = 1.0f;
     }
     m = wave_min(m);
     if (lane == 0) leaf_ih[leaf] = make_float4(m, m, m, 0.0f);

@@ -478,13 +478,16 @@ __global__ __launch_bounds__(256) void k_mean(const double* __restrict__ block_s
   if (threadIdx.x == 0) *ave = n_b > 0 ? (((lds[0] + lds[1]) + lds[2]) + lds[3]) / (double)n_b : 0.0;
 }
 
-// Eq. 6 per particle; pden <= 0 takes the cap.
+// Eq. 6 per particle; pden <= 0 takes the cap. The last leaf's padding slots
+// get finite parameters too (a zero would reach every node).
 __global__ __launch_bounds__(256) void k_asl(const double* __restrict__ pden, int64_t n_b,
                                              const double* __restrict__ ave_p, float e0, float e1,
                                              float e2, GridGeo gg, float4* __restrict__ pparam,
                                              float* __restrict__ ell_out) {
   const double ave = *ave_p;
   const float e[3] = {e0, e1, e2};
+  if (blockIdx.x == 0 && threadIdx.x < ((-n_b) & (SFK_LEAF - 1)))
+    pparam[n_b + threadIdx.x] = make_float4(1.0f, 1.0f, 1.0f, 0.0f);
   for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n_b;
        j += (int64_t)gridDim.x * blockDim.x) {
     const double pd = pden[j];
