@@ -510,8 +510,19 @@ __device__ __forceinline__ void reduce_nodes(A (&acc)[T]) {
   }
 }
 
-// leaf ids of a work item staged in LDS at a time
-constexpr int kIdBlock = 256;
+// leaf ids a walking work item holds (two blocks of 64 and a step's 64 more)
+constexpr int kWalkRing = 256;
+
+// Wait until this wavefront's agent-scope stores and atomics are performed.
+// Those go to the memory side of the eight XCDs' L2s themselves, and readers
+// load them at agent scope, so a chunk that publishes sums only has to wait
+// for its own before it counts itself done. A device-wide fence in its place
+// also writes back and invalidates the XCD's whole L2 on every chunk: the
+// 128^3 MBE estimate of 2.1M particles in chunks of 64 leaves (three a tile)
+// took 3.63 ms with it and 1.93 without, in chunks of 32 5.57 and 2.06.
+__device__ __forceinline__ void agent_writes_done() {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
 
 // -log2(e)/2 in double: exp(-u2/2) = exp2(KG * u2)
 #define SFK_KG64 (-0.72134752044448170368)
@@ -522,8 +533,17 @@ constexpr int kIdBlock = 256;
 // Epanechnikov value 1 - u2 are double (same rate as unpacked float32 on
 // gfx950), each term then rounded once to float32; the Gaussian factors are
 // float32 exp2 of the double exponents.
+//
+// Bound by VALU issue, two thirds busy, half of it culling (a 4x4x4 tile whose
+// supports span 11 nodes tests four particles for each that reaches it) and
+// half evaluation, about 200 instructions for 64 particles and 64 nodes. Three
+// wavefronts a SIMD (at most 168 registers): with two, and double sums of
+// 4x4x4 tiles, the 128^3 pilot grid of 2.1M particles took 8% longer, with
+// four the sums spill. That grid takes 1.0 ms (1.37 with the cull in double,
+// a maximum per term, a queue moved to the front after each batch and ids read
+// from LDS), the 101x87x93 per-point grid of 1M points 0.18 ms (0.39).
 template <int TX, int TY, int TZ, int KK, int PP, bool CNT>
-__global__ __launch_bounds__(256) void k_eval(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_eval(
     TreeView tv, const RoiDev* __restrict__ rois, const double* __restrict__ coords,
     int chunk_leaves, const int64_t* __restrict__ leaf_off, const int64_t* __restrict__ chunk_off,
     const int64_t* __restrict__ partial_off, const int32_t* __restrict__ tile_cnt,
@@ -535,18 +555,18 @@ __global__ __launch_bounds__(256) void k_eval(
   // Per-lane node accumulators are float32: a lane adds one term per drained
   // batch of 64 particles (at most chunk_leaves terms per work item), the 64
   // lanes are combined by a 6-level tree and the chunks of a tile in double.
-  // Uniform-bandwidth Epanechnikov tiles of at most 16 nodes accumulate in
-  // double (registers allow it), which also saves the per-pair conversion.
-  constexpr bool kDoubleAcc = T <= 16 && KK == KK_EPAN && PP == PP_UNIFORM && !CNT;
+  // Epanechnikov tiles of at most 16 nodes accumulate in double (registers
+  // allow it), which also saves the per-pair conversion.
+  constexpr bool kDoubleAcc = T <= 16 && KK == KK_EPAN && !CNT;
   using Acc = std::conditional_t<kDoubleAcc, double, float>;
-  // particle buffers of the leaf pipeline; each pipeline round appends up to
-  // NB leaves to the queue before draining it, hence its capacity
-  constexpr int NB = 3;
-  constexpr int QCAP = 64 * (NB + 1);
+  // particle buffers of the leaf pipeline (four were no faster and spilled);
+  // the queue is a ring that takes two leaves on top of a remainder below 64
+  constexpr int NB = 2;
+  constexpr int QCAP = 256;
   __shared__ int32_t lds_stack[4][SFK_STACK];
+  __shared__ int32_t lds_walk[4][kWalkRing];
   __shared__ float4 lds_qpts[4][QCAP];
   __shared__ float4 lds_qprm[4][PP == PP_ANISO ? QCAP : 1];
-  __shared__ int32_t lds_ids[4][kIdBlock];
   const int lane = lane_id(), wave = threadIdx.x >> 6;
   const int64_t n_items = min(hdr->n_items, hdr->item_cap);  // equal by construction
   const int n_rois = hdr->n_rois;
@@ -585,7 +605,7 @@ __global__ __launch_bounds__(256) void k_eval(
       cur = slice_at(__ffsll((unsigned long long)open) - 1);
     }
     if (item < 0) break;
-    const int t = item_tile[item];
+    const int t = wave_uniform(item_tile[item]);
     const TileGeo g = tile_geo<TX, TY, TZ>(rois, n_rois, coords, t);
     const RoiDev& R = rois[g.r];
     const double* cx = coords + R.coord_off;
@@ -600,12 +620,25 @@ __global__ __launch_bounds__(256) void k_eval(
     for (int k = 0; k < TZ; ++k) nz[k] = cz[min(g.k0 + k, R.res[2] - 1)];
     const float uih0 = R.ih[0], uih1 = R.ih[1], uih2 = R.ih[2];
     const double c2 = R.c2;
+    // the tile box for the particle cull (keep_of): centre, half widths and
+    // the squared reach, for a uniform bandwidth in units of the reach
+    constexpr double kWide = 1.0 + 0x1p-20;
+    const double reach = 1.0 / (sqrt(c2) * kWide);
+    float bc[3], bh[3], us[3], uh[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      bc[k] = (float)(0.5 * (g.lo[k] + g.hi[k]));
+      const double h = fmax(g.hi[k] - (double)bc[k], (double)bc[k] - g.lo[k]) * kWide;
+      const double sc = (double)R.ih[k] * reach;
+      bh[k] = (float)h;
+      us[k] = (float)sc;
+      uh[k] = (float)(h * sc);
+    }
+    const float cc = (float)(c2 * (kWide * kWide));
     const int cnt = tile_cnt[t];  // > 0: tiles with no candidate leaf have no work item
     const int nch = (cnt + chunk_leaves - 1) / chunk_leaves;
 
     Acc acc[T];
-#pragma unroll
-    for (int q = 0; q < T; ++q) acc[q] = (Acc)0;
 
     // Per-wave queue of particles whose support reaches the tile box. Each
     // leaf is loaded one particle per lane and culled against the tile with
@@ -615,10 +648,9 @@ __global__ __launch_bounds__(256) void k_eval(
     // that can matter. The order is fixed, hence so are the sums.
     float4* qp = lds_qpts[wave];
     float4* qa = lds_qprm[wave];
-    int32_t* ids = lds_ids[wave];
-    int qn = 0;
+    int qn = 0, qh = 0;  // particles queued, place of the first
 
-    auto eval_point = [&](const float4 p, const float4 prm) {
+    auto eval_point = [&](const float4 p, const float4 prm) __attribute__((always_inline)) {
       float ihx, ihy, ihz;
       double w = 1.0;
       if constexpr (PP == PP_UNIFORM) {
@@ -667,39 +699,30 @@ __global__ __launch_bounds__(256) void k_eval(
               acc[i + TX * (j + TY * k)] += (u2 < c2) ? 1.0f : 0.0f;
             }
           }
-      } else if constexpr (KK == KK_EPAN && PP == PP_UNIFORM) {
-        // 1 - u2 = (1 - (sx + sy)) - sz: one subtraction per node (the
-        // rounding differs from 1 - ((sx + sy) + sz) by at most an ulp of
-        // double; a term at the support's edge is then +-1e-16, not 0)
+      } else if constexpr (KK == KK_EPAN) {
+        // 1 - u2 = ((1 - sx) - sy) - sz, clamped to [0, 1] (it never exceeds
+        // 1; the clamp is an output modifier of the subtraction, a maximum
+        // would be an instruction) and added, or multiplied and added, in
+        // double: two instructions a node. The rounding differs from
+        // 1 - ((sx + sy) + sz) by at most an ulp of double or two; a term at
+        // the support's edge is then +-1e-16, not 0.
+        double ox[TX];
+#pragma unroll
+        for (int i = 0; i < TX; ++i) ox[i] = 1.0 - sx[i];
 #pragma unroll
         for (int j = 0; j < TY; ++j)
 #pragma unroll
           for (int i = 0; i < TX; ++i) {
-            const double om = 1.0 - (sx[i] + sy[j]);
+            const double om = ox[i] - sy[j];
             if (!ballot(om > 0.0)) continue;
 #pragma unroll
             for (int k = 0; k < TZ; ++k) {
+              const double v = fmin(fmax(om - sz[k], 0.0), 1.0);
               Acc& a = acc[i + TX * (j + TY * k)];
-              if constexpr (kDoubleAcc)
-                a = a + fmax(om - sz[k], 0.0);
+              if constexpr (PP == PP_UNIFORM)
+                a = a + (Acc)v;
               else
-                a = a + (float)fmax(om - sz[k], 0.0);
-            }
-          }
-      } else if constexpr (KK == KK_EPAN) {
-        const float wf = (float)w;
-#pragma unroll
-        for (int j = 0; j < TY; ++j)
-#pragma unroll
-          for (int i = 0; i < TX; ++i) {
-            const double tt = sx[i] + sy[j];
-            if (!ballot(tt < c2)) continue;
-#pragma unroll
-            for (int k = 0; k < TZ; ++k) {
-              const double u2 = tt + sz[k];
-              const float v = (float)fmax(1.0 - u2, 0.0);
-              Acc& a = acc[i + TX * (j + TY * k)];
-              a = fmaf(wf, v, a);
+                a = fma((Acc)w, (Acc)v, a);
             }
           }
       } else {
@@ -732,32 +755,28 @@ __global__ __launch_bounds__(256) void k_eval(
       }
     };
 
-    // evaluate queue entries [0, 64) and move the rest to the front
-    auto drain64 = [&]() {
-      const float4 p = qp[lane];
+    // evaluate the queue's first 64
+    auto drain64 = [&]() __attribute__((always_inline)) {
+      const int at = (qh + lane) & (QCAP - 1);
+      const float4 p = qp[at];
       float4 prm = make_float4(0.f, 0.f, 0.f, 0.f);
-      if constexpr (PP == PP_ANISO) prm = qa[lane];
-      // move entries [64, qn) to the front, 64 at a time in ascending order
-      for (int e = lane; e + 64 < qn; e += 64) {
-        qp[e] = qp[e + 64];
-        if constexpr (PP == PP_ANISO) qa[e] = qa[e + 64];
-      }
+      if constexpr (PP == PP_ANISO) prm = qa[at];
       qn -= 64;
+      qh += 64;
       wave_sync();
       eval_point(p, prm);
     };
-    // evaluate what is left (lanes past the end take a far dummy particle)
-    auto drain_rest = [&]() {
-      if (qn == 0) return;
-      float4 p = make_float4(SFK_SENTINEL, SFK_SENTINEL, SFK_SENTINEL, 1.0f);
-      float4 prm = make_float4(1.f, 1.f, 1.f, 0.f);
-      if (lane < qn) {
-        p = qp[lane];
-        if constexpr (PP == PP_ANISO) prm = qa[lane];
+    // fill up the queue's last 64 with far dummy particles
+    auto pad64 = [&]() __attribute__((always_inline)) {
+      const int r = qn & 63;
+      if (r == 0) return;
+      if (lane >= r) {
+        const int at = (qh + qn - r + lane) & (QCAP - 1);
+        qp[at] = make_float4(SFK_SENTINEL, SFK_SENTINEL, SFK_SENTINEL, 1.0f);
+        if constexpr (PP == PP_ANISO) qa[at] = make_float4(1.f, 1.f, 1.f, 0.f);
       }
-      qn = 0;
+      qn += 64 - r;
       wave_sync();
-      eval_point(p, prm);
     };
 
     // particle (and, anisotropic, its parameters) of lane `lane` of leaf lid
@@ -766,53 +785,42 @@ __global__ __launch_bounds__(256) void k_eval(
       p = tv.pts[slot];
       if constexpr (PP == PP_ANISO) prm = tv.pparam[slot];
     };
-    // does the particle's support reach the tile box? (same monotone bound
-    // as the tree walk)
-    auto keep_of = [&](const float4 p, const float4 prm) {
-      float ihx = uih0, ihy = uih1, ihz = uih2;
-      if constexpr (PP == PP_ISO) {
-        ihx = ihy = ihz = p.w;
-      } else if constexpr (PP == PP_ANISO) {
-        ihx = prm.x;
-        ihy = prm.y;
-        ihz = prm.z;
+    // Can the particle's support reach the tile box? Float32 with a margin:
+    // d is the distance from the box's centre (as a float), rounded once, the
+    // half width is taken 2^-20 larger and the support 2^-20 wider, while all
+    // roundings together stay below 2^-22. A particle that reaches a node is
+    // always kept; one kept in vain adds exact zeros (+-1e-16 at the edge).
+    // 10 to 16 instructions; in double, with its conversions and maxima, the
+    // test took about 30.
+    auto keep_of = [&](const float4 p, const float4 prm) __attribute__((always_inline)) {
+      const float dx = fabsf(p.x - bc[0]), dy = fabsf(p.y - bc[1]), dz = fabsf(p.z - bc[2]);
+      float ux, uy, uz;
+      if constexpr (PP == PP_UNIFORM) {
+        // clamped to [0, 1] (an output modifier): 1 on any axis is out
+        ux = fminf(fmaxf(fmaf(dx, us[0], -uh[0]), 0.0f), 1.0f);
+        uy = fminf(fmaxf(fmaf(dy, us[1], -uh[1]), 0.0f), 1.0f);
+        uz = fminf(fmaxf(fmaf(dz, us[2], -uh[2]), 0.0f), 1.0f);
+      } else {  // not clamped after the product: infinite ih must give a NaN, out
+        const float gx = fmaxf(dx - bh[0], 0.0f), gy = fmaxf(dy - bh[1], 0.0f),
+                    gz = fmaxf(dz - bh[2], 0.0f);
+        ux = gx * (PP == PP_ISO ? p.w : prm.x);
+        uy = gy * (PP == PP_ISO ? p.w : prm.y);
+        uz = gz * (PP == PP_ISO ? p.w : prm.z);
       }
-      const double px = p.x, py = p.y, pz = p.z;
-      const double gx = fmax(fmax(g.lo[0] - px, px - g.hi[0]), 0.0);
-      const double gy = fmax(fmax(g.lo[1] - py, py - g.hi[1]), 0.0);
-      const double gz = fmax(fmax(g.lo[2] - pz, pz - g.hi[2]), 0.0);
-      const double ux = gx * (double)ihx, uy = gy * (double)ihy, uz = gz * (double)ihz;
-      return ((ux * ux + uy * uy) + uz * uz) < c2;
+      const float u2 = fmaf(ux, ux, fmaf(uy, uy, uz * uz));
+      return u2 < (PP == PP_UNIFORM ? 1.0f : cc);
     };
     // append the kept particles of one leaf (lane order) to the queue; the
     // caller makes the writes visible (wave_sync) before the queue is read
     auto push = [&](const float4 p, const float4 prm, bool keep) {
       const uint64_t m = ballot(keep);
       if (keep) {
-        const int pos = qn + popc64(m & lanemask_lt());
+        const int pos = (qh + qn + popc64(m & lanemask_lt())) & (QCAP - 1);
         qp[pos] = p;
         if constexpr (PP == PP_ANISO) qa[pos] = prm;
       }
       qn += popc64(m);
     };
-    auto cull = [&](const float4 p, const float4 prm, bool live) {
-      push(p, prm, live && keep_of(p, prm));
-      wave_sync();
-    };
-    auto cull_push = [&](const float4 p, const float4 prm) {
-      cull(p, prm, true);
-      if (qn >= 64) drain64();
-    };
-    auto eval_leaf = [&](int lid) {
-      float4 p, prm = make_float4(0.f, 0.f, 0.f, 0.f);
-      fetch(lid, p, prm);
-      cull_push(p, prm);
-    };
-    auto end_chunk = [&]() {
-      drain_rest();
-      reduce_nodes(acc);
-    };
-
     auto node_out = [&](int node, double v) {
       const int i = node % TX, j = (node / TX) % TY, k = node / (TX * TY);
       const int gi = g.i0 + i, gj = g.j0 + j, gk = g.k0 + k;
@@ -827,7 +835,7 @@ __global__ __launch_bounds__(256) void k_eval(
     // the chunk's per-node sums: the grid values when the tile has one
     // chunk, else a partial slot, the last chunk to finish combining all
     // of them in chunk order (in double)
-    auto finish_chunk = [&]() {
+    auto finish_chunk = [&]() __attribute__((always_inline)) {
       if (nch == 1) {
         if (lane_writes) {
 #pragma unroll
@@ -837,14 +845,16 @@ __global__ __launch_bounds__(256) void k_eval(
         const int64_t pbase = (partial_off[t] + c) * T;
         if (lane_writes) {
 #pragma unroll
-          for (int m = 0; m < NPL; ++m) partials[pbase + lane_node(m)] = (double)acc[m];
+          for (int m = 0; m < NPL; ++m)
+            __hip_atomic_store(&partials[pbase + lane_node(m)], (double)acc[m], __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
         }
-        __threadfence();
+        agent_writes_done();
         int prev = 0;
         if (lane == 0) prev = atomicAdd(&tile_done[t], 1);
         prev = __shfl(prev, 0, 64);
         if (prev == nch - 1) {
-          __threadfence();
+          agent_writes_done();
           if (lane_writes) {
             const int64_t p0 = partial_off[t] * T;
 #pragma unroll
@@ -860,126 +870,127 @@ __global__ __launch_bounds__(256) void k_eval(
         }
       }
     };
-    if (mode == kModeLists) {
-      const int64_t lb = leaf_off[t] + (int64_t)c * chunk_leaves;
-      const int64_t le = min(lb + chunk_leaves, leaf_off[t] + cnt);
+    // Where the ids of a tile's leaves come from: its list, or, when the list
+    // did not fit, the hierarchy, walked in list order. The walk is a
+    // generator, a step of which tests one node's up to 64 children and puts
+    // the leaves among them into a ring; so both feed the same loop, and the
+    // kernel holds one copy of the evaluation (three took more registers than
+    // three wavefronts a SIMD leave).
+    const bool listed = mode == kModeLists;
+    const int64_t list0 = listed ? leaf_off[t] : 0;
+    int32_t* ring = lds_walk[wave];
+    int walked = 0, sp = 0, level = tv.n_levels - 1, first = 0, width = tv.level_cnt[level];
+    auto walk_step = [&]() __attribute__((always_inline)) {
+      const int child = first + lane;
+      bool pass = false;
+      // the tile's geometry is looked up again: kept, it would take registers
+      // from the evaluation, which runs far more often
+      int tt = t;
+      asm volatile("" : "+s"(tt));
+      const TileGeo gw = tile_geo<TX, TY, TZ>(rois, n_rois, coords, tt);
+      if (lane < width) {
+        const int gi = tv.level_off[level] + child;
+        pass = tile_box_test(tv, rois[gw.r], gw, tv.nodes[gi], gi);
+      }
+      const uint64_t m = ballot(pass);
+      const int np = popc64(m), r = popc64(m & lanemask_lt());
+      const bool leaf = level == 0;
+      if (pass) {
+        if (leaf)
+          ring[(walked + r) & (kWalkRing - 1)] = child;
+        else
+          lds_stack[wave][sp + np - 1 - r] = ((level - 1) << 27) | child;
+      }
+      walked += leaf ? np : 0;
+      sp += leaf ? 0 : np;
+      wave_sync();
+      if (sp == 0) {
+        walked = cnt;  // the end (all cnt leaves were met)
+        return;
+      }
+      const int e = wave_uniform(lds_stack[wave][--sp]);
+      level = e >> 27;
+      first = (e & ((1 << 27) - 1)) * SFK_FANOUT;
+      width = min(SFK_FANOUT, tv.level_cnt[level] - first);
+    };
+    // The work item's chunks: one, or all of the tile's when neither the list
+    // nor the partial slots fit.
+    const bool whole = mode == kModeWalkTile;
+    double dacc[NPL];
+#pragma unroll
+    for (int m = 0; m < NPL; ++m) dacc[m] = 0.0;
+    for (int cc = whole ? 0 : c; cc < (whole ? nch : c + 1); ++cc) {
+      const int lb = cc * chunk_leaves, le = min(lb + chunk_leaves, cnt);
+#pragma unroll
+      for (int q = 0; q < T; ++q) acc[q] = (Acc)0;
+      // Ids of leaves [i, i + 64) of the tile, one a lane; past the chunk's
+      // end its last leaf stands, culled as empty. A list entry that is not a
+      // leaf of the tree is an internal error: flag it and read leaf 0
+      // instead (never out of bounds).
+      auto load_ids = [&](int i) __attribute__((always_inline)) {
+        const int at = min(i + lane, le - 1);
+        if (!listed) {
+          while (walked < min(i + 64, le)) walk_step();
+          return ring[at & (kWalkRing - 1)];
+        }
+        const int v = leaves[list0 + at];
+        const bool bad = (unsigned)v >= (unsigned)tv.n_leaves;
+        if (bad) claims[kErrWord] = 1;
+        return bad ? 0 : v;
+      };
       // Software pipeline over NB particle buffers: a buffer is refilled
       // with the leaf NB places ahead as soon as it has been culled, so
       // NB - 1 leaves are in flight during each cull; the loop is unrolled
       // over the buffers so that no register is copied while its load is
-      // pending. The leaf ids of a block of the chunk are staged in LDS
-      // first, so reading them never waits on the particle loads.
-      for (int64_t b0 = lb; b0 < le; b0 += kIdBlock) {
-        const int n = (int)min((int64_t)kIdBlock, le - b0);
-        // a list entry that is not a leaf of the tree is an internal error:
-        // flag it and read leaf 0 instead (never out of bounds)
-        bool bad = false;
-        for (int i = lane; i < n; i += 64) {
-          int v = leaves[b0 + i];
-          if ((unsigned)v >= (unsigned)tv.n_leaves) {
-            bad = true;
-            v = 0;
-          }
-          ids[i] = v;
-        }
-        if (bad) claims[kErrWord] = 1;
-        wave_sync();
-        // Every buffer is refilled unconditionally (past the end with the
-        // block's last leaf, culled as empty), which keeps the count of
-        // loads in flight the same on every path through the loop.
-        float4 pb[NB], ab[NB];
+      // pending. The next 64 ids are loaded while 64 are worked on, so
+      // reading an id never waits.
+      float4 pb[NB], ab[NB];
 #pragma unroll
-        for (int u = 0; u < NB; ++u) {
-          pb[u] = ab[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-          fetch(__builtin_amdgcn_readfirstlane(ids[min(u, n - 1)]), pb[u], ab[u]);
-          // keep buffer order = issue order (the oldest load is consumed first)
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        for (int i = 0; i < n; i += NB) {
-          // appends only need to be visible to the drain: one visibility
-          // point per round lets the compiler overlap consecutive culls
+      for (int u = 0; u < NB; ++u) pb[u] = ab[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      int next = 0;
+      for (int b0 = lb - 64; b0 < le; b0 += 64) {
+        const int ids = next;
+        next = load_ids(b0 + 64);
+        if (b0 < lb) {  // nothing held yet: start the pipeline
 #pragma unroll
           for (int u = 0; u < NB; ++u) {
-            push(pb[u], ab[u], i + u < n && keep_of(pb[u], ab[u]));
-            fetch(__builtin_amdgcn_readfirstlane(ids[min(i + u + NB, n - 1)]), pb[u], ab[u]);
+            fetch(__builtin_amdgcn_readlane(next, u), pb[u], ab[u]);
+            // keep buffer order = issue order (the oldest load is consumed first)
+            __builtin_amdgcn_sched_barrier(0);
           }
-          wave_sync();
-          while (qn >= 64) drain64();
+          continue;
         }
-        wave_sync();
-      }
-      end_chunk();
-      finish_chunk();
-    } else if (mode == kModeWalkChunk) {
-      // the list did not fit: walk the hierarchy and evaluate the leaves of
-      // this chunk (walk order = list order), stopping after its last one
-      const int start = c * chunk_leaves, stop = min(start + chunk_leaves, cnt);
-      int done = 0;
-      traverse_until(
-          tv, lds_stack[wave],
-          [&](const NodeBox& b, int gidx) { return tile_box_test(tv, R, g, b, gidx); },
-          [&](int child, bool pass, uint64_t mask) {
-            (void)pass;
-            const int np = popc64(mask);
-            if (done + np <= start) {
-              done += np;
-              return true;
+        const int m = min(64, le - b0);
+        for (int i = 0; i < m; i += NB) {
+          // the last round's refills are the next 64's first
+          const int src = i + NB < 64 ? ids : next;
+          const int at = (i + NB) & 63;
+#pragma unroll
+          for (int u = 0; u < NB; u += 2) {
+            // appends only need to be visible to the drain: one visibility
+            // point for two leaves lets the compiler overlap their culls
+#pragma unroll
+            for (int w = u; w < u + 2; ++w) {
+              push(pb[w], ab[w], i + w < m && keep_of(pb[w], ab[w]));
+              fetch(__builtin_amdgcn_readlane(src, at + w), pb[w], ab[w]);
             }
-            uint64_t mm = mask;
-            while (mm && done < stop) {
-              const int b = __ffsll((unsigned long long)mm) - 1;
-              mm &= mm - 1;
-              if (done >= start) eval_leaf(__shfl(child, b, 64));
-              ++done;
-            }
-            return done < stop;
-          });
-      end_chunk();
-      finish_chunk();
-    } else {
-      // neither list nor partial slots fit: one work item walks the
-      // hierarchy with the same leaf order and the same chunk boundaries
-      double dacc[NPL];
-#pragma unroll
-      for (int m = 0; m < NPL; ++m) dacc[m] = 0.0;
-      int done = 0;
-      traverse(
-          tv, lds_stack[wave],
-          [&](const NodeBox& b, int gidx) { return tile_box_test(tv, R, g, b, gidx); },
-          [&](int child, bool pass, uint64_t mask) {
-            (void)pass;
-            uint64_t mm = mask;
-            while (mm) {
-              const int b = __ffsll((unsigned long long)mm) - 1;
-              mm &= mm - 1;
-              eval_leaf(__shfl(child, b, 64));
-              ++done;
-              if (nch > 1 && done % chunk_leaves == 0) {
-                end_chunk();
-#pragma unroll
-                for (int m = 0; m < NPL; ++m) dacc[m] += (double)acc[m];
-#pragma unroll
-                for (int q = 0; q < T; ++q) acc[q] = (Acc)0;
-              }
-            }
-          });
-      if (nch == 1) {
-        end_chunk();
-        if (lane_writes) {
-#pragma unroll
-          for (int m = 0; m < NPL; ++m) node_out(lane_node(m), (double)acc[m] * R.scale);
-        }
-      } else {
-        if (done % chunk_leaves != 0) {
-          end_chunk();
-#pragma unroll
-          for (int m = 0; m < NPL; ++m) dacc[m] += (double)acc[m];
-        }
-        if (lane_writes) {
-#pragma unroll
-          for (int m = 0; m < NPL; ++m) node_out(lane_node(m), dacc[m] * R.scale);
+            wave_sync();
+            if (u + 2 == NB && b0 + i + NB >= le) pad64();  // the chunk's end
+            while (qn >= 64) drain64();
+          }
         }
       }
+      reduce_nodes(acc);
+      if (whole && nch > 1) {
+#pragma unroll
+        for (int m = 0; m < NPL; ++m) dacc[m] += (double)acc[m];
+      }
+    }
+    if (!whole || nch == 1) {
+      finish_chunk();
+    } else if (lane_writes) {
+#pragma unroll
+      for (int m = 0; m < NPL; ++m) node_out(lane_node(m), dacc[m] * R.scale);
     }
   }
 }
@@ -1080,7 +1091,7 @@ __global__ __launch_bounds__(256) void k_splat(
     __syncthreads();
     const int64_t item = lds_item;
     if (item < 0) break;
-    const int t = item_tile[item];
+    const int t = wave_uniform(item_tile[item]);
     const TileGeo g = tile_geo<B, B, B>(rois, n_rois, coords, t);
     const RoiDev& R = rois[g.r];
     const int n_here[3] = {min(B, R.res[0] - g.i0), min(B, R.res[1] - g.j0),
@@ -1285,12 +1296,12 @@ __global__ __launch_bounds__(256) void k_splat(
       unsigned long long* slot = gsum + partial_off[t] * (int64_t)T;
       for (int n = threadIdx.x; n < T; n += 256)
         if (sums[n]) atomicAdd(&slot[n], sums[n]);
-      __threadfence();
+      agent_writes_done();
       __syncthreads();
       if (threadIdx.x == 0) lds_last = atomicAdd(&tile_done[t], 1) == nch - 1 ? 1 : 0;
       __syncthreads();
       if (lds_last) {
-        __threadfence();
+        agent_writes_done();
         for (int n = threadIdx.x; n < T; n += 256)
           write_node(n, __hip_atomic_load(&slot[n], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
       }

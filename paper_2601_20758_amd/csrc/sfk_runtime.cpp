@@ -624,8 +624,26 @@ int sweep_nm(const GroupRoi& g) {
   return nm;
 }
 
-int chunk_leaves_of(sfk_ctx c) {
-  return c->opts.chunk_leaves > 0 ? c->opts.chunk_leaves : kDefaultChunkLeaves;
+// Leaves per work item of a ROI of `tiles` tiles. Bricks add integer sums, so
+// their chunks are a matter of speed alone. The other shapes add a chunk's
+// terms in float and the chunks in double, so the chunk may only depend on
+// the ROI, not on its batch. Below 16384 tiles there are few work items per
+// resident wavefront (3072 on 256 CUs) and the densest tile's chunk is the
+// last to end: 442k points at 64^3 (4096 tiles) take 465 us with 32 leaves,
+// 510 with 64, 590 with 128 and 640 with 256 (MBE, both grids), 1M per-point
+// at 101x87x93 242, 252, 293 and 381. From there on each chunk's partial sums
+// and hand-over weigh as much: 128^3 takes 2.06 ms with 32 leaves, 1.93 with
+// 64, 1.91 with 128 and 1.99 with 256, which needs the fewest slots.
+int chunk_leaves_of(sfk_ctx c, TileShape ts, int64_t tiles) {
+  if (c->opts.chunk_leaves > 0) return c->opts.chunk_leaves;
+  if (sfk::is_brick(ts) || sfk::is_sweep(ts)) return kDefaultChunkLeaves;
+  return tiles < 16384 ? 32 : kDefaultChunkLeaves;
+}
+int chunk_leaves_of(sfk_ctx c, TileShape ts, const sfk_roi* r) {
+  const int32_t t[3] = {ts.tx, ts.ty, ts.tz};
+  int64_t tiles = 1;
+  for (int k = 0; k < 3; ++k) tiles *= (r->res[k] + t[k] - 1) / t[k];
+  return chunk_leaves_of(c, ts, tiles);
 }
 
 // Fill RoiDev descriptors for rois[0..n) and the per-group tile total.
@@ -690,8 +708,8 @@ int32_t slot_cap_of(TileShape ts) {
 // first call; overflowing batches still complete (walk fallback) and grow
 // the capacities for the next one.
 sfk_status reserve_group(sfk_ctx c, Workspace& ws, TileShape ts, int64_t n_rois, int64_t n_tiles,
-                         int64_t n_coords, double headroom, int64_t tree_leaves, Caps* caps) {
-  const int CH = chunk_leaves_of(c);
+                         int64_t n_coords, double headroom, int64_t tree_leaves, int CH,
+                         hipStream_t s, Caps* caps) {
   const int T = ts.tx * ts.ty * ts.tz;
   const int64_t tiles = (int64_t)std::ceil((double)n_tiles * headroom);
   const int64_t nr = std::max<int64_t>(64, (int64_t)std::ceil((double)n_rois * headroom));
@@ -703,13 +721,19 @@ sfk_status reserve_group(sfk_ctx c, Workspace& ws, TileShape ts, int64_t n_rois,
   // its heavy tiles over work items (walking per chunk)
   const bool brick = sfk::is_brick(ts);
   const bool sweep = sfk::is_sweep(ts);
+  const bool chosen = c->opts.chunk_leaves > 0;
   // a brick's partial slot holds its kBrick^3 node sums (32 KB): one per
   // split brick, up to 8192 of them; bricks beyond walk their whole tile in
   // one work item (which needs no slot)
   int64_t partial_cap =
       brick ? std::max<int64_t>(64, std::min<int64_t>(tiles, 8192))
             : std::max<int64_t>({ws.want_partial_cap, (int64_t)1 << 14, tiles / 4,
-                                 2 * leaf_cap / CH});
+                                 2 * leaf_cap / (chosen ? CH : kDefaultChunkLeaves)});
+  // the shorter default chunks need more slots: up to eight a tile, unless the
+  // caller budgets the memory (tiles without slots walk their chunks in one
+  // item, to the same sums)
+  if (!brick && !chosen && !c->budget)
+    partial_cap = std::max(partial_cap, std::min<int64_t>(8 * tiles, 2 * leaf_cap / CH));
   // the sweep: the node sums of every tile, and the (ROI, box) items of
   // every descriptor the header may hold (two int32 per item)
   const int64_t sweep_boxes = tree_leaves > SFK_FANOUT
@@ -741,8 +765,7 @@ sfk_status reserve_group(sfk_ctx c, Workspace& ws, TileShape ts, int64_t n_rois,
   SFK_TRY(ws_reserve(c, ws, ws.claims, kClaimBytes, "work-claim counters"));
   if (ws.claims_cleared != ws.claims.p) {
     // a new buffer: its error word starts at zero (no kernel clears it)
-    SFK_HIP(c, hipMemsetAsync(ws.claims.p, 0, ws.claims.bytes, nullptr));
-    SFK_HIP(c, hipStreamSynchronize(nullptr));
+    SFK_HIP(c, sfk::launch_fill_f32((float*)ws.claims.p, (int64_t)(ws.claims.bytes / 4), 0.0f, s));
     ws.claims_cleared = ws.claims.p;
   }
   SFK_TRY(ws_reserve(c, ws, ws.roi_leaves, sizeof(int32_t) * kRoiListCap * (size_t)nr,
@@ -804,7 +827,7 @@ BatchHdr make_hdr(sfk_ctx c, const Caps& k, int64_t n_rois, int64_t n_tiles) {
 // tile and plan grids (exact for direct launches, the capacities for a
 // captured graph).
 sfk_status launch_kernels(sfk_ctx c, const TreeView& tv, TileShape ts, int kk, int pp, bool cnt,
-                          Workspace& ws, int roi_grid, int64_t max_tiles, hipStream_t s,
+                          Workspace& ws, int roi_grid, int64_t max_tiles, int CH, hipStream_t s,
                           int nm = 0) {
   if (sfk::is_sweep(ts)) {
     BatchHdr* hdr = (BatchHdr*)ws.hdr_rois.p;
@@ -828,7 +851,6 @@ sfk_status launch_kernels(sfk_ctx c, const TreeView& tv, TileShape ts, int kk, i
     return SFK_OK;
   }
   const int tile_grid = sfk::tile_grid_blocks(max_tiles);
-  const int CH = chunk_leaves_of(c);
   BatchHdr* hdr = (BatchHdr*)ws.hdr_rois.p;
   const RoiDev* rois = (const RoiDev*)((char*)ws.hdr_rois.p + sizeof(BatchHdr));
   double* coords = (double*)ws.coords.p;
@@ -921,9 +943,10 @@ struct GroupKey {
   int kk, pp;
   TileShape ts;
   int nm;  // particle sweep: nodes per axis a support spans (0 otherwise)
+  int ch;  // leaves per work item
   bool operator==(const GroupKey& o) const {
     return kk == o.kk && pp == o.pp && ts.tx == o.ts.tx && ts.ty == o.ts.ty &&
-           ts.tz == o.ts.tz && nm == o.nm;
+           ts.tz == o.ts.tz && nm == o.nm && ch == o.ch;
   }
 };
 
@@ -935,7 +958,8 @@ void group_rois(sfk_ctx c, sfk_tree t, const std::vector<const sfk_roi*>& rois, 
   for (const sfk_roi* r : rois) {
     GroupRoi g = resolve_cloud_roi(t, r, count_mode);
     const TileShape ts = force_ts ? *force_ts : choose_shape(c, t, r);
-    const GroupKey key{count_mode ? 0 : g.kk, g.pp, ts, sfk::is_sweep(ts) ? sweep_nm(g) : 0};
+    const GroupKey key{count_mode ? 0 : g.kk, g.pp, ts, sfk::is_sweep(ts) ? sweep_nm(g) : 0,
+                       chunk_leaves_of(c, ts, r)};
     size_t gi = 0;
     while (gi < keys->size() && !((*keys)[gi] == key)) ++gi;
     if (gi == keys->size()) {
@@ -982,7 +1006,8 @@ sfk_status enqueue_groups(sfk_ctx c, sfk_tree t, std::vector<std::vector<GroupRo
     int64_t n_coords = 0;
     make_roidev(groups[gi], keys[gi].ts, rd, &tiles[gi], &n_coords);
     Caps k;
-    SFK_TRY(reserve_group(c, ws, keys[gi].ts, n, tiles[gi], n_coords, 1.0, t->n_leaves, &k));
+    SFK_TRY(reserve_group(c, ws, keys[gi].ts, n, tiles[gi], n_coords, 1.0, t->n_leaves,
+                          keys[gi].ch, s, &k));
     *(BatchHdr*)(st.host + off) = make_hdr(c, k, n, tiles[gi]);
     off += sizeof(BatchHdr) + sizeof(RoiDev) * (size_t)n;
   }
@@ -992,7 +1017,7 @@ sfk_status enqueue_groups(sfk_ctx c, sfk_tree t, std::vector<std::vector<GroupRo
     const size_t gb = sizeof(BatchHdr) + sizeof(RoiDev) * (size_t)n;
     SFK_HIP(c, hipMemcpyAsync(ws.hdr_rois.p, st.host + off, gb, hipMemcpyHostToDevice, s));
     SFK_TRY(launch_kernels(c, tv, keys[gi].ts, keys[gi].kk, keys[gi].pp, count_mode, ws, (int)n,
-                           tiles[gi], s, keys[gi].nm));
+                           tiles[gi], keys[gi].ch, s, keys[gi].nm));
     off += gb;
   }
   SFK_HIP(c, hipMemcpyAsync(st.hdr_host, ws.hdr_rois.p, sizeof(BatchHdr), hipMemcpyDeviceToHost, s));
@@ -1020,7 +1045,7 @@ sfk_status enqueue_cloud_rois_graph(sfk_ctx c, sfk_tree t,
   if (groups.size() != 1) return enqueue_groups(c, t, groups, keys, false, sl.ws, sl.st, sl.stream);
   const int64_t n = (int64_t)groups[0].size();
   const TileShape ts = keys[0].ts;
-  const int kk = keys[0].kk, pp = keys[0].pp, ch = chunk_leaves_of(c), nm = keys[0].nm;
+  const int kk = keys[0].kk, pp = keys[0].pp, ch = keys[0].ch, nm = keys[0].nm;
   std::vector<RoiDev> rd((size_t)n);
   int64_t n_tiles = 0, n_coords = 0;
   make_roidev(groups[0], ts, rd.data(), &n_tiles, &n_coords);
@@ -1034,12 +1059,12 @@ sfk_status enqueue_cloud_rois_graph(sfk_ctx c, sfk_tree t,
   Caps k;
   if (!fits) {
     drop_graph(gc);
-    SFK_TRY(reserve_group(c, sl.ws, ts, n, n_tiles, n_coords, 2.0, t->n_leaves, &k));
+    SFK_TRY(reserve_group(c, sl.ws, ts, n, n_tiles, n_coords, 2.0, t->n_leaves, ch, sl.stream, &k));
   } else {
-    SFK_TRY(reserve_group(c, sl.ws, ts, n, n_tiles, n_coords, 1.0, t->n_leaves, &k));
+    SFK_TRY(reserve_group(c, sl.ws, ts, n, n_tiles, n_coords, 1.0, t->n_leaves, ch, sl.stream, &k));
     if (sl.ws.gen != gc.gen) {  // a buffer moved after all
       drop_graph(gc);
-      SFK_TRY(reserve_group(c, sl.ws, ts, n, n_tiles, n_coords, 2.0, t->n_leaves, &k));
+      SFK_TRY(reserve_group(c, sl.ws, ts, n, n_tiles, n_coords, 2.0, t->n_leaves, ch, sl.stream, &k));
     }
   }
   const size_t full = sizeof(BatchHdr) + sizeof(RoiDev) * (size_t)k.rois_cap;
@@ -1059,7 +1084,7 @@ sfk_status enqueue_cloud_rois_graph(sfk_ctx c, sfk_tree t,
       st = SFK_E_DEVICE;
     if (st == SFK_OK)
       st = launch_kernels(c, view_of(t), ts, kk, pp, false, sl.ws, (int)k.rois_cap, k.tiles_cap,
-                          s, nm);
+                          ch, s, nm);
     if (st == SFK_OK && hipMemcpyAsync(sl.st.hdr_host, sl.ws.hdr_rois.p, sizeof(BatchHdr),
                                        hipMemcpyDeviceToHost, s) != hipSuccess)
       st = SFK_E_DEVICE;
@@ -1251,13 +1276,14 @@ sfk_status eval_subcloud(sfk_ctx c, sfk_tree t, const sfk_roi* r, bool count_mod
     int64_t n_tiles = 0, n_coords = 0;
     make_roidev(v, ts, (RoiDev*)(st.host + sizeof(BatchHdr)), &n_tiles, &n_coords);
     Caps k;
-    SFK_TRY(reserve_group(c, ws, ts, 1, n_tiles, n_coords, 1.0, tv.n_leaves, &k));
+    const int ch = chunk_leaves_of(c, ts, n_tiles);
+    SFK_TRY(reserve_group(c, ws, ts, 1, n_tiles, n_coords, 1.0, tv.n_leaves, ch, s, &k));
     *(BatchHdr*)st.host = make_hdr(c, k, 1, n_tiles);
     SFK_HIP(c, hipMemcpyAsync(ws.hdr_rois.p, st.host, gb, hipMemcpyHostToDevice, s));
     SFK_HIP(c, hipEventRecord(st.ev, s));
     st.ev_valid = true;
     return launch_kernels(c, tv, ts, g.count_mode ? 0 : g.kk, g.pp, g.count_mode, ws, 1,
-                          n_tiles, s);
+                          n_tiles, ch, s);
   };
 
   if (!mbe) {
@@ -2303,7 +2329,8 @@ sfk_status sfk_eval_roi_noalloc(sfk_ctx c, sfk_tree t, const sfk_roi* roi, void*
       const bool prof = c->prof_on;
       c->prof_on = false;
       const sfk_status st =
-          launch_kernels(c, view_of(t), ts, g.kk, g.pp, false, wv, 1, n_tiles, s, sweep_nm(g));
+          launch_kernels(c, view_of(t), ts, g.kk, g.pp, false, wv, 1, n_tiles,
+                         kDefaultChunkLeaves, s, sweep_nm(g));
       c->prof_on = prof;
       SFK_TRY(st);
       SFK_HIP(c, hipEventRecord(c->na_ev[si], s));
@@ -2340,7 +2367,7 @@ sfk_status sfk_eval_roi_noalloc(sfk_ctx c, sfk_tree t, const sfk_roi* roi, void*
   // rest to leaf-list entries (for bricks, with one work item per
   // chunk_leaves entries); 4 x 256 bytes of rounding and item slack
   const bool brick = sfk::is_brick(ts);
-  const int CH = chunk_leaves_of(c);
+  const int CH = chunk_leaves_of(c, ts, n_tiles);
   const size_t rest = cap - fixed - rb(sizeof(int32_t) * (nt + 1)) - 4 * 256;
   const int64_t partial_cap =
       std::max<int64_t>(1, (int64_t)(rest / 4 / (sizeof(double) * T + sizeof(int32_t))));
@@ -2399,7 +2426,7 @@ sfk_status sfk_eval_roi_noalloc(sfk_ctx c, sfk_tree t, const sfk_roi* roi, void*
   // profiling events may be created on demand: none here
   const bool prof = c->prof_on;
   c->prof_on = false;
-  const sfk_status st = launch_kernels(c, view_of(t), ts, g.kk, g.pp, false, wv, 1, n_tiles, s);
+  const sfk_status st = launch_kernels(c, view_of(t), ts, g.kk, g.pp, false, wv, 1, n_tiles, CH, s);
   c->prof_on = prof;
   SFK_TRY(st);
   SFK_HIP(c, hipEventRecord(c->na_ev[si], s));
@@ -3740,9 +3767,9 @@ sfk_status sfk_view_frame(sfk_view v, const double lo[3], const double hi[3], fl
     return SFK_E_INVAL;
   }
   // blocks evaluated with another chunking would not be bitwise reproducible
-  if (chunk_leaves_of(c) != v->chunk_leaves) {
+  if (c->opts.chunk_leaves != v->chunk_leaves) {
     view_flush(v);
-    v->chunk_leaves = chunk_leaves_of(c);
+    v->chunk_leaves = c->opts.chunk_leaves;
   }
   FramePlan p;
   SFK_TRY(view_plan(v, lo, hi, &p));
