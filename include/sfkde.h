@@ -231,8 +231,10 @@ typedef struct {
                             its grids equal the bricks' bit for bit; uniform bandwidths
                             whose support spans at most 8 nodes per axis, others take
                             the default of their key without the sweep) */
-  int32_t chunk_leaves;  /* leaves per work item (heavy tiles are split), 0 = 256,
-                            or 32 for wavefront tiles of ROIs below 16384 tiles */
+  int32_t chunk_leaves;  /* leaves per work item (heavy tiles are split), 0 =
+                            automatic: 256,
+                            wavefront tiles of ROIs below 16384 tiles 32, bricks 64
+                            or, few of them over a small cloud, 8 */
   int32_t persistent_waves_per_cu; /* 0 = automatic */
   int32_t list_capacity; /* leaf-list entries per batch, 0 = automatic; tiles whose
                             lists do not fit walk the tree inside the evaluation

@@ -70,3 +70,21 @@ def test_chunk_classes_alone_and_mixed(ctx, torch, bw, kernel):
             assert np.array_equal(a, ctx.eval_roi(tree, r).cpu().numpy()), (kw, r.res)
     ctx.set_eval_opts()
     tree.close()
+
+
+@pytest.mark.parametrize("n", [1000, 2047 * 64, 2048 * 64])
+def test_brick_chunk_classes_bitwise(ctx, torch, n):
+    # few bricks over a small cloud take short chunks; 4 x 4 x 4 and 3 x 4 x 4
+    # bricks lie either side of the line, as do the two larger clouds
+    tree = ctx.build_tree(dev(torch, synth.clumpy_cloud(n, 8)))
+    for res in [(16, 16, 16), (48, 64, 50), (64, 64, 49), (64, 64, 64)]:
+        roi = Roi((0.05,) * 3, (0.95,) * 3, res, bw="fixed", h=(0.02,) * 3)
+        ctx.set_eval_opts(tile_shape=6)
+        a = ctx.eval_roi(tree, roi).cpu().numpy()
+        out = torch.empty(roi.n_nodes, device="cuda")
+        ctx.wait(ctx.submit(tree, [roi], [out]))
+        ctx.set_eval_opts(tile_shape=6, chunk_leaves=256)
+        b = ctx.eval_roi(tree, roi).cpu().numpy()
+        assert np.array_equal(a, b) and np.array_equal(a, out.cpu().numpy()), res
+    ctx.set_eval_opts()
+    tree.close()
