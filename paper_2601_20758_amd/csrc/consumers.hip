@@ -14,6 +14,7 @@
 // and the eight corner terms ((wx * wy) * wz) * value accumulated z-major,
 // then y, then x, so a threshold decision is the same as the definition's.
 #include <algorithm>
+#include <cmath>
 
 #include "sfk_device.h"
 
@@ -21,8 +22,9 @@ namespace sfk {
 
 struct GridGeom {
   double lo[3], hi[3];
+  double span[3], rcp[3];  // hi - lo; 1 / span
   int32_t res[3];
-  int32_t pad_;
+  int32_t exact_rcp;  // div_span may use rcp (see geom_of)
 };
 
 __device__ __forceinline__ bool in_closed_box(const GridGeom& g, float x, float y, float z) {
@@ -33,21 +35,50 @@ __device__ __forceinline__ bool in_closed_box(const GridGeom& g, float x, float 
   return true;
 }
 
+// a / span, correctly rounded, from the correctly rounded reciprocal: the
+// first correction leaves a quotient within an ulp, and one more from such a
+// quotient is the rounded quotient (Markstein 1990; the remainders are exact
+// while nothing over- or underflows, which geom_of checks). 5 instructions
+// for a division's 14 and its quarter-rate reciprocal.
+__device__ __forceinline__ double div_span(const GridGeom& g, int k, double a) {
+  if (!g.exact_rcp) return a / g.span[k];
+  double q = a * g.rcp[k];
+  q = fma(fma(-q, g.span[k], a), g.rcp[k], q);
+  return fma(fma(-q, g.span[k], a), g.rcp[k], q);
+}
+
+// two neighbouring nodes of a row, at any node's alignment
+struct __attribute__((packed, aligned(4))) NodePair {
+  float v[2];
+};
+
+// Bound by the gathers: a point's four rows are four 128-byte lines through the
+// CU's cache at 64 bytes a cycle: 10M points at random positions take 130 us,
+// the time of 40M lines at that rate. A row's two nodes come in one load.
 __device__ __forceinline__ double trilinear_at(const float* __restrict__ grid, const GridGeom& g,
                                                float x, float y, float z) {
   const double p[3] = {(double)x, (double)y, (double)z};
-  int c[3];
+  uint32_t c[3];
   double t[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    const double f = ((p[k] - g.lo[k]) * (double)(g.res[k] - 1)) / (g.hi[k] - g.lo[k]);
+    const double f = div_span(g, k, (p[k] - g.lo[k]) * (double)(g.res[k] - 1));
     int ci = (int)floor(f);
     ci = max(0, min(ci, g.res[k] - 2));
     double tt = f - (double)ci;
     tt = fmin(fmax(tt, 0.0), 1.0);
-    c[k] = ci;
+    c[k] = (uint32_t)ci;
     t[k] = tt;
   }
+  // node numbers stay below 2^31
+  const uint32_t rx = (uint32_t)g.res[0], plane = rx * (uint32_t)g.res[1];
+  const uint32_t idx = c[0] + rx * c[1] + plane * c[2];
+  NodePair v[2][2];
+#pragma unroll
+  for (int dz = 0; dz < 2; ++dz)
+#pragma unroll
+    for (int dy = 0; dy < 2; ++dy)
+      v[dz][dy] = *(const NodePair*)(grid + (idx + (dy ? rx : 0u) + (dz ? plane : 0u)));
   double acc = 0.0;
 #pragma unroll
   for (int dz = 0; dz < 2; ++dz)
@@ -57,10 +88,7 @@ __device__ __forceinline__ double trilinear_at(const float* __restrict__ grid, c
       for (int dx = 0; dx < 2; ++dx) {
         const double w = ((dx ? t[0] : 1.0 - t[0]) * (dy ? t[1] : 1.0 - t[1])) *
                          (dz ? t[2] : 1.0 - t[2]);
-        const int64_t idx =
-            (int64_t)(c[0] + dx) +
-            (int64_t)g.res[0] * ((int64_t)(c[1] + dy) + (int64_t)g.res[1] * (int64_t)(c[2] + dz));
-        acc += w * (double)grid[idx];
+        acc += w * (double)v[dz][dy].v[dx];
       }
   return acc;
 }
@@ -76,59 +104,116 @@ __global__ __launch_bounds__(256) void k_sample(const float* __restrict__ grid, 
   }
 }
 
-// 1 where the point lies in the closed box and its density is >= iso
-__global__ __launch_bounds__(256) void k_select_flags(const float* __restrict__ grid, GridGeom g,
-                                                      double iso, const float* __restrict__ xyz,
-                                                      int64_t n, int32_t* __restrict__ flags) {
-  for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n;
-       j += (int64_t)gridDim.x * blockDim.x) {
-    const float x = xyz[3 * j], y = xyz[3 * j + 1], z = xyz[3 * j + 2];
-    flags[j] = (in_closed_box(g, x, y, z) && trilinear_at(grid, g, x, y, z) >= iso) ? 1 : 0;
+// ---- ordered selections ----
+//
+// Entries that pass a test, in ascending order, in three steps: a workgroup
+// tests kSelTile entries and keeps one bit of each and their number; the
+// numbers are scanned; a workgroup writes its tile's entries at its offset.
+// 1/8 byte an entry goes through memory between the steps, where a flag, a
+// 64-bit position and the scan's passes over both took 44: beside the test
+// (130 us for 10M points at random positions in a 128^3 grid) the selection
+// takes 20 us, and took 140.
+static constexpr int kSelWords = kSelTileWords, kSelTile = kSelWords * 64,
+                     kSelPerWave = kSelWords / 4;
+
+int64_t select_tiles(int64_t n) { return (n + kSelTile - 1) / kSelTile; }
+
+// the tile's sum of each wavefront's value (the same in all its lanes)
+__device__ __forceinline__ void tile_total(int v, int64_t* __restrict__ sums) {
+  __shared__ int part[4];
+  if (lane_id() == 0) part[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) sums[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
+}
+
+// lane l's exclusive prefix of the tile's 32 words' bit counts (l < 32)
+__device__ __forceinline__ int word_prefix(uint64_t word) {
+  const int c = popc64(word);
+  return wave_incl_scan(c) - c;
+}
+
+// bit: the point lies in the closed box and its density is >= iso
+__global__ __launch_bounds__(256) void k_select_mask(const float* __restrict__ grid, GridGeom g,
+                                                     double iso, const float* __restrict__ xyz,
+                                                     int64_t n, uint64_t* __restrict__ mask,
+                                                     int64_t* __restrict__ sums) {
+  const int64_t w0 = (int64_t)blockIdx.x * kSelWords + (threadIdx.x >> 6) * kSelPerWave;
+  int c = 0;
+#pragma unroll 2
+  for (int w = 0; w < kSelPerWave; ++w) {
+    const int64_t j = (w0 + w) * 64 + lane_id();
+    bool in = false;
+    if (j < n) {
+      const float x = xyz[3 * j], y = xyz[3 * j + 1], z = xyz[3 * j + 2];
+      in = in_closed_box(g, x, y, z) && trilinear_at(grid, g, x, y, z) >= iso;
+    }
+    const uint64_t m = ballot(in);
+    c += popc64(m);
+    if (lane_id() == 0) mask[w0 + w] = m;
+  }
+  tile_total(c, sums);
+}
+
+// ascending indices of the set bits (the first `cap` of them)
+__global__ __launch_bounds__(256) void k_select_write(const uint64_t* __restrict__ mask,
+                                                      const int64_t* __restrict__ offs,
+                                                      int64_t* __restrict__ idx, int64_t cap) {
+  const int64_t w0 = (int64_t)blockIdx.x * kSelWords, base = offs[blockIdx.x];
+  if (base >= cap) return;
+  const int lane = lane_id(), first = (threadIdx.x >> 6) * kSelPerWave;
+  const uint64_t word = lane < kSelWords ? mask[w0 + lane] : 0;
+  const int pre = word_prefix(word);
+  for (int w = first; w < first + kSelPerWave; ++w) {
+    const uint64_t m = __shfl((unsigned long long)word, w, 64);
+    const int64_t at = base + __shfl(pre, w, 64) + popc64(m & lanemask_lt());
+    if (((m >> lane) & 1) && at < cap) idx[at] = (w0 + w) * 64 + lane;
   }
 }
 
-// ascending indices of the flagged entries (the first `cap` of them)
-__global__ __launch_bounds__(256) void k_compact_index(const int32_t* __restrict__ flags,
-                                                       const int64_t* __restrict__ pos, int64_t n,
-                                                       int64_t* __restrict__ idx, int64_t cap) {
-  for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n;
-       j += (int64_t)gridDim.x * blockDim.x)
-    if (flags[j] && pos[j] < cap) idx[pos[j]] = j;
-}
-
-// Marching Cubes case of every cell (bit dx + 2 dy + 4 dz set when that
-// corner's value is >= iso); flag = case not in {0, 255}
-__global__ __launch_bounds__(256) void k_iso_flags(const float* __restrict__ grid, GridGeom g,
-                                                   double iso, int64_t n_cells,
-                                                   int32_t* __restrict__ flags,
-                                                   uint8_t* __restrict__ case_all) {
-  const int64_t cx = g.res[0] - 1, cy = g.res[1] - 1;
-  for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n_cells;
-       q += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = q % cx, j = (q / cx) % cy, k = q / (cx * cy);
-    int cs = 0;
+// Marching Cubes case of a cell: bit dx + 2 dy + 4 dz set when that corner's
+// value is >= iso
+__device__ __forceinline__ int mc_case_at(const float* __restrict__ grid, const GridGeom& g,
+                                          double iso, uint32_t i, uint32_t j, uint32_t k) {
+  const uint32_t rx = (uint32_t)g.res[0], plane = rx * (uint32_t)g.res[1];
+  const uint32_t idx = i + rx * j + plane * k;
+  int cs = 0;
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const int dx = b & 1, dy = (b >> 1) & 1, dz = (b >> 2) & 1;
-      const double v = (double)grid[(i + dx) + (int64_t)g.res[0] * ((j + dy) + (int64_t)g.res[1] * (k + dz))];
-      if (v >= iso) cs |= 1 << b;
-    }
-    case_all[q] = (uint8_t)cs;
-    flags[q] = (cs != 0 && cs != 255) ? 1 : 0;
+  for (int r = 0; r < 4; ++r) {
+    const NodePair v = *(const NodePair*)(grid + (idx + ((r & 1) ? rx : 0u) + ((r & 2) ? plane : 0u)));
+    if ((double)v.v[0] >= iso) cs |= 1 << (2 * r);
+    if ((double)v.v[1] >= iso) cs |= 2 << (2 * r);
   }
+  return cs;
 }
 
-__global__ __launch_bounds__(256) void k_compact_cells(const int32_t* __restrict__ flags,
-                                                       const int64_t* __restrict__ pos,
-                                                       const uint8_t* __restrict__ case_all,
-                                                       int64_t n, int64_t* __restrict__ cells,
-                                                       uint8_t* __restrict__ cases, int64_t cap) {
-  for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n;
-       q += (int64_t)gridDim.x * blockDim.x)
-    if (flags[q] && pos[q] < cap) {
-      cells[pos[q]] = q;
-      cases[pos[q]] = case_all[q];
+// cell q's coordinates (cells stay below 2^31)
+__device__ __forceinline__ void cell_at(const GridGeom& g, uint32_t q, uint32_t c[3]) {
+  const uint32_t cx = (uint32_t)g.res[0] - 1, cy = (uint32_t)g.res[1] - 1;
+  const uint32_t row = q / cx;
+  c[0] = q - row * cx;
+  c[2] = row / cy;
+  c[1] = row - c[2] * cy;
+}
+
+__global__ __launch_bounds__(256) void k_cells_write(const uint64_t* __restrict__ mask,
+                                                     const int64_t* __restrict__ offs,
+                                                     const uint8_t* __restrict__ case_all,
+                                                     int64_t* __restrict__ cells,
+                                                     uint8_t* __restrict__ cases, int64_t cap) {
+  const int64_t w0 = (int64_t)blockIdx.x * kSelWords, base = offs[blockIdx.x];
+  if (base >= cap) return;
+  const int lane = lane_id(), first = (threadIdx.x >> 6) * kSelPerWave;
+  const uint64_t word = lane < kSelWords ? mask[w0 + lane] : 0;
+  const int pre = word_prefix(word);
+  for (int w = first; w < first + kSelPerWave; ++w) {
+    const uint64_t m = __shfl((unsigned long long)word, w, 64);
+    const int64_t at = base + __shfl(pre, w, 64) + popc64(m & lanemask_lt());
+    if (((m >> lane) & 1) && at < cap) {
+      const int64_t q = (w0 + w) * 64 + lane;
+      cells[at] = q;
+      cases[at] = case_all[q];
     }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -259,59 +344,114 @@ int mc_case_host(int cs, int8_t* edges) {
   return t.ntri[cs];
 }
 
-// triangles of each cell (from the cell's case)
-__global__ __launch_bounds__(256) void k_iso_tri_count(const uint8_t* __restrict__ case_all,
-                                                       int64_t n_cells,
-                                                       int32_t* __restrict__ cnt) {
-  for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n_cells;
-       q += (int64_t)gridDim.x * blockDim.x)
-    cnt[q] = kMcCases.ntri[case_all[q]];
+// Case of every cell; the mask of the cells whose case is neither 0 nor 255
+// and the tile's number of them or, with TRI, of their triangles.
+template <bool TRI>
+__global__ __launch_bounds__(256) void k_iso_mask(const float* __restrict__ grid, GridGeom g,
+                                                  double iso, int64_t n_cells,
+                                                  uint8_t* __restrict__ case_all,
+                                                  uint64_t* __restrict__ mask,
+                                                  int64_t* __restrict__ sums) {
+  const int64_t w0 = (int64_t)blockIdx.x * kSelWords + (threadIdx.x >> 6) * kSelPerWave;
+  int c = 0;
+#pragma unroll 2
+  for (int w = 0; w < kSelPerWave; ++w) {
+    const int64_t q = (w0 + w) * 64 + lane_id();
+    int cs = 0;
+    if (q < n_cells) {
+      uint32_t ci[3];
+      cell_at(g, (uint32_t)q, ci);
+      cs = mc_case_at(grid, g, iso, ci[0], ci[1], ci[2]);
+      case_all[q] = (uint8_t)cs;
+    }
+    const uint64_t m = ballot(cs != 0 && cs != 255);
+    if (lane_id() == 0) mask[w0 + w] = m;
+    if constexpr (TRI) {
+      if (m) c += wave_sum((int)kMcCases.ntri[cs]);
+    } else {
+      c += popc64(m);
+    }
+  }
+  tile_total(c, sums);
 }
 
 __device__ __forceinline__ double node_x(const GridGeom& g, int k, int64_t i) {
   return g.lo[k] + ((double)i * (g.hi[k] - g.lo[k])) / (double)(g.res[k] - 1);
 }
 
-// the triangles of every cell at their offsets (the first `cap` of them):
-// 9 floats each, three vertices (x, y, z)
-__global__ __launch_bounds__(256) void k_iso_emit(const float* __restrict__ grid, GridGeom g,
-                                                  double iso, const uint8_t* __restrict__ case_all,
-                                                  const int64_t* __restrict__ pos,
-                                                  int64_t n_cells, float* __restrict__ tris,
-                                                  int64_t cap) {
-  const int64_t cx = g.res[0] - 1, cy = g.res[1] - 1;
-  for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n_cells;
-       q += (int64_t)gridDim.x * blockDim.x) {
-    const int cs = case_all[q];
-    const int nt = kMcCases.ntri[cs];
-    if (nt == 0) continue;
-    const int64_t base = pos[q];
-    if (base >= cap) continue;
-    const int64_t ci[3] = {q % cx, (q / cx) % cy, q / (cx * cy)};
-    double f[8];
+// The triangles of every cell at their offsets (the first `cap` of them): 9
+// floats each, three vertices (x, y, z). A wavefront takes 64 cells, lists
+// their triangles (at most 5 a cell) in LDS and then gives each lane a vertex,
+// so the cells without triangles idle no lanes and the writes are contiguous.
+// Bound by the chain of loads of a word with triangles, hence two words a
+// wavefront: 30 us for the surface of a 128^3 grid, 33 with eight words, 82
+// with a lane per cell.
+static constexpr int kEmitWaves = 16, kEmitPerWave = kSelWords / kEmitWaves;
+
+__global__ __launch_bounds__(64 * kEmitWaves) void k_iso_emit(const float* __restrict__ grid, GridGeom g,
+                                                  double iso,
+                                                  const uint8_t* __restrict__ case_all,
+                                                  const uint64_t* __restrict__ mask,
+                                                  const int64_t* __restrict__ offs,
+                                                  float* __restrict__ tris, int64_t cap) {
+  __shared__ uint16_t list[kEmitWaves][64 * 5];  // cell << 3 | triangle
+  __shared__ uint8_t lcase[kEmitWaves][64];
+  __shared__ int before[kEmitWaves];
+  const int lane = lane_id(), wave = threadIdx.x >> 6;
+  const int64_t w0 = (int64_t)blockIdx.x * kSelWords + wave * kEmitPerWave;
+  if (offs[blockIdx.x] >= cap) return;
+  // the wavefront's place within the tile
+  int nt[kEmitPerWave], sum = 0;
+  uint8_t cs[kEmitPerWave];
 #pragma unroll
-    for (int c = 0; c < 8; ++c)
-      f[c] = (double)grid[(ci[0] + (c & 1)) +
-                          (int64_t)g.res[0] * ((ci[1] + ((c >> 1) & 1)) +
-                                               (int64_t)g.res[1] * (ci[2] + ((c >> 2) & 1)))];
-    for (int tr = 0; tr < nt && base + tr < cap; ++tr) {
-      float* out = tris + 9 * (base + tr);
-      for (int vtx = 0; vtx < 3; ++vtx) {
-        const int e = kMcCases.edge[cs][3 * tr + vtx];
-        const int axis = e >> 2, bits = e & 3;
-        // lower corner of the edge: its two other coordinates from the id
-        const int o0 = axis == 0 ? 1 : 0, o1 = axis == 2 ? 1 : 2;
-        const int p = ((bits & 1) << o0) | ((bits >> 1) << o1);
-        const int qc = p | (1 << axis);
-        const double t = (iso - f[p]) / (f[qc] - f[p]);
-        for (int d = 0; d < 3; ++d) {
-          const int64_t idx = ci[d] + ((p >> d) & 1);
-          double x = node_x(g, d, idx);
-          if (d == axis) x = x + t * (node_x(g, d, idx + 1) - x);
-          out[3 * vtx + d] = (float)x;
-        }
+  for (int w = 0; w < kEmitPerWave; ++w) {
+    const uint64_t m = mask[w0 + w];
+    cs[w] = ((m >> lane) & 1) ? case_all[(w0 + w) * 64 + lane] : (uint8_t)0;
+    nt[w] = kMcCases.ntri[cs[w]];
+    sum += nt[w];
+  }
+  sum = wave_sum(sum);
+  if (lane == 0) before[wave] = sum;
+  __syncthreads();
+  int64_t base = offs[blockIdx.x];
+  for (int w = 0; w < wave; ++w) base += before[w];
+  if (sum == 0) return;
+#pragma unroll
+  for (int w = 0; w < kEmitPerWave; ++w) {
+    const int inc = wave_incl_scan(nt[w]);
+    const int total = __builtin_amdgcn_readlane(inc, 63);
+    if (total == 0) continue;
+    wave_sync();  // the last word's readers are done
+    for (int tr = 0; tr < nt[w]; ++tr) list[wave][inc - nt[w] + tr] = (uint16_t)(lane << 3 | tr);
+    lcase[wave][lane] = cs[w];
+    wave_sync();
+    for (int v = lane; v < 3 * total; v += 64) {
+      const int tri = v / 3, vtx = v - 3 * tri;
+      const int64_t at = base + tri;
+      if (at >= cap) break;
+      const int cell = list[wave][tri] >> 3, tr = list[wave][tri] & 7;
+      uint32_t ci[3];
+      cell_at(g, (uint32_t)((w0 + w) * 64 + cell), ci);
+      const int e = kMcCases.edge[lcase[wave][cell]][3 * tr + vtx];
+      const int axis = e >> 2, bits = e & 3;
+      // lower corner of the edge: its two other coordinates from the id
+      const int o0 = axis == 0 ? 1 : 0, o1 = axis == 2 ? 1 : 2;
+      const int p = ((bits & 1) << o0) | ((bits >> 1) << o1);
+      const int64_t row = g.res[0], plane = row * g.res[1];
+      const float* f = grid + ((int64_t)(ci[0] + (p & 1)) + row * (int64_t)(ci[1] + ((p >> 1) & 1)) +
+                               plane * (int64_t)(ci[2] + (p >> 2)));
+      const double fp = (double)f[0], fq = (double)f[axis == 0 ? 1 : axis == 1 ? row : plane];
+      const double t = (iso - fp) / (fq - fp);
+      float* out = tris + 9 * at + 3 * vtx;
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        const int64_t idx = (int64_t)ci[d] + ((p >> d) & 1);
+        double x = node_x(g, d, idx);
+        if (d == axis) x = x + t * (node_x(g, d, idx + 1) - x);
+        out[d] = (float)x;
       }
     }
+    base += total;
   }
 }
 
@@ -395,10 +535,17 @@ __global__ __launch_bounds__(256) void k_brick_minmax(const BrickDesc* __restric
 
 static GridGeom geom_of(const double lo[3], const double hi[3], const int32_t res[3]) {
   GridGeom g{};
+  g.exact_rcp = 1;
+  // magnitudes for which no step of div_span over- or underflows: a numerator
+  // is a multiple of 2^-452 below 2^432
+  auto plain = [](double v) { return std::fabs(v) >= 0x1p-400 && std::fabs(v) <= 0x1p400; };
   for (int k = 0; k < 3; ++k) {
     g.lo[k] = lo[k];
     g.hi[k] = hi[k];
     g.res[k] = res[k];
+    g.span[k] = hi[k] - lo[k];
+    g.rcp[k] = 1.0 / g.span[k];
+    if (!plain(g.span[k]) || (lo[k] != 0.0 && !plain(lo[k]))) g.exact_rcp = 0;
   }
   return g;
 }
@@ -416,55 +563,54 @@ hipError_t launch_sample(const float* grid, const double lo[3], const double hi[
   return hipGetLastError();
 }
 
-hipError_t launch_select_flags(const float* grid, const double lo[3], const double hi[3],
-                               const int32_t res[3], double iso, const float* xyz, int64_t n,
-                               int32_t* flags, hipStream_t s) {
+hipError_t launch_select_mask(const float* grid, const double lo[3], const double hi[3],
+                              const int32_t res[3], double iso, const float* xyz, int64_t n,
+                              uint64_t* mask, int64_t* sums, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_select_flags, dim3(grid_of(n)), dim3(256), 0, s, grid,
-                     geom_of(lo, hi, res), iso, xyz, n, flags);
+  hipLaunchKernelGGL(k_select_mask, dim3((unsigned)select_tiles(n)), dim3(256), 0, s, grid,
+                     geom_of(lo, hi, res), iso, xyz, n, mask, sums);
   return hipGetLastError();
 }
 
-hipError_t launch_compact_index(const int32_t* flags, const int64_t* pos, int64_t n, int64_t* idx,
-                                int64_t cap, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_compact_index, dim3(grid_of(n)), dim3(256), 0, s, flags, pos, n, idx, cap);
+hipError_t launch_select_write(const uint64_t* mask, const int64_t* offs, int64_t n, int64_t* idx,
+                               int64_t cap, hipStream_t s) {
+  if (n <= 0 || cap <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_select_write, dim3((unsigned)select_tiles(n)), dim3(256), 0, s, mask, offs,
+                     idx, cap);
   return hipGetLastError();
 }
 
-hipError_t launch_iso_flags(const float* grid, const int32_t res[3], double iso, int64_t n_cells,
-                            int32_t* flags, uint8_t* case_all, hipStream_t s) {
+hipError_t launch_iso_mask(const float* grid, const int32_t res[3], double iso, int64_t n_cells,
+                           bool triangles, uint8_t* case_all, uint64_t* mask, int64_t* sums,
+                           hipStream_t s) {
   if (n_cells <= 0) return hipSuccess;
   const double z[3] = {0.0, 0.0, 0.0};
-  hipLaunchKernelGGL(k_iso_flags, dim3(grid_of(n_cells)), dim3(256), 0, s, grid,
-                     geom_of(z, z, res), iso, n_cells, flags, case_all);
+  const dim3 nb((unsigned)select_tiles(n_cells));
+  if (triangles)
+    hipLaunchKernelGGL((k_iso_mask<true>), nb, dim3(256), 0, s, grid, geom_of(z, z, res), iso,
+                       n_cells, case_all, mask, sums);
+  else
+    hipLaunchKernelGGL((k_iso_mask<false>), nb, dim3(256), 0, s, grid, geom_of(z, z, res), iso,
+                       n_cells, case_all, mask, sums);
   return hipGetLastError();
 }
 
-hipError_t launch_compact_cells(const int32_t* flags, const int64_t* pos, const uint8_t* case_all,
-                                int64_t n, int64_t* cells, uint8_t* cases, int64_t cap,
-                                hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_compact_cells, dim3(grid_of(n)), dim3(256), 0, s, flags, pos, case_all, n,
-                     cells, cases, cap);
-  return hipGetLastError();
-}
-
-hipError_t launch_iso_tri_count(const uint8_t* case_all, int64_t n_cells, int32_t* cnt,
-                                hipStream_t s) {
-  if (n_cells <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_iso_tri_count, dim3(grid_of(n_cells)), dim3(256), 0, s, case_all, n_cells,
-                     cnt);
+hipError_t launch_cells_write(const uint64_t* mask, const int64_t* offs, const uint8_t* case_all,
+                              int64_t n_cells, int64_t* cells, uint8_t* cases, int64_t cap,
+                              hipStream_t s) {
+  if (n_cells <= 0 || cap <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_cells_write, dim3((unsigned)select_tiles(n_cells)), dim3(256), 0, s, mask,
+                     offs, case_all, cells, cases, cap);
   return hipGetLastError();
 }
 
 hipError_t launch_iso_emit(const float* grid, const double lo[3], const double hi[3],
                            const int32_t res[3], double iso, const uint8_t* case_all,
-                           const int64_t* pos, int64_t n_cells, float* tris, int64_t cap,
-                           hipStream_t s) {
+                           const uint64_t* mask, const int64_t* offs, int64_t n_cells, float* tris,
+                           int64_t cap, hipStream_t s) {
   if (n_cells <= 0 || cap <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_iso_emit, dim3(grid_of(n_cells)), dim3(256), 0, s, grid,
-                     geom_of(lo, hi, res), iso, case_all, pos, n_cells, tris, cap);
+  hipLaunchKernelGGL(k_iso_emit, dim3((unsigned)select_tiles(n_cells)), dim3(64 * kEmitWaves), 0,
+                     s, grid, geom_of(lo, hi, res), iso, case_all, mask, offs, tris, cap);
   return hipGetLastError();
 }
 

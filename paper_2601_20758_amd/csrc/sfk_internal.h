@@ -142,32 +142,37 @@ hipError_t launch_view_gather(const float* cache, int64_t n_slots, int block, co
 hipError_t launch_sample(const float* grid, const double lo[3], const double hi[3],
                          const int32_t res[3], const float* xyz, int64_t n, float* out,
                          hipStream_t s);
-hipError_t launch_select_flags(const float* grid, const double lo[3], const double hi[3],
-                               const int32_t res[3], double iso, const float* xyz, int64_t n,
-                               int32_t* flags, hipStream_t s);
-hipError_t launch_compact_index(const int32_t* flags, const int64_t* pos, int64_t n, int64_t* idx,
-                                int64_t cap, hipStream_t s);
-hipError_t launch_iso_flags(const float* grid, const int32_t res[3], double iso, int64_t n_cells,
-                            int32_t* flags, uint8_t* case_all, hipStream_t s);
-hipError_t launch_compact_cells(const int32_t* flags, const int64_t* pos, const uint8_t* case_all,
-                                int64_t n, int64_t* cells, uint8_t* cases, int64_t cap,
-                                hipStream_t s);
-// Marching Cubes triangles: per-cell counts from the cases, then 9 floats per
-// triangle at the cells' exclusive-scan offsets (the first `cap` triangles)
+// Ordered selections: per tile of entries a mask (32 words) and a number, then,
+// from the numbers' exclusive scan (scan_sums_i64), the selected entries
+int64_t select_tiles(int64_t n);
+constexpr int kSelTileWords = 32;
+hipError_t launch_select_mask(const float* grid, const double lo[3], const double hi[3],
+                              const int32_t res[3], double iso, const float* xyz, int64_t n,
+                              uint64_t* mask, int64_t* sums, hipStream_t s);
+hipError_t launch_select_write(const uint64_t* mask, const int64_t* offs, int64_t n, int64_t* idx,
+                               int64_t cap, hipStream_t s);
+// every cell's case, and the tiles' numbers of cut cells or of triangles
+hipError_t launch_iso_mask(const float* grid, const int32_t res[3], double iso, int64_t n_cells,
+                           bool triangles, uint8_t* case_all, uint64_t* mask, int64_t* sums,
+                           hipStream_t s);
+hipError_t launch_cells_write(const uint64_t* mask, const int64_t* offs, const uint8_t* case_all,
+                              int64_t n_cells, int64_t* cells, uint8_t* cases, int64_t cap,
+                              hipStream_t s);
 // the Marching Cubes case table the kernels use, read on the host:
 // 3 * n edge ids of case cs, returns n
 int mc_case_host(int cs, int8_t* edges);
-hipError_t launch_iso_tri_count(const uint8_t* case_all, int64_t n_cells, int32_t* cnt,
-                                hipStream_t s);
+// Marching Cubes triangles: 9 floats each (the first `cap` of them)
 hipError_t launch_iso_emit(const float* grid, const double lo[3], const double hi[3],
                            const int32_t res[3], double iso, const uint8_t* case_all,
-                           const int64_t* pos, int64_t n_cells, float* tris, int64_t cap,
-                           hipStream_t s);
+                           const uint64_t* mask, const int64_t* offs, int64_t n_cells, float* tris,
+                           int64_t cap, hipStream_t s);
 
 // scan.hip
 hipError_t scan_exclusive_i32_i64(const int32_t* in, int64_t* out, int64_t n,
                                   int64_t* total, void* tmp, size_t tmp_bytes, hipStream_t s);
 size_t scan_tmp_bytes(int64_t n);
+// one workgroup: exclusive scan of n sums in place, and their total
+hipError_t scan_sums_i64(int64_t* sums, int64_t n, int64_t* total, hipStream_t s);
 hipError_t scan_exclusive_u32(const uint32_t* in, uint32_t* out, int64_t n, void* tmp,
                               size_t tmp_bytes, hipStream_t s);
 

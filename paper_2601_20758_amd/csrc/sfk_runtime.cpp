@@ -2593,6 +2593,28 @@ sfk_status sfk_sample_density(sfk_ctx c, const sfk_roi* roi, const float* d_grid
   SFK_GUARD_END(c)
 }
 
+namespace {
+// Scratch of an ordered selection over n entries: one allocation for the
+// tiles' masks, numbers and total and, for cells, the cases.
+struct SelectTmp {
+  TmpBuf b;
+  int64_t tiles = 0, *sums = nullptr, *total = nullptr;
+  uint64_t* mask = nullptr;
+  uint8_t* cases = nullptr;
+  explicit SelectTmp(sfk_ctx c) : b(c) {}
+  sfk_status get(int64_t n, int64_t n_cases) {
+    tiles = sfk::select_tiles(n);
+    const size_t words = (size_t)tiles * (sfk::kSelTileWords + 1) + 1;
+    SFK_TRY(b.get(8 * words + (size_t)n_cases, "selection masks"));
+    mask = b.as<uint64_t>();
+    sums = b.as<int64_t>() + tiles * sfk::kSelTileWords;
+    total = sums + tiles;
+    cases = (uint8_t*)(total + 1);
+    return SFK_OK;
+  }
+};
+}  // namespace
+
 sfk_status sfk_select_points(sfk_ctx c, const sfk_roi* roi, const float* d_grid, double iso,
                              const float* d_xyz, int64_t n, int64_t* d_idx, int64_t cap,
                              int64_t* h_count, void* hip_stream) {
@@ -2606,21 +2628,14 @@ sfk_status sfk_select_points(sfk_ctx c, const sfk_roi* roi, const float* d_grid,
   *h_count = 0;
   if (n == 0) return SFK_OK;
   hipStream_t s = (hipStream_t)hip_stream;
-  TmpBuf flags(c), pos(c), tmp(c), total(c);
-  sfk_status st;
-  if ((st = flags.get(sizeof(int32_t) * (size_t)n, "selection flags")) != SFK_OK ||
-      (st = pos.get(sizeof(int64_t) * (size_t)n, "selection offsets")) != SFK_OK ||
-      (st = tmp.get(sfk::scan_tmp_bytes(n), "scan scratch")) != SFK_OK ||
-      (st = total.get(sizeof(int64_t), "selection count")) != SFK_OK)
-    return st;
+  SelectTmp t(c);
+  SFK_TRY(t.get(n, 0));
   int64_t cnt = 0;
-  if (sfk::launch_select_flags(d_grid, roi->lo, roi->hi, roi->res, iso, d_xyz, n,
-                               flags.as<int32_t>(), s) != hipSuccess ||
-      sfk::scan_exclusive_i32_i64(flags.as<int32_t>(), pos.as<int64_t>(), n, total.as<int64_t>(),
-                                  tmp.b.p, tmp.b.bytes, s) != hipSuccess ||
-      sfk::launch_compact_index(flags.as<int32_t>(), pos.as<int64_t>(), n, d_idx, cap, s) !=
-          hipSuccess ||
-      hipMemcpyAsync(&cnt, total.b.p, sizeof cnt, hipMemcpyDeviceToHost, s) != hipSuccess ||
+  if (sfk::launch_select_mask(d_grid, roi->lo, roi->hi, roi->res, iso, d_xyz, n, t.mask, t.sums,
+                              s) != hipSuccess ||
+      sfk::scan_sums_i64(t.sums, t.tiles, t.total, s) != hipSuccess ||
+      sfk::launch_select_write(t.mask, t.sums, n, d_idx, cap, s) != hipSuccess ||
+      hipMemcpyAsync(&cnt, t.total, sizeof cnt, hipMemcpyDeviceToHost, s) != hipSuccess ||
       hipStreamSynchronize(s) != hipSuccess) {
     (void)hipStreamSynchronize(s);
     set_err(c, "selection kernels failed");
@@ -2643,22 +2658,15 @@ sfk_status sfk_iso_cells(sfk_ctx c, const sfk_roi* roi, const float* d_grid, dou
   }
   const int64_t nc = (int64_t)(roi->res[0] - 1) * (roi->res[1] - 1) * (roi->res[2] - 1);
   hipStream_t s = (hipStream_t)hip_stream;
-  TmpBuf flags(c), pos(c), cases(c), tmp(c), total(c);
-  sfk_status st;
-  if ((st = flags.get(sizeof(int32_t) * (size_t)nc, "cell flags")) != SFK_OK ||
-      (st = pos.get(sizeof(int64_t) * (size_t)nc, "cell offsets")) != SFK_OK ||
-      (st = cases.get((size_t)nc, "cell cases")) != SFK_OK ||
-      (st = tmp.get(sfk::scan_tmp_bytes(nc), "scan scratch")) != SFK_OK ||
-      (st = total.get(sizeof(int64_t), "cell count")) != SFK_OK)
-    return st;
+  SelectTmp t(c);
+  SFK_TRY(t.get(nc, nc));
   int64_t cnt = 0;
-  if (sfk::launch_iso_flags(d_grid, roi->res, iso, nc, flags.as<int32_t>(), cases.as<uint8_t>(),
-                            s) != hipSuccess ||
-      sfk::scan_exclusive_i32_i64(flags.as<int32_t>(), pos.as<int64_t>(), nc, total.as<int64_t>(),
-                                  tmp.b.p, tmp.b.bytes, s) != hipSuccess ||
-      sfk::launch_compact_cells(flags.as<int32_t>(), pos.as<int64_t>(), cases.as<uint8_t>(), nc,
-                                d_cells, d_cases, cap, s) != hipSuccess ||
-      hipMemcpyAsync(&cnt, total.b.p, sizeof cnt, hipMemcpyDeviceToHost, s) != hipSuccess ||
+  if (sfk::launch_iso_mask(d_grid, roi->res, iso, nc, false, t.cases, t.mask, t.sums, s) !=
+          hipSuccess ||
+      sfk::scan_sums_i64(t.sums, t.tiles, t.total, s) != hipSuccess ||
+      sfk::launch_cells_write(t.mask, t.sums, t.cases, nc, d_cells, d_cases, cap, s) !=
+          hipSuccess ||
+      hipMemcpyAsync(&cnt, t.total, sizeof cnt, hipMemcpyDeviceToHost, s) != hipSuccess ||
       hipStreamSynchronize(s) != hipSuccess) {
     (void)hipStreamSynchronize(s);
     set_err(c, "iso-cell kernels failed");
@@ -2680,24 +2688,15 @@ sfk_status sfk_iso_surface(sfk_ctx c, const sfk_roi* roi, const float* d_grid, d
   }
   const int64_t nc = (int64_t)(roi->res[0] - 1) * (roi->res[1] - 1) * (roi->res[2] - 1);
   hipStream_t s = (hipStream_t)hip_stream;
-  TmpBuf flags(c), cnt(c), pos(c), cases(c), tmp(c), total(c);
-  sfk_status st;
-  if ((st = flags.get(sizeof(int32_t) * (size_t)nc, "cell flags")) != SFK_OK ||
-      (st = cnt.get(sizeof(int32_t) * (size_t)nc, "cell triangle counts")) != SFK_OK ||
-      (st = pos.get(sizeof(int64_t) * (size_t)nc, "cell offsets")) != SFK_OK ||
-      (st = cases.get((size_t)nc, "cell cases")) != SFK_OK ||
-      (st = tmp.get(sfk::scan_tmp_bytes(nc), "scan scratch")) != SFK_OK ||
-      (st = total.get(sizeof(int64_t), "triangle count")) != SFK_OK)
-    return st;
+  SelectTmp t(c);
+  SFK_TRY(t.get(nc, nc));
   int64_t n = 0;
-  if (sfk::launch_iso_flags(d_grid, roi->res, iso, nc, flags.as<int32_t>(), cases.as<uint8_t>(),
-                            s) != hipSuccess ||
-      sfk::launch_iso_tri_count(cases.as<uint8_t>(), nc, cnt.as<int32_t>(), s) != hipSuccess ||
-      sfk::scan_exclusive_i32_i64(cnt.as<int32_t>(), pos.as<int64_t>(), nc, total.as<int64_t>(),
-                                  tmp.b.p, tmp.b.bytes, s) != hipSuccess ||
-      sfk::launch_iso_emit(d_grid, roi->lo, roi->hi, roi->res, iso, cases.as<uint8_t>(),
-                           pos.as<int64_t>(), nc, d_tris, cap, s) != hipSuccess ||
-      hipMemcpyAsync(&n, total.b.p, sizeof n, hipMemcpyDeviceToHost, s) != hipSuccess ||
+  if (sfk::launch_iso_mask(d_grid, roi->res, iso, nc, true, t.cases, t.mask, t.sums, s) !=
+          hipSuccess ||
+      sfk::scan_sums_i64(t.sums, t.tiles, t.total, s) != hipSuccess ||
+      sfk::launch_iso_emit(d_grid, roi->lo, roi->hi, roi->res, iso, t.cases, t.mask, t.sums, nc,
+                           d_tris, cap, s) != hipSuccess ||
+      hipMemcpyAsync(&n, t.total, sizeof n, hipMemcpyDeviceToHost, s) != hipSuccess ||
       hipStreamSynchronize(s) != hipSuccess) {
     (void)hipStreamSynchronize(s);
     set_err(c, "iso-surface kernels failed");
