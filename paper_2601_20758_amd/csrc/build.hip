@@ -138,6 +138,20 @@ __host__ __device__ __forceinline__ uint64_t spread3(uint64_t v) {
   return v;
 }
 
+// the same for 10 bits, in 32-bit operations
+__host__ __device__ __forceinline__ uint32_t spread3_10(uint32_t v) {
+  v &= 0x3ffu;
+  v = (v | (v << 16)) & 0x30000ffu;
+  v = (v | (v << 8)) & 0x300f00fu;
+  v = (v | (v << 4)) & 0x30c30c3u;
+  v = (v | (v << 2)) & 0x9249249u;
+  return v;
+}
+
+__host__ __device__ __forceinline__ uint32_t bit_mask(uint32_t v, int b) {
+  return (uint32_t)((int32_t)(v << (31 - b)) >> 31);
+}
+
 // Key of the cell (x, y, z) of a 2^bits-per-axis lattice, 3*bits bits.
 // Morton: the coordinate bits interleaved, x the most significant of each
 // triple. Hilbert: J. Skilling's transpose method (Programming the Hilbert
@@ -150,35 +164,44 @@ __host__ __device__ __forceinline__ uint64_t spread3(uint64_t v) {
 __host__ __device__ __forceinline__ uint64_t curve_key(uint32_t x, uint32_t y, uint32_t z,
                                                        int bits, int hilbert) {
   if (hilbert) {
-    for (uint32_t q = 1u << (bits - 1); q > 1u; q >>= 1) {
-      const uint32_t p = q - 1u;
-      if (x & q) x ^= p;
-      uint32_t t = (x ^ y) & p;
-      if (y & q) { x ^= p; t = 0u; }
-      x ^= t;
+    // all selections by masks: bit b of a word, spread over the word
+    for (int b = bits - 1; b > 0; --b) {
+      const uint32_t p = (1u << b) - 1u;
+      x ^= bit_mask(x, b) & p;
+      uint32_t m = bit_mask(y, b), t = (x ^ y) & p & ~m;
+      x ^= (p & m) | t;
       y ^= t;
-      t = (x ^ z) & p;
-      if (z & q) { x ^= p; t = 0u; }
-      x ^= t;
+      m = bit_mask(z, b);
+      t = (x ^ z) & p & ~m;
+      x ^= (p & m) | t;
       z ^= t;
     }
     y ^= x;
     z ^= y;
-    uint32_t t = 0u;
-    for (uint32_t q = 1u << (bits - 1); q > 1u; q >>= 1)
-      if (z & q) t ^= q - 1u;
+    // bit i of t: the parity of z's bits above i
+    uint32_t t = z >> 1;
+    t ^= t >> 1;
+    t ^= t >> 2;
+    t ^= t >> 4;
+    t ^= t >> 8;
+    t ^= t >> 16;
     x ^= t;
     y ^= t;
     z ^= t;
   }
+  if (bits <= 10)
+    return (spread3_10(x) << 2) | (spread3_10(y) << 1) | spread3_10(z);
   return (spread3(x) << 2) | (spread3(y) << 1) | spread3(z);
 }
 
+// Four points a thread and round: 48 bytes in three loads when the cloud's
+// address allows it (vec), twelve 4-byte loads otherwise. Bound by VALU issue,
+// half of it the curve's bit steps: 10M points 62 us (74 with a point a
+// thread, an index written beside each key and 64-bit interleaving).
 template <typename K>
 __global__ __launch_bounds__(256) void k_curve_keys(const float* __restrict__ xyz, int64_t n,
-                                                    const float* __restrict__ bbox, int bits,
-                                                    int hilbert, K* __restrict__ keys,
-                                                    uint32_t* __restrict__ vals) {
+                                                    int vec, const float* __restrict__ bbox,
+                                                    int bits, int hilbert, K* __restrict__ keys) {
   const float cells = (float)(1u << bits);
   float lo[3], sc[3];
 #pragma unroll
@@ -188,29 +211,51 @@ __global__ __launch_bounds__(256) void k_curve_keys(const float* __restrict__ xy
     sc[k] = ext > 0.0f ? cells / ext : 0.0f;
   }
   const uint32_t qmax = (1u << bits) - 1u;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    uint32_t q[3];
+  for (int64_t i = 4 * ((int64_t)blockIdx.x * blockDim.x + threadIdx.x); i < n;
+       i += 4 * (int64_t)gridDim.x * blockDim.x) {
+    const int m = (int)min((int64_t)4, n - i);
+    float p[12];
+    if (vec && m == 4) {
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const float f = (xyz[3 * i + k] - lo[k]) * sc[k];
-      q[k] = f <= 0.0f ? 0u : (f >= (float)qmax ? qmax : (uint32_t)f);
+      for (int v = 0; v < 3; ++v) {
+        const float4 f = ((const float4*)(xyz + 3 * i))[v];
+        p[4 * v] = f.x;
+        p[4 * v + 1] = f.y;
+        p[4 * v + 2] = f.z;
+        p[4 * v + 3] = f.w;
+      }
+    } else {
+#pragma unroll
+      for (int v = 0; v < 12; ++v) p[v] = v < 3 * m ? xyz[3 * i + v] : 0.0f;
     }
-    keys[i] = (K)curve_key(q[0], q[1], q[2], bits, hilbert);
-    vals[i] = (uint32_t)i;
+    K key[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      uint32_t q[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const float f = (p[3 * c + k] - lo[k]) * sc[k];
+        q[k] = f <= 0.0f ? 0u : (f >= (float)qmax ? qmax : (uint32_t)f);
+      }
+      key[c] = (K)curve_key(q[0], q[1], q[2], bits, hilbert);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if (c < m) keys[i + c] = key[c];
   }
 }
 
 hipError_t launch_curve_keys(const float* xyz, int64_t n, const float* bbox, int bits,
-                             int hilbert, void* keys, uint32_t* vals, hipStream_t s) {
+                             int hilbert, void* keys, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  const int64_t nb = std::min<int64_t>((n + 255) / 256, 65536);
+  const int vec = ((uintptr_t)xyz & 15) == 0 ? 1 : 0;
+  const dim3 nb((unsigned)std::min<int64_t>((n + 1023) / 1024, 65536));
   if (3 * bits <= 32)
-    hipLaunchKernelGGL(k_curve_keys<uint32_t>, dim3((unsigned)nb), dim3(256), 0, s, xyz, n, bbox,
-                       bits, hilbert, (uint32_t*)keys, vals);
+    hipLaunchKernelGGL(k_curve_keys<uint32_t>, nb, dim3(256), 0, s, xyz, n, vec, bbox, bits,
+                       hilbert, (uint32_t*)keys);
   else
-    hipLaunchKernelGGL(k_curve_keys<uint64_t>, dim3((unsigned)nb), dim3(256), 0, s, xyz, n, bbox,
-                       bits, hilbert, (uint64_t*)keys, vals);
+    hipLaunchKernelGGL(k_curve_keys<uint64_t>, nb, dim3(256), 0, s, xyz, n, vec, bbox, bits,
+                       hilbert, (uint64_t*)keys);
   return hipGetLastError();
 }
 
@@ -220,18 +265,21 @@ void curve_keys_host(const uint32_t* cells, int64_t n, int bits, int hilbert, ui
 }
 
 // ---------------------------------------------------------------------------
-// stable LSD radix sort of (u32 or u64 key, u32 value) pairs, 8-bit digits.
-// Per pass: block digit histograms (digit-major) -> exclusive scan ->
-// scatter. The scatter ranks equal digits inside a wavefront with eight
-// ballots (one per digit bit); each wavefront owns a contiguous quarter of
-// the block's tile and starts each digit after the earlier wavefronts'
-// elements of that digit, so the order of equal keys is preserved; the
-// ranked tile is staged in LDS and written out in digit order.
+// stable order of n (u32 or u64) keys: an LSD radix sort of (key, u32 index)
+// pairs, 8-bit digits. Per pass: tile digit counts (digit-major), an exclusive
+// scan of each digit's row with its total, scatter. The first pass makes the
+// indices, the last writes no keys.
+//
+// Bound by memory and the scatter's LDS traffic: a pass over 10M 32-bit pairs
+// moves 200 MB (its floor 42 us) and takes 75 us (120 with a second read of
+// the keys, a slot per element taken in a serial chain, and the counts scanned
+// as one array in three launches).
 // ---------------------------------------------------------------------------
 
 static constexpr int kRsNT = 256;
 static constexpr int kRsItems = 16;
 static constexpr int kRsTile = kRsNT * kRsItems;
+static constexpr int kRsRowNT = 1024;
 
 template <typename K>
 __global__ __launch_bounds__(kRsNT) void k_rs_hist(const K* __restrict__ keys, int64_t n,
@@ -241,76 +289,89 @@ __global__ __launch_bounds__(kRsNT) void k_rs_hist(const K* __restrict__ keys, i
   h[threadIdx.x] = 0;
   __syncthreads();
   const int64_t base = (int64_t)blockIdx.x * kRsTile;
-#pragma unroll 4
+  const int tile_n = (int)min((int64_t)kRsTile, n - base);
+  K key[kRsItems];  // all loads in flight at once
+#pragma unroll
   for (int r = 0; r < kRsItems; ++r) {
-    const int64_t g = base + (int64_t)r * kRsNT + threadIdx.x;
-    if (g < n) atomicAdd(&h[(uint32_t)(keys[g] >> shift) & 255u], 1u);
+    const int i = r * kRsNT + (int)threadIdx.x;
+    key[r] = i < tile_n ? keys[base + i] : (K)0;
   }
+#pragma unroll
+  for (int r = 0; r < kRsItems; ++r)
+    if (r * kRsNT + (int)threadIdx.x < tile_n)
+      atomicAdd(&h[(uint32_t)(key[r] >> shift) & 255u], 1u);
   __syncthreads();
   hist[(int64_t)threadIdx.x * nblk + blockIdx.x] = h[threadIdx.x];
 }
 
-template <typename K>
+// One workgroup per digit: exclusive scan of the digit's counts in place.
+__global__ __launch_bounds__(kRsRowNT) void k_rs_rows(uint32_t* __restrict__ hist, int nblk,
+                                                      uint32_t* __restrict__ totals) {
+  __shared__ uint32_t lds[kRsRowNT / 64];
+  uint32_t* row = hist + (int64_t)blockIdx.x * nblk;
+  uint32_t carry = 0;
+  for (int base = 0; base < nblk; base += 4 * kRsRowNT) {
+    const int g = base + 4 * (int)threadIdx.x;
+    uint32_t v[4], sum = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v[i] = g + i < nblk ? row[g + i] : 0u;
+      sum += v[i];
+    }
+    uint32_t tot;
+    uint32_t ex = carry + block_excl_scan<kRsRowNT>(sum, &tot, lds);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (g + i < nblk) row[g + i] = ex;
+      ex += v[i];
+    }
+    carry += tot;
+  }
+  if (threadIdx.x == 0) totals[blockIdx.x] = carry;
+}
+
+// Each wavefront owns a contiguous quarter of the tile, held in registers. It
+// ranks its elements among its own of the same digit, in index order (eight
+// ballots find the lanes with a lane's digit); the four wavefronts' counts
+// then give every (wavefront, digit) its first place in the tile, digits in
+// order and wavefronts in order within a digit, so equal keys keep their
+// order. The tile is staged in LDS in that order and written out, the elements
+// of one digit to consecutive places.
+template <typename K, bool FIRST, bool LAST>
 __global__ __launch_bounds__(kRsNT) void k_rs_scatter(const K* __restrict__ kin,
                                                       const uint32_t* __restrict__ vin,
                                                       K* __restrict__ kout,
                                                       uint32_t* __restrict__ vout, int64_t n,
                                                       int shift,
-                                                      const uint32_t* __restrict__ hist,
                                                       const uint32_t* __restrict__ offs,
+                                                      const uint32_t* __restrict__ totals,
                                                       int nblk) {
-  // Each wavefront owns a contiguous quarter of the block's tile. Its digit
-  // counts give every (wavefront, digit) a first local slot (digits in
-  // order, wavefronts in order within a digit); each wavefront then ranks its
-  // elements in index order into an LDS copy of the tile (stable), and the
-  // tile is written out in that order, so the elements of one digit go to
-  // consecutive global positions.
-  constexpr int kPerWave = kRsTile / 4;
+  constexpr int kRounds = kRsTile / 4 / 64;
   __shared__ K stage_k[kRsTile];
   __shared__ uint32_t stage_v[kRsTile];
-  __shared__ uint32_t wslot[4][256];  // counts, then next local slot per (wavefront, digit)
-  __shared__ uint32_t lstart[256];    // first local slot of each digit
-  __shared__ uint32_t gbase[256];     // global position of the digit's first element
+  __shared__ uint32_t wcnt[4][256];  // counts, then first place per (wavefront, digit)
+  __shared__ uint32_t move[256];     // a digit's place in the output less that in the tile
+  __shared__ uint32_t wsum[2][4];
   const int tid = threadIdx.x, wave = tid >> 6, lane = lane_id();
   const int64_t base = (int64_t)blockIdx.x * kRsTile;
   const int tile_n = (int)min((int64_t)kRsTile, n - base);
-  const int w0 = wave * kPerWave;
-  for (int d = lane; d < 256; d += 64) wslot[wave][d] = 0;
-  wave_sync();
-  for (int r = 0; r < kPerWave / 64; ++r) {
-    const int li = w0 + r * 64 + lane;
-    if (li < tile_n) atomicAdd(&wslot[wave][(uint32_t)(kin[base + li] >> shift) & 255u], 1u);
-  }
-  // local digit starts: exclusive scan of this block's histogram
-  const uint32_t hc = hist[(int64_t)tid * nblk + blockIdx.x];
-  uint32_t inc = hc;
+  const int w0 = wave * (kRsTile / 4) + lane;
+  K key[kRounds];
+  uint32_t val[kRounds], rank[kRounds];
 #pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t t = __shfl_up(inc, off, 64);
-    if (lane >= off) inc += t;
+  for (int r = 0; r < kRounds; ++r) {
+    const int li = w0 + r * 64;
+    key[r] = li < tile_n ? kin[base + li] : (K)0;
+    if constexpr (!FIRST) val[r] = li < tile_n ? vin[base + li] : 0u;
   }
-  __shared__ uint32_t wsum[4];
-  if (lane == 63) wsum[wave] = inc;
-  __syncthreads();
-  uint32_t start = inc - hc;
-  for (int w = 0; w < wave; ++w) start += wsum[w];
-  lstart[tid] = start;
-  gbase[tid] = offs[(int64_t)tid * nblk + blockIdx.x];
-  {
-    const uint32_t c0 = wslot[0][tid], c1 = wslot[1][tid], c2 = wslot[2][tid];
-    wslot[0][tid] = start;
-    wslot[1][tid] = start + c0;
-    wslot[2][tid] = start + c0 + c1;
-    wslot[3][tid] = start + c0 + c1 + c2;
-  }
-  __syncthreads();
+  const uint32_t total = totals[tid], before = offs[(int64_t)tid * nblk + blockIdx.x];
+  for (int d = lane; d < 256; d += 64) wcnt[wave][d] = 0;
+  wave_sync();
   const uint64_t lt = lanemask_lt();
-  for (int r = 0; r < kPerWave / 64; ++r) {
-    const int li = w0 + r * 64 + lane;
-    const bool valid = li < tile_n;
-    const K key = valid ? kin[base + li] : (K)0;
-    const uint32_t val = valid ? vin[base + li] : 0u;
-    const uint32_t dig = (uint32_t)(key >> shift) & 255u;
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) {
+    const bool valid = w0 + r * 64 < tile_n;
+    const uint32_t dig = (uint32_t)(key[r] >> shift) & 255u;
     uint64_t mask = ballot(valid);
 #pragma unroll
     for (int b = 0; b < 8; ++b) {
@@ -318,76 +379,106 @@ __global__ __launch_bounds__(kRsNT) void k_rs_scatter(const K* __restrict__ kin,
       const uint64_t bb = ballot(bit);
       mask &= bit ? bb : ~bb;
     }
-    const uint32_t rank = (uint32_t)popc64(mask & lt);
-    uint32_t slot = 0;
-    if (valid) slot = wslot[wave][dig];
-    wave_sync();  // every lane has read its digit's slot before the leaders advance it
-    if (valid) {
-      stage_k[slot + rank] = key;
-      stage_v[slot + rank] = val;
-      if (rank == 0) wslot[wave][dig] = slot + (uint32_t)popc64(mask);
-    }
+    const uint32_t among = (uint32_t)popc64(mask & lt);
+    const uint32_t had = wcnt[wave][dig];
+    rank[r] = had + among;
+    wave_sync();  // every lane has read its digit's count before the first advances it
+    if (valid && among == 0) wcnt[wave][dig] = had + (uint32_t)popc64(mask);
     wave_sync();
   }
   __syncthreads();
+  {
+    const uint32_t c0 = wcnt[0][tid], c1 = wcnt[1][tid], c2 = wcnt[2][tid], c3 = wcnt[3][tid];
+    const uint32_t c = c0 + c1 + c2 + c3;
+    uint32_t start = wave_incl_scan(c), gstart = wave_incl_scan(total);
+    if (lane == 63) {
+      wsum[0][wave] = start;
+      wsum[1][wave] = gstart;
+    }
+    __syncthreads();
+    start -= c;
+    gstart -= total;
+    for (int w = 0; w < wave; ++w) {
+      start += wsum[0][w];
+      gstart += wsum[1][w];
+    }
+    wcnt[0][tid] = start;
+    wcnt[1][tid] = start + c0;
+    wcnt[2][tid] = start + c0 + c1;
+    wcnt[3][tid] = start + c0 + c1 + c2;
+    move[tid] = gstart + before - start;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) {
+    const int li = w0 + r * 64;
+    if (li < tile_n) {
+      const uint32_t at = wcnt[wave][(uint32_t)(key[r] >> shift) & 255u] + rank[r];
+      stage_k[at] = key[r];
+      stage_v[at] = FIRST ? (uint32_t)(base + li) : val[r];
+    }
+  }
+  __syncthreads();
+#pragma unroll 4
   for (int i = tid; i < tile_n; i += kRsNT) {
-    const K key = stage_k[i];
-    const uint32_t dig = (uint32_t)(key >> shift) & 255u;
-    kout[gbase[dig] + ((uint32_t)i - lstart[dig])] = key;
-    vout[gbase[dig] + ((uint32_t)i - lstart[dig])] = stage_v[i];
+    const K k = stage_k[i];
+    const uint32_t to = (uint32_t)i + move[(uint32_t)(k >> shift) & 255u];
+    if constexpr (!LAST) kout[to] = k;
+    vout[to] = stage_v[i];
   }
 }
 
-size_t radix_sort_tmp_bytes(int64_t n) {
+size_t radix_order_tmp_bytes(int64_t n) {
   const int64_t nblk = (n + kRsTile - 1) / kRsTile;
-  const int64_t nh = 256 * nblk;
-  return (size_t)nh * 2 * sizeof(uint32_t) + scan_tmp_bytes(nh) + 1024;
+  return ((size_t)nblk + 1) * 256 * sizeof(uint32_t);
 }
 
 template <typename K>
-static hipError_t radix_sort_impl(K* keys, uint32_t* vals, K* keys_alt, uint32_t* vals_alt,
-                                  int64_t n, int key_bits, void* tmp, size_t tmp_bytes,
-                                  hipStream_t s, int* result_in_alt) {
-  *result_in_alt = 0;
-  if (n <= 1) return hipSuccess;
+static hipError_t radix_order_impl(K* keys, K* keys_alt, uint32_t* order, uint32_t* other,
+                                   int64_t n, int key_bits, void* tmp, size_t tmp_bytes,
+                                   hipStream_t s) {
+  if (n <= 0) return hipSuccess;
   const int64_t nblk = (n + kRsTile - 1) / kRsTile;
-  const int64_t nh = 256 * nblk;
-  if (radix_sort_tmp_bytes(n) > tmp_bytes) return hipErrorInvalidValue;
+  if (radix_order_tmp_bytes(n) > tmp_bytes) return hipErrorInvalidValue;
   uint32_t* hist = (uint32_t*)tmp;
-  uint32_t* offs = hist + nh;
-  void* stmp = (void*)(offs + nh);
-  const size_t stmp_bytes = tmp_bytes - (size_t)nh * 2 * sizeof(uint32_t);
+  uint32_t* totals = hist + nblk * 256;
+  const int passes = std::max(1, (key_bits + 7) / 8);
   K *ka = keys, *kb = keys_alt;
-  uint32_t *va = vals, *vb = vals_alt;
-  const int passes = (key_bits + 7) / 8;
+  // the last pass writes `order`; the first reads no indices
+  uint32_t *va = (passes & 1) ? other : order, *vb = (passes & 1) ? order : other;
+  const dim3 g((unsigned)nblk), b(kRsNT);
   for (int p = 0; p < passes; ++p) {
     const int shift = 8 * p;
-    hipLaunchKernelGGL(k_rs_hist<K>, dim3((unsigned)nblk), dim3(kRsNT), 0, s, ka, n, shift, hist,
-                       (int)nblk);
-    hipError_t e = scan_exclusive_u32(hist, offs, nh, stmp, stmp_bytes, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_rs_scatter<K>, dim3((unsigned)nblk), dim3(kRsNT), 0, s, ka, va, kb, vb,
-                       n, shift, hist, offs, (int)nblk);
+    const bool first = p == 0, last = p == passes - 1;
+    hipLaunchKernelGGL(k_rs_hist<K>, g, b, 0, s, ka, n, shift, hist, (int)nblk);
+    hipLaunchKernelGGL(k_rs_rows, dim3(256), dim3(kRsRowNT), 0, s, hist, (int)nblk, totals);
+#define SFK_RS(F, L)                                                                              \
+  hipLaunchKernelGGL((k_rs_scatter<K, F, L>), g, b, 0, s, ka, va, kb, vb, n, shift, hist, totals, \
+                     (int)nblk)
+    if (first && last)
+      SFK_RS(true, true);
+    else if (first)
+      SFK_RS(true, false);
+    else if (last)
+      SFK_RS(false, true);
+    else
+      SFK_RS(false, false);
+#undef SFK_RS
     std::swap(ka, kb);
     std::swap(va, vb);
   }
-  *result_in_alt = (passes & 1) ? 1 : 0;
   return hipGetLastError();
 }
 
-hipError_t radix_sort_pairs(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt,
-                            uint32_t* vals_alt, int64_t n, int key_bits, void* tmp,
-                            size_t tmp_bytes, hipStream_t s, int* result_in_alt) {
-  return radix_sort_impl(keys, vals, keys_alt, vals_alt, n, key_bits, tmp, tmp_bytes, s,
-                         result_in_alt);
+hipError_t radix_order(uint64_t* keys, uint64_t* keys_alt, uint32_t* order, uint32_t* other,
+                       int64_t n, int key_bits, void* tmp, size_t tmp_bytes, hipStream_t s) {
+  return radix_order_impl(keys, keys_alt, order, other, n, key_bits, tmp, tmp_bytes, s);
 }
 
-hipError_t radix_sort_pairs_u32(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt,
-                                uint32_t* vals_alt, int64_t n, int key_bits, void* tmp,
-                                size_t tmp_bytes, hipStream_t s, int* result_in_alt) {
+hipError_t radix_order_u32(uint32_t* keys, uint32_t* keys_alt, uint32_t* order, uint32_t* other,
+                           int64_t n, int key_bits, void* tmp, size_t tmp_bytes, hipStream_t s) {
   if (key_bits > 32) return hipErrorInvalidValue;
-  return radix_sort_impl(keys, vals, keys_alt, vals_alt, n, key_bits, tmp, tmp_bytes, s,
-                         result_in_alt);
+  return radix_order_impl(keys, keys_alt, order, other, n, key_bits, tmp, tmp_bytes, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -411,7 +502,6 @@ static_assert(kKnnBoxFloats <= 64, "a leaf's sub-block boxes are loaded one floa
 __global__ __launch_bounds__(256) void k_gather(const float* __restrict__ xyz,
                                                 const uint32_t* __restrict__ perm, int64_t n,
                                                 int32_t n_leaves, float4* __restrict__ pts,
-                                                int32_t* __restrict__ perm_out,
                                                 NodeBox* __restrict__ leaf_box,
                                                 float4* __restrict__ sub_box) {
   const int lane = lane_id();
@@ -422,7 +512,6 @@ __global__ __launch_bounds__(256) void k_gather(const float* __restrict__ xyz,
       const uint32_t j = perm[slot];
       p = make_float4(xyz[3 * (int64_t)j], xyz[3 * (int64_t)j + 1], xyz[3 * (int64_t)j + 2],
                       0.0f);
-      perm_out[slot] = (int32_t)j;
     }
     pts[slot] = p;
     const bool real = slot < n && p.x < 1.0e29f;
@@ -457,12 +546,11 @@ __global__ __launch_bounds__(256) void k_gather(const float* __restrict__ xyz,
 }
 
 hipError_t launch_gather(const float* xyz, const uint32_t* perm, int64_t n, int32_t n_leaves,
-                         float4* pts, int32_t* perm_out, NodeBox* leaf_box, float* sub_box,
-                         hipStream_t s) {
+                         float4* pts, NodeBox* leaf_box, float* sub_box, hipStream_t s) {
   if (n_leaves <= 0) return hipSuccess;
   if (n > (int64_t)n_leaves * SFK_LEAF) return hipErrorInvalidValue;
   const int nb = std::min<int>((n_leaves + 3) / 4, 65536);
-  hipLaunchKernelGGL(k_gather, dim3(nb), dim3(256), 0, s, xyz, perm, n, n_leaves, pts, perm_out,
+  hipLaunchKernelGGL(k_gather, dim3(nb), dim3(256), 0, s, xyz, perm, n, n_leaves, pts,
                      leaf_box, reinterpret_cast<float4*>(sub_box));
   return hipGetLastError();
 }

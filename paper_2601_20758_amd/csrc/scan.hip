@@ -1,5 +1,5 @@
 // Device-wide exclusive prefix sums (reduce-then-scan, three launches).
-// Used for radix-sort digit offsets and for the per-tile work plan.
+// Used for the in-box particle set's leaf offsets and for selections' tiles.
 #include "sfk_device.h"
 
 namespace sfk {
@@ -105,11 +105,6 @@ hipError_t scan_sums_i64(int64_t* sums, int64_t n, int64_t* total, hipStream_t s
   // bound by the latency of its rounds: 5 us for 4883 sums, 8 with 256 a round
   hipLaunchKernelGGL((k_scan_blocks<1024, int64_t>), dim3(1), dim3(1024), 0, s, sums, n, total);
   return hipGetLastError();
-}
-
-hipError_t scan_exclusive_u32(const uint32_t* in, uint32_t* out, int64_t n, void* tmp,
-                              size_t tmp_bytes, hipStream_t s) {
-  return scan_impl<uint32_t, uint32_t>(in, out, n, (uint32_t*)nullptr, tmp, tmp_bytes, s);
 }
 
 }  // namespace sfk

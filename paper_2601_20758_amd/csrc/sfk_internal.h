@@ -173,31 +173,28 @@ hipError_t scan_exclusive_i32_i64(const int32_t* in, int64_t* out, int64_t n,
 size_t scan_tmp_bytes(int64_t n);
 // one workgroup: exclusive scan of n sums in place, and their total
 hipError_t scan_sums_i64(int64_t* sums, int64_t n, int64_t* total, hipStream_t s);
-hipError_t scan_exclusive_u32(const uint32_t* in, uint32_t* out, int64_t n, void* tmp,
-                              size_t tmp_bytes, hipStream_t s);
 
 // build.hip
 hipError_t launch_bbox(const float* xyz, int64_t n, float* partial, int nblk, float* result,
                        hipStream_t s);
 // keys: uint32_t[n] when 3*bits <= 32, else uint64_t[n]
 hipError_t launch_curve_keys(const float* xyz, int64_t n, const float* bbox, int bits,
-                             int hilbert, void* keys, uint32_t* vals, hipStream_t s);
+                             int hilbert, void* keys, hipStream_t s);
 // the same key function on the host: cells = n (x, y, z) triples < 2^bits
 void curve_keys_host(const uint32_t* cells, int64_t n, int bits, int hilbert, uint64_t* keys);
-size_t radix_sort_tmp_bytes(int64_t n);
-hipError_t radix_sort_pairs(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt,
-                            uint32_t* vals_alt, int64_t n, int key_bits, void* tmp,
-                            size_t tmp_bytes, hipStream_t s, int* result_in_alt);
+// The stable order of n keys of key_bits bits: the indices 0 .. n - 1 sorted
+// by key. The keys and `other` (n entries) are scratch.
+size_t radix_order_tmp_bytes(int64_t n);
+hipError_t radix_order(uint64_t* keys, uint64_t* keys_alt, uint32_t* order, uint32_t* other,
+                       int64_t n, int key_bits, void* tmp, size_t tmp_bytes, hipStream_t s);
 // the same with 32-bit keys (key_bits <= 32)
-hipError_t radix_sort_pairs_u32(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt,
-                                uint32_t* vals_alt, int64_t n, int key_bits, void* tmp,
-                                size_t tmp_bytes, hipStream_t s, int* result_in_alt);
+hipError_t radix_order_u32(uint32_t* keys, uint32_t* keys_alt, uint32_t* order, uint32_t* other,
+                           int64_t n, int key_bits, void* tmp, size_t tmp_bytes, hipStream_t s);
 // Sorted particles into n_leaves * SFK_LEAF slots (n <= that), the leaf
 // boxes into leaf_box[0, n_leaves), and with sub_box non-null the k-NN
 // sub-block boxes (knn_sub_box_bytes(n_leaves))
 hipError_t launch_gather(const float* xyz, const uint32_t* perm, int64_t n, int32_t n_leaves,
-                         float4* pts, int32_t* perm_out, NodeBox* leaf_box, float* sub_box,
-                         hipStream_t s);
+                         float4* pts, NodeBox* leaf_box, float* sub_box, hipStream_t s);
 // only_if: nullptr, or a device flag; the launch does nothing while it is 0
 hipError_t launch_leaf_boxes(const float4* pts, int64_t n, int32_t n_leaves, NodeBox* out,
                              const int32_t* only_if, hipStream_t s);

@@ -1995,7 +1995,7 @@ sfk_status sfk_build_tree(sfk_ctx c, const float* d_xyz, int64_t n, const float*
   // stage's buffers are taken while the GPU runs the stage before, so no
   // allocation (a host callback under a caller's allocator) or release sits
   // between two launches.
-  TmpBuf part(c), res(c), keys(c), keys2(c), vals(c), vals2(c), stmp(c), sub(c), moved(c);
+  TmpBuf part(c), res(c), keys(c), keys2(c), vals(c), stmp(c), sub(c), moved(c);
   const bool per_point = o.knn_k > 0 || d_h;
   // bounding box (6 floats) and the count of non-finite coordinates, read at
   // the build's one synchronisation at the end: nothing before needs them on
@@ -2018,32 +2018,30 @@ sfk_status sfk_build_tree(sfk_ctx c, const float* d_xyz, int64_t n, const float*
       const int lg = (int)std::ceil(std::log2((double)std::max<int64_t>(n, 2)));
       bits = std::min(21, std::max(10, (lg + 2) / 3 + 2));
     }
-    if ((st = keys.get(sizeof(uint64_t) * (size_t)n, "sort keys")) != SFK_OK ||
-        (st = keys2.get(sizeof(uint64_t) * (size_t)n, "sort keys")) != SFK_OK ||
-        (st = vals.get(sizeof(uint32_t) * (size_t)n, "sort values")) != SFK_OK ||
-        (st = vals2.get(sizeof(uint32_t) * (size_t)n, "sort values")) != SFK_OK ||
-        (st = stmp.get(sfk::radix_sort_tmp_bytes(n), "sort scratch")) != SFK_OK)
-      return fail(st);
-    int alt = 0;
-    ProfScope prof(c, PK_BUILD, s);
     // keys of at most 32 bits are sorted as uint32 (a third less traffic per pass)
     const bool narrow = 3 * bits <= 32;
+    const size_t key_bytes = (narrow ? sizeof(uint32_t) : sizeof(uint64_t)) * (size_t)n;
+    if ((st = keys.get(key_bytes, "sort keys")) != SFK_OK ||
+        (st = keys2.get(key_bytes, "sort keys")) != SFK_OK ||
+        (st = vals.get(sizeof(uint32_t) * (size_t)n, "sort values")) != SFK_OK ||
+        (st = stmp.get(sfk::radix_order_tmp_bytes(n), "sort scratch")) != SFK_OK)
+      return fail(st);
+    ProfScope prof(c, PK_BUILD, s);
+    uint32_t* order = (uint32_t*)t->perm.p;
     if (sfk::launch_curve_keys(d_xyz, n, res.as<float>(), bits, o.curve == SFK_CURVE_HILBERT,
-                               keys.b.p, vals.as<uint32_t>(), s) != hipSuccess ||
-        (narrow ? sfk::radix_sort_pairs_u32(keys.as<uint32_t>(), vals.as<uint32_t>(),
-                                            keys2.as<uint32_t>(), vals2.as<uint32_t>(), n,
-                                            3 * bits, stmp.b.p, stmp.b.bytes, s, &alt)
-                : sfk::radix_sort_pairs(keys.as<uint64_t>(), vals.as<uint32_t>(),
-                                        keys2.as<uint64_t>(), vals2.as<uint32_t>(), n, 3 * bits,
-                                        stmp.b.p, stmp.b.bytes, s, &alt)) != hipSuccess)
+                               keys.b.p, s) != hipSuccess ||
+        (narrow ? sfk::radix_order_u32(keys.as<uint32_t>(), keys2.as<uint32_t>(), order,
+                                       vals.as<uint32_t>(), n, 3 * bits, stmp.b.p, stmp.b.bytes, s)
+                : sfk::radix_order(keys.as<uint64_t>(), keys2.as<uint64_t>(), order,
+                                   vals.as<uint32_t>(), n, 3 * bits, stmp.b.p, stmp.b.bytes,
+                                   s)) != hipSuccess)
       return fail((set_err(c, "sort failed"), SFK_E_DEVICE));
     // the k-NN's sub-block boxes come out of the gather, from the same registers
     const bool knn = per_point && o.knn_k > 0;
     if (knn &&
         (st = sub.get(sfk::knn_sub_box_bytes(t->n_leaves), "k-NN sub-block boxes")) != SFK_OK)
       return fail(st);
-    if (sfk::launch_gather(d_xyz, alt ? vals2.as<uint32_t>() : vals.as<uint32_t>(), n,
-                           t->n_leaves, (float4*)t->pts.p, (int32_t*)t->perm.p,
+    if (sfk::launch_gather(d_xyz, order, n, t->n_leaves, (float4*)t->pts.p,
                            (NodeBox*)t->nodes.p + t->level_off[0],
                            knn ? sub.as<float>() : nullptr, s) != hipSuccess)
       return fail((set_err(c, "gather failed"), SFK_E_DEVICE));
