@@ -1022,15 +1022,25 @@ __device__ __forceinline__ unsigned int splat_units(double v) {
   return (unsigned int)fma(fmax(v, 0.0), kSplatUnit, 0.5);
 }
 
-// The Epanechnikov term (1 - (ux^2 + uy^2)) - uz^2 in fixed point, from the
-// units of its two parts: the row part a = 1 - (ux^2 + uy^2) counts
-// splat_units(a) (at most 2^31), uz^2 counts floor(uz^2 2^31 + 1/2) saturated
-// at 2^32 - 1, and the term is their difference, 0 when it is not positive
-// (one saturating subtraction per node; a pair outside the support counts 0
-// up to one unit at its edge).
-__device__ __forceinline__ unsigned int epan_z_units(double sz) {
-  return (unsigned int)fmin(fma(sz, kSplatUnit, 0.5), 4294967295.0);
+// The Epanechnikov term ((1 - ux^2) - uy^2) - uz^2 in fixed point, 2^32 - 1
+// units to 1, from the units of its three parts, each rounded to the nearest
+// and saturated at 1: a term is 1 - ux^2's less uy^2's less uz^2's, 0 when
+// that is not positive (saturating subtractions; a pair outside the support
+// counts 0 up to a unit and a half at its edge). A part belongs to a node
+// coordinate, so a row of nodes takes one integer subtraction (units of 2^-31
+// of 1 - (ux^2 + uy^2), converted for every row, rounded twice as coarsely).
+// The clamps are output modifiers.
+constexpr double kEpanUnit = 4294967295.0;
+__device__ __forceinline__ double clamp01(double v) { return fmin(fmax(v, 0.0), 1.0); }
+__device__ __forceinline__ unsigned int epan_sq_units(double sq) {
+  return (unsigned int)fma(clamp01(sq), kEpanUnit, 0.5);
 }
+__device__ __forceinline__ unsigned int epan_x_units(double sx) {
+  return (unsigned int)fma(clamp01(1.0 - sx), kEpanUnit, 0.5);
+}
+// units of a node sum
+template <int KK, bool CNT>
+constexpr double kSumUnit = CNT ? 1.0 : KK == KK_EPAN ? 1.0 / kEpanUnit : 1.0 / kSplatUnit;
 __device__ __forceinline__ unsigned int epan_units(unsigned int row, unsigned int z) {
   return row > z ? row - z : 0u;
 }
@@ -1143,12 +1153,13 @@ __global__ __launch_bounds__(256) void k_splat(
         kz = kz > b[2] ? kz - nz : kz;
         const double uz = (lds_c[2][kz] - pp[2]) * ih[2];
         const double sz = uz * uz;
-        const unsigned int zq = epan_z_units(sz);
+        const unsigned int zq = epan_sq_units(sz);
         for (int dy = 0; dy < ny; ++dy) {
           int jy = a[1] + dy + ry;
           jy = jy > b[1] ? jy - ny : jy;
           const double uy = (lds_c[1][jy] - pp[1]) * ih[1];
           const double sy = uy * uy;
+          const unsigned int yq = epan_sq_units(sy);
           const int row = B * (jy + B * kz);
           const int sw = (3 * jy + 5 * kz) & (B - 1);  // bank swizzle of the row
           for (int dx = 0; dx < nx; ++dx) {
@@ -1156,8 +1167,7 @@ __global__ __launch_bounds__(256) void k_splat(
             ix = ix > b[0] ? ix - nx : ix;
             const double ux = (lds_c[0][ix] - pp[0]) * ih[0];
             if constexpr (KK == KK_EPAN && !CNT) {
-              // the Epanechnikov term (1 - (ux^2 + uy^2)) - uz^2, quantised
-              const unsigned int q = epan_units(splat_units(1.0 - (ux * ux + sy)), zq);
+              const unsigned int q = epan_units(epan_units(epan_x_units(ux * ux), yq), zq);
               if (q != 0u) atomicAdd(&sums[row + ((ix + sw) & (B - 1))], (unsigned long long)q);
             } else {
               const double u2 = (ux * ux + sy) + sz;
@@ -1279,7 +1289,7 @@ __global__ __launch_bounds__(256) void k_splat(
           });
     }
     __syncthreads();
-    const double unit = CNT ? 1.0 : 1.0 / kSplatUnit;
+    const double unit = kSumUnit<KK, CNT>;
     // LDS slot n holds node (ix, jy, kz) with n = B (jy + B kz) + ((ix + sw) mod B)
     auto write_node = [&](int n, unsigned long long v) {
       const int jy = (n / B) % B, kz = n / (B * B);
@@ -1595,33 +1605,39 @@ void k_sweep(TreeView tv, const BatchHdr* __restrict__ hdr, const RoiDev* __rest
               // 0 (no add), so the inner loop needs no range test
               sz[m] = m < n[2] ? uz * uz : kSweepFar;
             }
-            unsigned int zq[NM];
+            unsigned int xq[NM], yq[NM], zq[NM];
+            if constexpr (KK == KK_EPAN && !CNT) {
 #pragma unroll
-            for (int m = 0; m < NM; ++m) zq[m] = epan_z_units(sz[m]);
+              for (int m = 0; m < NM; ++m) {
+                xq[m] = epan_x_units(sx[m]);
+                yq[m] = epan_sq_units(sy[m]);
+                zq[m] = epan_sq_units(sz[m]);
+              }
+            }
 #pragma unroll
             for (int my = 0; my < NM; ++my) {
 #pragma unroll
               for (int mx = 0; mx < NM; ++mx) {
                 if (mx < n[0] && my < n[1]) {
-                  const double sxy = sx[mx] + sy[my];
                   const int row = base + nbk[2] * my + nyz * mx;
                   if constexpr (KK == KK_EPAN && !CNT) {
-                    // the Epanechnikov term (1 - (ux^2 + uy^2)) - uz^2,
-                    // quantised: no membership test (a non-member's term
-                    // counts 0); one saturating subtraction per node
+                    // the quantised Epanechnikov term: no membership test (a
+                    // non-member's term counts 0); one saturating subtraction
+                    // a row and one a node
                     // Up to 3 nodes per axis every lane adds, a zero where
                     // its term is 0 (no lane mask per node; the LDS has room
                     // for the extra adds). Wider spans add only nonzero
                     // terms: with 216 or more pairs per particle the unmasked
                     // adds made the LDS the bound (6 nodes: 5.9 -> 10 ms on
                     // a full 100M-point box at 256^3).
-                    const unsigned int aq = splat_units(1.0 - sxy);
+                    const unsigned int aq = epan_units(xq[mx], yq[my]);
 #pragma unroll
                     for (int mz = 0; mz < NM; ++mz) {
                       const unsigned int q = epan_units(aq, zq[mz]);
                       if (NM <= 3 || q != 0u) atomicAdd(&sums[row + mz], (unsigned long long)q);
                     }
                   } else {
+                    const double sxy = sx[mx] + sy[my];
 #pragma unroll
                     for (int mz = 0; mz < NM; ++mz) {
                       const double u2 = sxy + sz[mz];
@@ -1729,16 +1745,16 @@ void k_sweep(TreeView tv, const BatchHdr* __restrict__ hdr, const RoiDev* __rest
   if (bad) claims[kErrWord] = 1;
 }
 
-// One block per tile of kSweep^3 nodes: sum * 2^-31 * scale, rounded once to
+// One block per tile of kSweep^3 nodes: sum * unit * scale, rounded once to
 // float (the brick's conversion).
-template <bool CNT>
+template <int KK, bool CNT>
 __global__ __launch_bounds__(256) void k_sweep_write(const BatchHdr* __restrict__ hdr,
                                                      const RoiDev* __restrict__ rois,
                                                      const unsigned long long* __restrict__ acc) {
   constexpr int S = kSweep;
   const int64_t n_tiles = hdr->n_tiles;
   const int n_rois = hdr->n_rois;
-  const double unit = CNT ? 1.0 : 1.0 / kSplatUnit;
+  const double unit = kSumUnit<KK, CNT>;
   for (int64_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
     const int r = find_roi(rois, n_rois, t);
     const RoiDev& R = rois[r];
@@ -1889,9 +1905,11 @@ hipError_t launch_sweep_eval(TreeView tv, const BatchHdr* hdr, const RoiDev* roi
   if (e != hipSuccess) return e;
   const int wb = (int)std::max<int64_t>(1, std::min<int64_t>(max_tiles, 16384));
   if (cnt)
-    hipLaunchKernelGGL(k_sweep_write<true>, dim3(wb), dim3(256), 0, s, hdr, rois, acc);
+    hipLaunchKernelGGL((k_sweep_write<KK_EPAN, true>), dim3(wb), dim3(256), 0, s, hdr, rois, acc);
+  else if (kk == KK_EPAN)
+    hipLaunchKernelGGL((k_sweep_write<KK_EPAN, false>), dim3(wb), dim3(256), 0, s, hdr, rois, acc);
   else
-    hipLaunchKernelGGL(k_sweep_write<false>, dim3(wb), dim3(256), 0, s, hdr, rois, acc);
+    hipLaunchKernelGGL((k_sweep_write<KK_GAUSS, false>), dim3(wb), dim3(256), 0, s, hdr, rois, acc);
   return hipGetLastError();
 }
 
