@@ -1001,8 +1001,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 // Each lane takes one particle of a candidate leaf, computes on each axis the
 // range of brick nodes whose distance can be inside the support (rounded
 // outwards by a relative 1e-9, so the range never misses a member), and
-// visits those nodes only. An Epanechnikov term is (1 - (ux^2 + uy^2)) - uz^2
-// in double, counted as floor(v * 2^31 + 1/2) units (0 when v <= 0) with
+// visits those nodes only. An Epanechnikov term is ((1 - ux^2) - uy^2) - uz^2,
+// its parts in double and counted in fixed point (epan_sq_units), added with
 // an LDS atomic; the support counts and the truncated Gaussian decide
 // membership by the canonical u2 = (ux^2 + uy^2) + uz^2 < c2 as the
 // definition does (the Gaussian's term is exp(-u2/2) in float). The
@@ -1011,9 +1011,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 // is the same whatever the order of particles, chunks or workgroups (alone,
 // in any batch, in any evaluation mode). The brick's chunks add their sums
 // into one 64-bit slot per node with global atomics; the last chunk to
-// finish writes the nodes: sum * 2^-31 * scale, rounded once to float.
-// Per term the fixed point adds about 2^-32 at most (in units of the
-// kernel's peak) to a node sum.
+// finish writes the nodes: sum * unit * scale, rounded once to float. Per
+// term the fixed point adds at most 0.75 * 2^-31 (2^-32 for the Gaussian, in
+// units of the kernel's peak) to a node sum.
 // ---------------------------------------------------------------------------
 
 // Fixed-point units of a scattered term v in [0, 1]: floor(v * 2^31 + 1/2)
@@ -1027,9 +1027,8 @@ __device__ __forceinline__ unsigned int splat_units(double v) {
 // and saturated at 1: a term is 1 - ux^2's less uy^2's less uz^2's, 0 when
 // that is not positive (saturating subtractions; a pair outside the support
 // counts 0 up to a unit and a half at its edge). A part belongs to a node
-// coordinate, so a row of nodes takes one integer subtraction (units of 2^-31
-// of 1 - (ux^2 + uy^2), converted for every row, rounded twice as coarsely).
-// The clamps are output modifiers.
+// coordinate, so a row of nodes takes one integer subtraction. The clamps are
+// output modifiers.
 constexpr double kEpanUnit = 4294967295.0;
 __device__ __forceinline__ double clamp01(double v) { return fmin(fmax(v, 0.0), 1.0); }
 __device__ __forceinline__ unsigned int epan_sq_units(double sq) {
@@ -1333,9 +1332,13 @@ __global__ __launch_bounds__(256) void k_splat(
 // brick's terms and fixed point (the same operations in the same order)
 // and LDS atomics into private copies of the window (lane l adds to copy
 // l mod ncp), then adds the window's nonzero sums into the batch's 64-bit
-// node sums with global atomics. Per node the Epanechnikov term is one
-// saturating subtraction of fixed-point units (those of 1 - (ux^2 + uy^2),
-// taken once per node row, minus those of uz^2), with no membership branch.
+// node sums with global atomics. The Epanechnikov term takes two saturating
+// subtractions of fixed-point units, one per node row (those of 1 - ux^2 less
+// those of uy^2) and one per node (less those of uz^2), with no membership
+// branch. Bound by VALU issue and the LDS atomics together (3-node spans: both
+// three quarters busy; their share of 256 zooms into 100M points takes 5.2
+// ms, 5.9 when each row converted 1 - (ux^2 + uy^2) and rows without a term
+// were added).
 // Integer sums make the grid independent of the order of items, particles
 // and workgroups, and equal to the brick's grid bit for bit. For spans of 3
 // nodes or more the lanes of a wavefront take particles of different leaves
@@ -1503,6 +1506,8 @@ void k_sweep(TreeView tv, const BatchHdr* __restrict__ hdr, const RoiDev* __rest
       empty |= !(fa <= fb);
       w0[k] = empty ? 0 : (int)fa;
       w1[k] = empty ? -1 : (int)fb;
+      // a support wider than the NM nodes a particle visits: internal error
+      if (!(floor(2.0 * half[k]) + 1.0 <= (double)NM)) bad = empty = true;
     }
     if (empty) continue;
     const double c2 = (double)R.c2;
@@ -1566,9 +1571,27 @@ void k_sweep(TreeView tv, const BatchHdr* __restrict__ hdr, const RoiDev* __rest
                 n[k] = 1;
               }
               if (!ok) return;
+            } else if constexpr (NM <= 3) {
+              // The first node of the range on each axis, one exit, and the
+              // nodes from there to the block's end. The range's own end
+              // needs no test: past it a square is at least 1 (c^2 in the
+              // other modes) and the terms are 0 (15 instructions of 250;
+              // 3-node supports 5.45 -> 5.20 ms of a batch of 256 zooms).
+#pragma unroll
+              for (int k = 0; k < 3; ++k) {
+                const double ic = (pp[k] - lo[k]) * inv_s[k];
+                const double f = fmax(ceil(ic - half[k]), (double)blk0[k]);
+                ok &= f <= (double)(blk0[k] + nbk[k] - 1);
+                a[k] = (int)f - blk0[k];
+                n[k] = nbk[k] - a[k];
+              }
+              if (!ok) return;
             } else {
               // the ranges of all three axes first, one exit, then the
-              // conversions (no lane mask per axis)
+              // conversions (no lane mask per axis): wider supports are swept
+              // in more blocks, and a particle that only lies before a block
+              // would visit NM^2 rows for nothing (6 nodes: 5.49 ms, 5.97
+              // without the ranges' ends)
               double fa[3], fb[3];
 #pragma unroll
               for (int k = 0; k < 3; ++k) {
@@ -1583,10 +1606,6 @@ void k_sweep(TreeView tv, const BatchHdr* __restrict__ hdr, const RoiDev* __rest
                 a[k] = (int)fa[k] - blk0[k];
                 n[k] = (int)(fb[k] - fa[k]) + 1;
               }
-              if (n[0] > NM || n[1] > NM || n[2] > NM) {
-                bad = true;
-                return;
-              }
             }
             // the particle's first node in this lane's copy of the window
             // (stored z fastest, x stride nyz); a node (mx, my, mz) past it
@@ -1599,45 +1618,51 @@ void k_sweep(TreeView tv, const BatchHdr* __restrict__ hdr, const RoiDev* __rest
               const double ux = (lds_c[0][a[0] + m] - pp[0]) * ih[0];
               const double uy = (lds_c[1][a[1] + m] - pp[1]) * ih[1];
               const double uz = (lds_c[2][a[2] + m] - pp[2]) * ih[2];
-              sx[m] = ux * ux;
-              sy[m] = uy * uy;
-              // past the particle's z range a huge square makes every term
-              // 0 (no add), so the inner loop needs no range test
-              sz[m] = m < n[2] ? uz * uz : kSweepFar;
+              // past the range a huge square makes every term 0 (no add), so
+              // the loops need no range tests
+              sx[m] = NM == 1 || m < n[0] ? ux * ux : kSweepFar;
+              sy[m] = NM == 1 || m < n[1] ? uy * uy : kSweepFar;
+              sz[m] = NM == 1 || m < n[2] ? uz * uz : kSweepFar;
             }
-            unsigned int xq[NM], yq[NM], zq[NM];
+            unsigned int xq[NM], yq[NM], zq[NM], zmin = 0xffffffffu;
+            double szmin = sz[0];
             if constexpr (KK == KK_EPAN && !CNT) {
 #pragma unroll
               for (int m = 0; m < NM; ++m) {
                 xq[m] = epan_x_units(sx[m]);
                 yq[m] = epan_sq_units(sy[m]);
                 zq[m] = epan_sq_units(sz[m]);
+                zmin = min(zmin, zq[m]);
               }
+            } else {
+#pragma unroll
+              for (int m = 1; m < NM; ++m) szmin = fmin(szmin, sz[m]);
             }
 #pragma unroll
             for (int my = 0; my < NM; ++my) {
 #pragma unroll
               for (int mx = 0; mx < NM; ++mx) {
-                if (mx < n[0] && my < n[1]) {
-                  const int row = base + nbk[2] * my + nyz * mx;
-                  if constexpr (KK == KK_EPAN && !CNT) {
-                    // the quantised Epanechnikov term: no membership test (a
-                    // non-member's term counts 0); one saturating subtraction
-                    // a row and one a node
-                    // Up to 3 nodes per axis every lane adds, a zero where
-                    // its term is 0 (no lane mask per node; the LDS has room
-                    // for the extra adds). Wider spans add only nonzero
-                    // terms: with 216 or more pairs per particle the unmasked
-                    // adds made the LDS the bound (6 nodes: 5.9 -> 10 ms on
-                    // a full 100M-point box at 256^3).
-                    const unsigned int aq = epan_units(xq[mx], yq[my]);
+                const int row = base + nbk[2] * my + nyz * mx;
+                if constexpr (KK == KK_EPAN && !CNT) {
+                  const unsigned int aq = epan_units(xq[mx], yq[my]);
+                  // Lanes whose row has no nonzero term take no part: fewer
+                  // lanes add to LDS, and the ranges' far ends need no tests
+                  // of their own. Within a row of up to 3 nodes every
+                  // lane adds, a zero where its term is 0 (a mask per node
+                  // made 3-node supports 5% slower); wider spans add only
+                  // nonzero terms: with 216 or more pairs per particle the
+                  // unmasked adds made the LDS the bound (6 nodes: 5.9 -> 10
+                  // ms on a full 100M-point box at 256^3).
+                  if (NM == 1 || aq > zmin) {
 #pragma unroll
                     for (int mz = 0; mz < NM; ++mz) {
                       const unsigned int q = epan_units(aq, zq[mz]);
                       if (NM <= 3 || q != 0u) atomicAdd(&sums[row + mz], (unsigned long long)q);
                     }
-                  } else {
-                    const double sxy = sx[mx] + sy[my];
+                  }
+                } else {
+                  const double sxy = sx[mx] + sy[my];
+                  if (sxy + szmin < c2) {
 #pragma unroll
                     for (int mz = 0; mz < NM; ++mz) {
                       const double u2 = sxy + sz[mz];
