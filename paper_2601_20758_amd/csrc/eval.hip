@@ -1016,10 +1016,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 // units of the kernel's peak) to a node sum.
 // ---------------------------------------------------------------------------
 
-// Fixed-point units of a scattered term v in [0, 1]: floor(v * 2^31 + 1/2)
-// with one rounding (a fused multiply-add), 0 for v <= 0.
-__device__ __forceinline__ unsigned int splat_units(double v) {
-  return (unsigned int)fma(fmax(v, 0.0), kSplatUnit, 0.5);
+// Fixed-point units of a truncated Gaussian's term e in [0, 1], rounded to the
+// nearest: the scaling is exact, and a float of 2^23 units or more is whole
+// (through double, two conversions more a term, 10M points at 128^3 in a
+// 3-node sweep took 184 us for 173).
+__device__ __forceinline__ unsigned int gauss_units(float e) {
+  return (unsigned int)rintf(e * (float)kSplatUnit);
 }
 
 // The Epanechnikov term ((1 - ux^2) - uy^2) - uz^2 in fixed point, 2^32 - 1
@@ -1176,7 +1178,7 @@ __global__ __launch_bounds__(256) void k_splat(
                   q = 1u;
                 } else {
                   const float e = __builtin_amdgcn_exp2f((float)(SFK_KG64S * u2));
-                  q = splat_units((double)e);
+                  q = gauss_units(e);
                 }
                 atomicAdd(&sums[row + ((ix + sw) & (B - 1))], (unsigned long long)q);
               }
@@ -1448,6 +1450,9 @@ void k_sweep(TreeView tv, const BatchHdr* __restrict__ hdr, const RoiDev* __rest
   // gained).
   constexpr int W = NM == 1 ? kSweepWin / 2 : kSweepWin;
   constexpr int S = kSweep;
+  // rows tested by their Epanechnikov units (the other modes' ranges, with
+  // their ends, leave fewer pairs to decide one by one)
+  constexpr bool kRowTest = NM > 1 && KK == KK_EPAN && !CNT;
   // the window's node sums, z fastest, with an odd x stride (W^2 + 1 at
   // most) so that threads reading consecutive x fall in different banks
   constexpr int WN = W * (W * W + 1);
@@ -1571,7 +1576,7 @@ void k_sweep(TreeView tv, const BatchHdr* __restrict__ hdr, const RoiDev* __rest
                 n[k] = 1;
               }
               if (!ok) return;
-            } else if constexpr (NM <= 3) {
+            } else if constexpr (kRowTest && NM <= 3) {
               // The first node of the range on each axis, one exit, and the
               // nodes from there to the block's end. The range's own end
               // needs no test: past it a square is at least 1 (c^2 in the
@@ -1619,13 +1624,12 @@ void k_sweep(TreeView tv, const BatchHdr* __restrict__ hdr, const RoiDev* __rest
               const double uy = (lds_c[1][a[1] + m] - pp[1]) * ih[1];
               const double uz = (lds_c[2][a[2] + m] - pp[2]) * ih[2];
               // past the range a huge square makes every term 0 (no add), so
-              // the loops need no range tests
-              sx[m] = NM == 1 || m < n[0] ? ux * ux : kSweepFar;
-              sy[m] = NM == 1 || m < n[1] ? uy * uy : kSweepFar;
+              // the inner loop needs no range test, nor a row its own
+              sx[m] = !kRowTest || m < n[0] ? ux * ux : kSweepFar;
+              sy[m] = !kRowTest || m < n[1] ? uy * uy : kSweepFar;
               sz[m] = NM == 1 || m < n[2] ? uz * uz : kSweepFar;
             }
             unsigned int xq[NM], yq[NM], zq[NM], zmin = 0xffffffffu;
-            double szmin = sz[0];
             if constexpr (KK == KK_EPAN && !CNT) {
 #pragma unroll
               for (int m = 0; m < NM; ++m) {
@@ -1634,9 +1638,6 @@ void k_sweep(TreeView tv, const BatchHdr* __restrict__ hdr, const RoiDev* __rest
                 zq[m] = epan_sq_units(sz[m]);
                 zmin = min(zmin, zq[m]);
               }
-            } else {
-#pragma unroll
-              for (int m = 1; m < NM; ++m) szmin = fmin(szmin, sz[m]);
             }
 #pragma unroll
             for (int my = 0; my < NM; ++my) {
@@ -1653,7 +1654,7 @@ void k_sweep(TreeView tv, const BatchHdr* __restrict__ hdr, const RoiDev* __rest
                   // nonzero terms: with 216 or more pairs per particle the
                   // unmasked adds made the LDS the bound (6 nodes: 5.9 -> 10
                   // ms on a full 100M-point box at 256^3).
-                  if (NM == 1 || aq > zmin) {
+                  if (!kRowTest || aq > zmin) {
 #pragma unroll
                     for (int mz = 0; mz < NM; ++mz) {
                       const unsigned int q = epan_units(aq, zq[mz]);
@@ -1662,7 +1663,7 @@ void k_sweep(TreeView tv, const BatchHdr* __restrict__ hdr, const RoiDev* __rest
                   }
                 } else {
                   const double sxy = sx[mx] + sy[my];
-                  if (sxy + szmin < c2) {
+                  if (mx < n[0] && my < n[1]) {
 #pragma unroll
                     for (int mz = 0; mz < NM; ++mz) {
                       const double u2 = sxy + sz[mz];
@@ -1672,7 +1673,7 @@ void k_sweep(TreeView tv, const BatchHdr* __restrict__ hdr, const RoiDev* __rest
                           q = 1u;
                         } else {
                           const float e = __builtin_amdgcn_exp2f((float)(SFK_KG64S * u2));
-                          q = splat_units((double)e);
+                          q = gauss_units(e);
                         }
                         atomicAdd(&sums[row + mz], (unsigned long long)q);
                       }
