@@ -1128,6 +1128,15 @@ __global__ __launch_bounds__(256) void k_splat(
     }
     const double ih[3] = {(double)R.ih[0], (double)R.ih[1], (double)R.ih[2]};
 
+    // Supports that span at most kSpan nodes in x keep the x nodes' parts in
+    // registers: a row then takes a subtraction, a test and an add per node,
+    // where each node of the general loop reads and converts its coordinate
+    // again. 4096 bricks of a 256^3 zoom into 100M points, 6 nodes an axis:
+    // whole call 199 us, 298 without; with 8 nodes kept 212, with the y nodes
+    // kept as well 200 and three wavefronts a SIMD, at which batches lost 1%.
+    constexpr int kSpan = 6;
+    const bool short_span = floor(2.0 * half[0]) + 1.0 <= (double)kSpan;
+
     // scatter one particle (lane's own) into the brick's node sums
     auto splat = [&](const float4 p) {
       const double pp[3] = {(double)p.x, (double)p.y, (double)p.z};
@@ -1143,6 +1152,40 @@ __global__ __launch_bounds__(256) void k_splat(
         b[k] = empty ? -1 : (int)fb;
       }
       if (empty) return;
+      if constexpr (KK == KK_EPAN && !CNT) {
+        if (short_span) {
+          // (past the range 0 units: no term)
+          unsigned int xq[kSpan], xmax = 0u;
+#pragma unroll
+          for (int m = 0; m < kSpan; ++m) {
+            const double ux = (lds_c[0][min(a[0] + m, B - 1)] - pp[0]) * ih[0];
+            xq[m] = a[0] + m <= b[0] ? epan_x_units(ux * ux) : 0u;
+            xmax = max(xmax, xq[m]);
+          }
+          const int ny = b[1] - a[1] + 1, nz = b[2] - a[2] + 1;
+          const int ry = (lane >> 2) % ny, rz = (lane >> 4) % nz;
+          for (int dz = 0; dz < nz; ++dz) {
+            int kz = a[2] + dz + rz;
+            kz = kz > b[2] ? kz - nz : kz;
+            const double uz = (lds_c[2][kz] - pp[2]) * ih[2];
+            const unsigned int zq = epan_sq_units(uz * uz);
+            for (int dy = 0; dy < ny; ++dy) {
+              int jy = a[1] + dy + ry;
+              jy = jy > b[1] ? jy - ny : jy;
+              const double uy = (lds_c[1][jy] - pp[1]) * ih[1];
+              const unsigned int yq = epan_sq_units(uy * uy);
+              if (epan_units(xmax, yq) <= zq) continue;
+              const int row = B * (jy + B * kz), at = a[0] + 3 * jy + 5 * kz;
+#pragma unroll
+              for (int m = 0; m < kSpan; ++m) {
+                const unsigned int q = epan_units(epan_units(xq[m], yq), zq);
+                if (q != 0u) atomicAdd(&sums[row + ((at + m) & (B - 1))], (unsigned long long)q);
+              }
+            }
+          }
+          return;
+        }
+      }
       // Lanes of a leaf often share their range: each lane starts its walk
       // over the range at its own rotation (lane mod the range size per
       // axis), so the atomics of one instruction spread over the range's

@@ -88,3 +88,23 @@ def test_brick_chunk_classes_bitwise(ctx, torch, n):
         assert np.array_equal(a, b) and np.array_equal(a, out.cpu().numpy()), res
     ctx.set_eval_opts()
     tree.close()
+
+
+@pytest.mark.parametrize("h", [(0.4, 0.9, 0.3), (1.2, 1.2, 1.2), (1.4, 3.4, 0.6), (2.4, 1.0, 3.4),
+                               (2.499, 2.5, 2.501), (2.6, 2.6, 2.6), (3.4, 0.7, 3.4),
+                               (5.5, 6.5, 2.2)])
+def test_brick_spans(ctx, torch, h):
+    # supports of 1 to 14 nodes an axis, either side of the 6 in x that a
+    # brick keeps in registers, on ragged bricks; up to 8 the sweep takes them
+    pts = synth.clumpy_cloud(5000, 9)
+    tree = ctx.build_tree(dev(torch, pts))
+    roi = Roi((0.1, 0.2, 0.15), (0.9, 0.8, 0.95), (35, 18, 33), bw="fixed",
+              h=tuple(v * s for v, s in zip(h, (0.8 / 34, 0.6 / 17, 0.8 / 32))))
+    ctx.set_eval_opts(tile_shape=6)
+    a = ctx.eval_roi(tree, roi).cpu().numpy()
+    check_density(a, oracle.density(pts, roi), h)
+    if max(h) < 3.5:
+        ctx.set_eval_opts(tile_shape=7)
+        assert np.array_equal(a, ctx.eval_roi(tree, roi).cpu().numpy())
+    ctx.set_eval_opts()
+    tree.close()
