@@ -86,7 +86,8 @@ __global__ __launch_bounds__(256) void k_box_write(
   const int lane = lane_id();
   const int64_t l0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kBoxLeaves;
   if (blockIdx.x == 0 && n_b + threadIdx.x < n_slots_out)
-    out_pts[n_b + threadIdx.x] = make_float4(SFK_SENTINEL, SFK_SENTINEL, SFK_SENTINEL, 0.0f);
+    // (w is a per-point inverse bandwidth: with 0 a slot would reach every node)
+    out_pts[n_b + threadIdx.x] = make_float4(SFK_SENTINEL, SFK_SENTINEL, SFK_SENTINEL, 1.0f);
   int64_t at = 0;
   bool any = false;
   if (lane < kBoxLeaves && l0 + lane < n_leaves) {
