@@ -399,6 +399,22 @@ struct TmpBuf {
   T* as() const { return (T*)b.p; }
 };
 
+// Waits for the stream on the way out of a scope that fails: declared after
+// the temporary buffers its kernels use, so that none goes back to the
+// allocator while they run. A caller's allocator may hand the memory on at once.
+struct WaitOnFailure {
+  hipStream_t s;
+  bool armed = true;
+  explicit WaitOnFailure(hipStream_t ss) : s(ss) {}
+  ~WaitOnFailure() {
+    if (armed) (void)hipStreamSynchronize(s);
+  }
+  sfk_status done() {
+    armed = false;
+    return SFK_OK;
+  }
+};
+
 sfk_status staging_reserve(sfk_ctx c, Staging& st, size_t bytes) {
   if (!st.ev) SFK_HIP(c, hipEventCreateWithFlags(&st.ev, hipEventDisableTiming));
   if (!st.hdr_host) {
@@ -1260,6 +1276,8 @@ sfk_status eval_subcloud(sfk_ctx c, sfk_tree t, const sfk_roi* r, bool count_mod
                          Workspace& ws, Staging& st, hipStream_t s, MbeDebug* dbg) {
   const bool mbe = r->bw == SFK_BW_MBE;
   SubCloud sc(c);
+  TmpBuf stmp(c), ell_d(c), pilot(c), pden(c), bsum(c), ave_d(c), ellj_d(c);
+  WaitOnFailure wait(s);
   SFK_TRY(make_subcloud(c, t, r, mbe, sc, s));
   const int64_t n_b = sc.n_b;
   const int64_t m = (int64_t)r->res[0] * r->res[1] * r->res[2];
@@ -1269,7 +1287,7 @@ sfk_status eval_subcloud(sfk_ctx c, sfk_tree t, const sfk_roi* r, bool count_mod
     if (dbg && dbg->aveden) *dbg->aveden = 0.0;
     if (dbg && dbg->ell0) dbg->ell0[0] = dbg->ell0[1] = dbg->ell0[2] = 0.0f;
     SFK_HIP(c, hipStreamSynchronize(s));
-    return SFK_OK;
+    return wait.done();
   }
   const double ck = r->kernel == SFK_KERNEL_GAUSS_TRUNC3 ? ck_gauss_trunc3() : ck_epanechnikov();
   const double nu = r->norm == SFK_NORM_COUNT ? 1.0 : 1.0 / (double)n_b;
@@ -1321,12 +1339,11 @@ sfk_status eval_subcloud(sfk_ctx c, sfk_tree t, const sfk_roi* r, bool count_mod
     if (count_mode) g.scale = 1.0;
     SFK_TRY(run_one(sc.view(g.pp), g, r->d_out));
     SFK_HIP(c, hipStreamSynchronize(s));
-    return SFK_OK;
+    return wait.done();
   }
 
   // ---- MBE (Section 3.1) ----
   // Eq. 1: exact order statistics of the three axes
-  TmpBuf stmp(c), ell_d(c), pilot(c), pden(c), bsum(c), ave_d(c), ellj_d(c);
   SFK_TRY(stmp.get(sfk::axis_select_tmp_bytes(), "selection scratch"));
   SFK_TRY(ell_d.get(4 * sizeof(float), "smoothing lengths"));
   SFK_HIP(c, sfk::launch_axis_select(sc.axes.as<float>(), n_b, r->lo, r->hi, r->res, stmp.b.p,
@@ -1423,7 +1440,7 @@ sfk_status eval_subcloud(sfk_ctx c, sfk_tree t, const sfk_roi* r, bool count_mod
     set_err(c, "%s", kErrLeafIds);
     return SFK_E_INTERNAL;
   }
-  return SFK_OK;
+  return wait.done();
 }
 
 constexpr int kEstGrid = 32;  // cells per axis of the particle-count table

@@ -24,3 +24,59 @@ def test_support_counts_on_a_ragged_last_leaf(ctx, torch, n, kernel):
         assert np.array_equal(cnt, oracle.support_counts(pts, roi, h2=h2)), (lo, hi)
         check_density(ctx.eval_roi(tree, roi).cpu().numpy(), oracle.density(pts, roi, h2=h2), lo)
     tree.close()
+
+
+
+class _Memory:
+    """torch's allocator as a context sees it: it refuses call `fail_at` with
+    work left on `stream`, and notes what is on it when memory comes back."""
+
+    def __init__(self, torch, monkeypatch, stream):
+        self.calls, self.fail_at, self.idle_at_free = 0, -1, []
+        alloc, free = torch.cuda.caching_allocator_alloc, torch.cuda.caching_allocator_delete
+
+        def take(n, device):
+            self.calls += 1
+            if self.calls == self.fail_at:
+                with torch.cuda.stream(stream):
+                    torch.cuda._sleep(30_000_000)
+                return None
+            return alloc(n, device)
+
+        def give(p):
+            if 0 <= self.fail_at <= self.calls:
+                self.idle_at_free.append(stream.query())
+            free(p)
+
+        monkeypatch.setattr(torch.cuda, "caching_allocator_alloc", take)
+        monkeypatch.setattr(torch.cuda, "caching_allocator_delete", give)
+
+
+@pytest.mark.parametrize("bw", ["mbe", "fixed", "per_point"])
+def test_nothing_is_given_back_while_kernels_run(sfk, torch, monkeypatch, bw):
+    # each allocation of an in-box evaluation refused once: the call fails only
+    # when its stream is done with what it gives back
+    pts = synth.clumpy_cloud(20_000, 3)
+    roi = Roi((0.2,) * 3, (0.8,) * 3, (20,) * 3, bw=bw, set="in_roi", h=(0.05,) * 3)
+    s = torch.cuda.Stream()
+    mem = _Memory(torch, monkeypatch, s)
+    out = torch.empty(roi.n_nodes, device="cuda")
+    refused, last = 0, False
+    for k in range(1, 80):
+        with sfk.Context(0) as c:
+            tree = c.build_tree(dev(torch, pts), knn_k=5 if bw == "per_point" else 0)
+            torch.cuda.synchronize()
+            mem.fail_at, mem.idle_at_free = mem.calls + k, []
+            try:
+                c.eval_roi(tree, roi, out=out, stream=s)
+            except sfk.SfkError as e:
+                assert e.status == 2 and s.query(), k  # SFK_E_NOMEM
+            assert all(mem.idle_at_free), k
+            last = mem.calls < mem.fail_at
+            mem.fail_at = -1
+            torch.cuda.synchronize()
+            tree.close()
+        if last:
+            break
+        refused += 1
+    assert last and refused >= 10
