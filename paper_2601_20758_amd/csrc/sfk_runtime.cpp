@@ -384,7 +384,12 @@ struct TmpBuf {
   sfk_ctx c;
   DevBuf b;
   explicit TmpBuf(sfk_ctx cc) : c(cc) {}
-  ~TmpBuf() { raw_free(c, b.p, b.bytes); }
+  ~TmpBuf() { release(); }
+  void release() {
+    raw_free(c, b.p, b.bytes);
+    b.p = nullptr;
+    b.bytes = 0;
+  }
   sfk_status get(size_t bytes, const char* what) {
     bytes = round_bytes(std::max<size_t>(bytes, 256));
     b.p = raw_alloc(c, bytes);
@@ -1202,9 +1207,16 @@ struct SubCloud {
   int32_t n_leaves = 0, n_levels = 0, total_nodes = 0;
   int32_t off[SFK_MAX_LEVELS], cnt[SFK_MAX_LEVELS];
   TmpBuf pts, perm, nodes, node_ih, pparam, axes;
-  TmpBuf cnt_b, pos, stmp;  // per leaf of the cloud; live until the evaluation is done
+  // per leaf of the cloud, read by the kernels of make_subcloud, which does not
+  // wait for them: released once something has
+  TmpBuf cnt_b, pos, stmp;
   explicit SubCloud(sfk_ctx c)
       : pts(c), perm(c), nodes(c), node_ih(c), pparam(c), axes(c), cnt_b(c), pos(c), stmp(c) {}
+  void release_scratch() {
+    cnt_b.release();
+    pos.release();
+    stmp.release();
+  }
   TreeView view(int pp) const {
     TreeView tv{};
     tv.pts = pts.as<const float4>();
@@ -1314,6 +1326,15 @@ sfk_status eval_subcloud(sfk_ctx c, sfk_tree t, const sfk_roi* r, bool count_mod
     return launch_kernels(c, tv, ts, g.count_mode ? 0 : g.kk, g.pp, g.count_mode, ws, 1,
                           n_tiles, ch, s);
   };
+  // Memory that is refused may be the sub-cloud's scratch, over all the cloud's
+  // leaves: wait for its kernels, give it back and ask again.
+  auto with_room = [&](auto ask) -> sfk_status {
+    const sfk_status st1 = ask();
+    if (st1 != SFK_E_NOMEM) return st1;
+    SFK_HIP(c, hipStreamSynchronize(s));
+    sc.release_scratch();
+    return ask();
+  };
 
   if (!mbe) {
     GroupRoi g{};
@@ -1337,7 +1358,7 @@ sfk_status eval_subcloud(sfk_ctx c, sfk_tree t, const sfk_roi* r, bool count_mod
       g.scale = ck * nu / ((double)h[0] * (double)h[1] * (double)h[2]);
     }
     if (count_mode) g.scale = 1.0;
-    SFK_TRY(run_one(sc.view(g.pp), g, r->d_out));
+    SFK_TRY(with_room([&] { return run_one(sc.view(g.pp), g, r->d_out); }));
     SFK_HIP(c, hipStreamSynchronize(s));
     return wait.done();
   }
@@ -1354,7 +1375,7 @@ sfk_status eval_subcloud(sfk_ctx c, sfk_tree t, const sfk_roi* r, bool count_mod
   if (dbg && dbg->ell0) std::memcpy(dbg->ell0, ell0, sizeof ell0);
 
   // pilot grid (Eq. 2): uniform ellipsoid l_k over the particles in B
-  SFK_TRY(pilot.get(sizeof(float) * (size_t)m, "pilot grid"));
+  SFK_TRY(with_room([&] { return pilot.get(sizeof(float) * (size_t)m, "pilot grid"); }));
   GroupRoi gp{};
   gp.roi = r;
   gp.kk = KK_EPAN;
@@ -1362,7 +1383,8 @@ sfk_status eval_subcloud(sfk_ctx c, sfk_tree t, const sfk_roi* r, bool count_mod
   gp.c2 = 1.0f;
   for (int k = 0; k < 3; ++k) gp.ih[k] = (float)(1.0 / (double)ell0[k]);
   gp.scale = ck * nu / ((double)ell0[0] * (double)ell0[1] * (double)ell0[2]);
-  SFK_TRY(run_one(sc.view(PP_UNIFORM), gp, pilot.as<float>()));
+  SFK_TRY(with_room([&] { return run_one(sc.view(PP_UNIFORM), gp, pilot.as<float>()); }));
+  sc.release_scratch();  // (its kernels were done when ell0 was read)
 
   // ASL (Eqs. 5-6): trilinear pilot at each particle, mean, lengths
   const int nblk = (int)((n_b + 255) / 256);

@@ -80,3 +80,43 @@ def test_nothing_is_given_back_while_kernels_run(sfk, torch, monkeypatch, bw):
             break
         refused += 1
     assert last and refused >= 10
+
+
+@pytest.mark.parametrize("bw", ["mbe", "fixed", "per_point"])
+def test_scratch_makes_room_for_the_grid(sfk, torch, monkeypatch, bw):
+    # a few particles of a large cloud: the scratch over the cloud's leaves, the
+    # evaluation's first three allocations, is given back when the grid's own
+    # memory does not fit beside it
+    pts = synth.clumpy_cloud(3_000_000, 4)
+    roi = Roi((0.4,) * 3, (0.5,) * 3, (24,) * 3, bw=bw, set="in_roi", h=(0.01,) * 3)
+    alloc, free = torch.cuda.caching_allocator_alloc, torch.cuda.caching_allocator_delete
+    held, calls, need, limit = {}, [0], [0], [None]
+
+    def take(n, device):
+        calls[0] += 1
+        used = sum(b for b, _ in held.values()) + n
+        if limit[0] is not None and used > limit[0]:
+            return None
+        p = alloc(n, device)
+        held[p] = n, calls[0]
+        if calls[0] > 8:  # past the sub-cloud
+            used -= sum(b for b, i in held.values() if 1 <= i <= 3)
+        need[0] = max(need[0], used)
+        return p
+
+    def give(p):
+        held.pop(p)
+        free(p)
+
+    monkeypatch.setattr(torch.cuda, "caching_allocator_alloc", take)
+    monkeypatch.setattr(torch.cuda, "caching_allocator_delete", give)
+    grids, room = [], None
+    for _ in range(2):
+        with sfk.Context(0) as c:
+            calls[0] = -10_000
+            tree = c.build_tree(dev(torch, pts), knn_k=5 if bw == "per_point" else 0)
+            limit[0], need[0], calls[0] = room, 0, 0
+            grids.append(c.eval_roi(tree, roi).cpu().numpy())
+            limit[0], room, calls[0] = None, need[0], -10_000
+            tree.close()
+    assert np.array_equal(*grids)
