@@ -2245,6 +2245,18 @@ sfk_status sfk_set_eval_opts(sfk_ctx c, const sfk_eval_opts* opts) {
   return SFK_OK;
 }
 
+// What a direct call left on its stream, a refused one too (a new buffer's
+// counters are cleared there), comes before the next call on another stream.
+static sfk_status direct_enqueued(sfk_ctx c, hipStream_t s, sfk_status st) {
+  const hipError_t e = hipEventRecord(c->direct_last, s);
+  if (st == SFK_OK) SFK_HIP(c, e);
+  c->direct_last_valid = true;
+  c->direct_last_stream = s;
+  c->direct_ws.last_use = c->direct_last;
+  c->direct_ws.last_use_valid = true;
+  return st;
+}
+
 // Stream-ordered single ROI on the caller's stream.
 // CLOUD-set ROIs in one batch on the caller's stream (the direct path's
 // workspace and staging ring), optionally all with one tile shape.
@@ -2261,13 +2273,7 @@ static sfk_status eval_direct_cloud(sfk_ctx c, sfk_tree t, const std::vector<con
     set_err(c, "%s (reported by the next call on the context)", kErrLeafIds);
     return SFK_E_INTERNAL;
   }
-  SFK_TRY(enqueue_cloud_rois(c, t, v, count_mode, c->direct_ws, st, s, force_ts));
-  SFK_HIP(c, hipEventRecord(c->direct_last, s));
-  c->direct_last_valid = true;
-  c->direct_last_stream = s;
-  c->direct_ws.last_use = c->direct_last;
-  c->direct_ws.last_use_valid = true;
-  return SFK_OK;
+  return direct_enqueued(c, s, enqueue_cloud_rois(c, t, v, count_mode, c->direct_ws, st, s, force_ts));
 }
 
 static sfk_status eval_direct(sfk_ctx c, sfk_tree t, const sfk_roi* roi, hipStream_t s,
@@ -2280,13 +2286,9 @@ static sfk_status eval_direct(sfk_ctx c, sfk_tree t, const sfk_roi* roi, hipStre
     SFK_HIP(c, hipStreamWaitEvent(s, c->direct_last, 0));
   Staging& st = c->direct_st[c->direct_next];
   c->direct_next = (c->direct_next + 1) % kStagingRing;
+  // (a call that fails here has waited for its stream)
   SFK_TRY(eval_subcloud(c, t, roi, count_mode, shape_of(1), c->direct_ws, st, s, nullptr));
-  SFK_HIP(c, hipEventRecord(c->direct_last, s));
-  c->direct_last_valid = true;
-  c->direct_last_stream = s;
-  c->direct_ws.last_use = c->direct_last;
-  c->direct_ws.last_use_valid = true;
-  return SFK_OK;
+  return direct_enqueued(c, s, SFK_OK);
 }
 
 sfk_status sfk_eval_roi(sfk_ctx c, sfk_tree t, const sfk_roi* roi, void* hip_stream) {
