@@ -837,17 +837,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KM <= 32 ? 
   if (skip_if && *skip_if > 0.0f) return;  // the build fails: non-finite coordinates
   __shared__ float4 lds_pts[4][SFK_LEAF];
   __shared__ int32_t lds_stack[4][SFK_STACK];
-  __shared__ float lds_queue[4][kKnnRows * 64];
+  __shared__ int32_t lds_queue[4][kKnnRows * 64];  // distances as bit patterns
   __shared__ int32_t lds_ord[4][kKnnList];
   __shared__ float4 lds_sb[4][2 * kKnnSubPerLeaf];
   const int lane = lane_id(), wave = threadIdx.x >> 6;
   float4* lp = lds_pts[wave];
   float4* lsb = lds_sb[wave];
-  float* queue = lds_queue[wave];
+  int32_t* queue = lds_queue[wave];
   int32_t* stack = lds_stack[wave];
   // the leaves held by the walk live in the queue's LDS: it is empty then
-  float* lkey = queue;
-  int32_t* lid = reinterpret_cast<int32_t*>(queue + kKnnList);
+  int32_t* lkey = queue;
+  int32_t* lid = queue + kKnnList;
   int32_t* ord = lds_ord[wave];
   const int nl = tv.n_leaves;
   const NodeBox* leaf_box = tv.nodes + tv.level_off[0];
@@ -890,10 +890,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KM <= 32 ? 
     // past a column's end hold +inf, but for the first of them, which may
     // hold a distance that was not taken.
     auto flush = [&]() {
-      int* top = reinterpret_cast<int*>(queue) + lane;
+      int32_t* top = queue + lane;
       top[qn * 64] = kInf;
       qn = max(qn - kKnnRun, 0);
-      int* c = top + qn * 64;
+      int32_t* c = top + qn * 64;
       int b[kKnnRun];
 #pragma unroll
       for (int i = 0; i < kKnnRun; ++i) b[i] = c[i * 64];
@@ -903,7 +903,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KM <= 32 ? 
     };
     // rows [0, n) of the queue to +inf
     auto clear_rows = [&](int n) {
-      for (int i = 0; i < n; ++i) reinterpret_cast<int*>(queue)[i * 64 + lane] = kInf;
+      for (int i = 0; i < n; ++i) queue[i * 64 + lane] = kInf;
     };
 
     // One candidate leaf, its particle for this lane in pc and its eight
@@ -953,7 +953,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KM <= 32 ? 
         for (int u = 0; u < kKnnSub; ++u) {
           const float4 p = lp[j * kKnnSub + u];
           const float x = canon_d2(q.x, q.y, q.z, p.x, p.y, p.z);
-          queue[qn * 64 + lane] = x;  // own column: no other lane reads it
+          queue[qn * 64 + lane] = __float_as_int(x);  // own column: no other lane reads it
           qn += x < thr ? 1 : 0;
         }
       }
@@ -1002,7 +1002,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KM <= 32 ? 
           if (take) {
             const int pos = ln + popc64(tm & lanemask_lt());
             lid[pos] = child;
-            lkey[pos] = key;
+            lkey[pos] = __float_as_int(key);
           }
           ln += popc64(tm);
         } else {
@@ -1039,7 +1039,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KM <= 32 ? 
                                  : tau * __builtin_ldexpf(1.0f, -2 * (kKnnBands - 1 - band));
         for (int i0 = 0; i0 < ln; i0 += 64) {
           const int i = i0 + lane;
-          const float key = i < ln ? lkey[i] : -2.0f;
+          const float key = i < ln ? __int_as_float(lkey[i]) : -2.0f;
           const bool inb = key > lo_lim && key <= hi_lim;
           uint64_t m = ballot(inb);
           if (!m) continue;
