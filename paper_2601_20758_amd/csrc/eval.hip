@@ -205,6 +205,7 @@ __global__ __launch_bounds__(256) void k_tile_count(TreeView tv, const BatchHdr*
                                                     const int32_t* __restrict__ roi_leaves,
                                                     const int32_t* __restrict__ roi_nl,
                                                     int32_t* __restrict__ tile_cnt,
+                                                    int32_t* __restrict__ tile_fit,
                                                     int32_t* __restrict__ tile_done,
                                                     int32_t* __restrict__ tile_slots) {
   __shared__ int32_t lds_stack[4][SFK_STACK];
@@ -227,6 +228,7 @@ __global__ __launch_bounds__(256) void k_tile_count(TreeView tv, const BatchHdr*
                 });
     if (lane == 0) {
       tile_cnt[t] = cnt;
+      tile_fit[t] = R.chunk;
       tile_done[t] = 0;
     }
   }
@@ -313,12 +315,13 @@ __global__ __launch_bounds__(256) void k_tile_fill(
 
 // ---------------------------------------------------------------------------
 // work plan: per tile, leaf_off (prefix of candidate leaves), partial_off
-// (prefix of partial-sum slots of split tiles), tile_fit (how the tile is
-// evaluated, below) and chunk_off (prefix of work items). Three launches over
-// blocks of kPlanNT consecutive tiles (coalesced; no block waits for
-// another): per-block sums of leaves and partial slots; then each block adds
-// the sums of the blocks before it, scans its tiles, decides each tile's mode
-// from the prefixes and sums its work items; then the same for the items.
+// (prefix of partial-sum slots of split tiles), tile_fit (the count pass left
+// the tile's chunk there: how the tile is evaluated, below) and chunk_off
+// (prefix of work items). Three launches over blocks of kPlanNT consecutive
+// tiles (coalesced; no block waits for another): per-block sums of leaves and
+// partial slots; then each block adds the sums of the blocks before it, scans
+// its tiles, decides each tile's mode from the prefixes and its number of work
+// items (kept in chunk_off) and sums those; then the same for the items.
 // Block 0 of the last launch writes the totals. A batch of at most kPlanNT
 // tiles takes one launch of one block instead.
 // ---------------------------------------------------------------------------
@@ -354,15 +357,15 @@ __device__ __forceinline__ int64_t sum_before(const int64_t* __restrict__ bs, in
 }
 
 __global__ __launch_bounds__(kPlanNT) void k_plan_sums(const int32_t* __restrict__ tile_cnt,
+                                                       const int32_t* __restrict__ tile_fit,
                                                        const BatchHdr* __restrict__ hdr,
-                                                       int chunk_leaves,
                                                        int64_t* __restrict__ bs) {
   __shared__ int64_t lds[kPlanNT / 64];
   const int64_t n_tiles = hdr->n_tiles;
   const int64_t t = (int64_t)blockIdx.x * kPlanNT + threadIdx.x;
   if ((int64_t)blockIdx.x * kPlanNT >= n_tiles) return;  // whole block past the end
   const int64_t cnt = t < n_tiles ? tile_cnt[t] : 0;
-  const int64_t nch = plan_chunks(cnt, chunk_leaves);
+  const int64_t nch = plan_chunks(cnt, t < n_tiles ? tile_fit[t] : 1);
   const int64_t sl = block_sum(cnt, lds);
   const int64_t sp = block_sum(t < n_tiles ? plan_partials(nch, hdr->splat) : 0, lds);
   if (threadIdx.x == 0) {
@@ -373,9 +376,10 @@ __global__ __launch_bounds__(kPlanNT) void k_plan_sums(const int32_t* __restrict
 
 __global__ __launch_bounds__(kPlanNT) void k_plan_modes(const int32_t* __restrict__ tile_cnt,
                                                         const BatchHdr* __restrict__ hdr,
-                                                        int chunk_leaves, int64_t* __restrict__ bs,
+                                                        int64_t* __restrict__ bs,
                                                         int64_t* __restrict__ leaf_off,
                                                         int64_t* __restrict__ partial_off,
+                                                        int64_t* __restrict__ chunk_off,
                                                         int32_t* __restrict__ tile_fit) {
   __shared__ int64_t lds[kPlanNT / 64];
   const int64_t n_tiles = hdr->n_tiles;
@@ -387,7 +391,7 @@ __global__ __launch_bounds__(kPlanNT) void k_plan_modes(const int32_t* __restric
   const int64_t t = (int64_t)blockIdx.x * kPlanNT + threadIdx.x;
   const bool v = t < n_tiles;
   const int64_t cnt = v ? tile_cnt[t] : 0;
-  const int64_t nch = plan_chunks(cnt, chunk_leaves);
+  const int64_t nch = plan_chunks(cnt, v ? tile_fit[t] : 1);
   const int64_t pneed = v ? plan_partials(nch, hdr->splat) : 0;
   int64_t tot;
   const int64_t lo = base_l + block_excl_scan<kPlanNT>(cnt, &tot, lds);
@@ -401,21 +405,19 @@ __global__ __launch_bounds__(kPlanNT) void k_plan_modes(const int32_t* __restric
   if (v) {
     leaf_off[t] = lo;
     partial_off[t] = po;
+    chunk_off[t] = nit;
     tile_fit[t] = mode;
   }
   const int64_t si = block_sum(nit, lds);
   if (threadIdx.x == 0) bs[3 * blockIdx.x + 2] = si;
 }
 
-__global__ __launch_bounds__(kPlanNT) void k_plan_items(const int32_t* __restrict__ tile_cnt,
-                                                        BatchHdr* __restrict__ hdr,
+__global__ __launch_bounds__(kPlanNT) void k_plan_items(BatchHdr* __restrict__ hdr,
                                                         int32_t* __restrict__ claims,
-                                                        int chunk_leaves,
                                                         const int64_t* __restrict__ bs,
                                                         int64_t* __restrict__ leaf_off,
                                                         int64_t* __restrict__ partial_off,
-                                                        int64_t* __restrict__ chunk_off,
-                                                        const int32_t* __restrict__ tile_fit) {
+                                                        int64_t* __restrict__ chunk_off) {
   __shared__ int64_t lds[kPlanNT / 64];
   const int64_t n_tiles = hdr->n_tiles;
   const int64_t nb = (n_tiles + kPlanNT - 1) / kPlanNT;
@@ -442,9 +444,7 @@ __global__ __launch_bounds__(kPlanNT) void k_plan_items(const int32_t* __restric
   const int64_t base_c = sum_before(bs, 3, 2, blockIdx.x, lds);
   const int64_t t = (int64_t)blockIdx.x * kPlanNT + threadIdx.x;
   const bool v = t < n_tiles;
-  int64_t nit = 0;
-  if (v && tile_cnt[t] > 0)
-    nit = tile_fit[t] == kModeWalkTile ? 1 : plan_chunks(tile_cnt[t], chunk_leaves);
+  const int64_t nit = v ? chunk_off[t] : 0;
   int64_t tot;
   const int64_t co = base_c + block_excl_scan<kPlanNT>(nit, &tot, lds);
   if (v) chunk_off[t] = co;
@@ -545,7 +545,7 @@ __device__ __forceinline__ void agent_writes_done() {
 template <int TX, int TY, int TZ, int KK, int PP, bool CNT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_eval(
     TreeView tv, const RoiDev* __restrict__ rois, const double* __restrict__ coords,
-    int chunk_leaves, const int64_t* __restrict__ leaf_off, const int64_t* __restrict__ chunk_off,
+    const int64_t* __restrict__ leaf_off, const int64_t* __restrict__ chunk_off,
     const int64_t* __restrict__ partial_off, const int32_t* __restrict__ tile_cnt,
     const int32_t* __restrict__ tile_fit, const int32_t* __restrict__ leaves,
     const int32_t* __restrict__ item_tile, double* __restrict__ partials,
@@ -608,6 +608,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     const int t = wave_uniform(item_tile[item]);
     const TileGeo g = tile_geo<TX, TY, TZ>(rois, n_rois, coords, t);
     const RoiDev& R = rois[g.r];
+    const int chunk_leaves = wave_uniform(R.chunk);
     const double* cx = coords + R.coord_off;
     const double* cy = cx + R.res[0];
     const double* cz = cy + R.res[1];
@@ -1075,7 +1076,7 @@ __device__ __forceinline__ int64_t claim_item(int32_t* __restrict__ claims, int6
 template <int KK, bool CNT>
 __global__ __launch_bounds__(256) void k_splat(
     TreeView tv, const RoiDev* __restrict__ rois, const double* __restrict__ coords,
-    int chunk_leaves, const int64_t* __restrict__ leaf_off, const int64_t* __restrict__ chunk_off,
+    const int64_t* __restrict__ leaf_off, const int64_t* __restrict__ chunk_off,
     const int64_t* __restrict__ partial_off, const int32_t* __restrict__ tile_cnt,
     const int32_t* __restrict__ tile_fit, const int32_t* __restrict__ leaves,
     const int32_t* __restrict__ item_tile, double* __restrict__ partials,
@@ -1277,7 +1278,7 @@ __global__ __launch_bounds__(256) void k_splat(
       splat(p);
     };
 
-    const int cnt = tile_cnt[t];
+    const int cnt = tile_cnt[t], chunk_leaves = R.chunk;
     const int nch = (cnt + chunk_leaves - 1) / chunk_leaves;
     const int mode = tile_fit[t];
     const int c = (int)(item - chunk_off[t]);
@@ -2012,12 +2013,12 @@ int tile_grid_blocks(int64_t n_tiles) { return grid_for(n_tiles); }
 hipError_t launch_tile_count(TreeView tv, const BatchHdr* hdr, const RoiDev* rois,
                              const double* coords, const int32_t* roi_leaves,
                              const int32_t* roi_nl, TileShape ts, int grid_blocks,
-                             int32_t* tile_cnt, int32_t* tile_done, int32_t* tile_slots,
-                             hipStream_t s) {
+                             int32_t* tile_cnt, int32_t* tile_fit, int32_t* tile_done,
+                             int32_t* tile_slots, hipStream_t s) {
   const int nb = std::max(1, grid_blocks);
 #define SFK_L(X, Y, Z)                                                                      \
   hipLaunchKernelGGL((k_tile_count<X, Y, Z>), dim3(nb), dim3(256), 0, s, tv, hdr, rois,  \
-                     coords, roi_leaves, roi_nl, tile_cnt, tile_done, tile_slots)
+                     coords, roi_leaves, roi_nl, tile_cnt, tile_fit, tile_done, tile_slots)
   SFK_SHAPE_SWITCH(ts, SFK_L);
 #undef SFK_L
   return hipGetLastError();
@@ -2027,7 +2028,6 @@ hipError_t launch_tile_count(TreeView tv, const BatchHdr* hdr, const RoiDev* roi
 __global__ __launch_bounds__(kPlanNT) void k_plan_one(const int32_t* __restrict__ tile_cnt,
                                                       BatchHdr* __restrict__ hdr,
                                                       int32_t* __restrict__ claims,
-                                                      int chunk_leaves,
                                                       int64_t* __restrict__ leaf_off,
                                                       int64_t* __restrict__ partial_off,
                                                       int64_t* __restrict__ chunk_off,
@@ -2038,7 +2038,7 @@ __global__ __launch_bounds__(kPlanNT) void k_plan_one(const int32_t* __restrict_
   const int64_t t = threadIdx.x;
   const bool v = t < n_tiles;
   const int64_t cnt = v ? tile_cnt[t] : 0;
-  const int64_t nch = plan_chunks(cnt, chunk_leaves);
+  const int64_t nch = plan_chunks(cnt, v ? tile_fit[t] : 1);
   const int64_t pneed = v ? plan_partials(nch, hdr->splat) : 0;
   int64_t tl, tp, tc;
   const int64_t lo = block_excl_scan<kPlanNT>(cnt, &tl, lds);
@@ -2074,21 +2074,21 @@ int plan_blocks(int64_t max_tiles) {
   return (int)std::max<int64_t>(1, (max_tiles + kPlanNT - 1) / kPlanNT);
 }
 
-hipError_t launch_plan(const int32_t* tile_cnt, BatchHdr* hdr, int32_t* claims, int chunk_leaves,
-                       int64_t* leaf_off, int64_t* partial_off, int64_t* chunk_off,
-                       int32_t* tile_fit, int64_t* plan_tmp, int64_t max_tiles, hipStream_t s) {
+hipError_t launch_plan(const int32_t* tile_cnt, BatchHdr* hdr, int32_t* claims, int64_t* leaf_off,
+                       int64_t* partial_off, int64_t* chunk_off, int32_t* tile_fit,
+                       int64_t* plan_tmp, int64_t max_tiles, hipStream_t s) {
   const int nb = plan_blocks(max_tiles);
   if (nb == 1) {
     hipLaunchKernelGGL(k_plan_one, dim3(1), dim3(kPlanNT), 0, s, tile_cnt, hdr, claims,
-                       chunk_leaves, leaf_off, partial_off, chunk_off, tile_fit);
+                       leaf_off, partial_off, chunk_off, tile_fit);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(k_plan_sums, dim3(nb), dim3(kPlanNT), 0, s, tile_cnt, hdr, chunk_leaves,
+  hipLaunchKernelGGL(k_plan_sums, dim3(nb), dim3(kPlanNT), 0, s, tile_cnt, tile_fit, hdr,
                      plan_tmp);
-  hipLaunchKernelGGL(k_plan_modes, dim3(nb), dim3(kPlanNT), 0, s, tile_cnt, hdr, chunk_leaves,
-                     plan_tmp, leaf_off, partial_off, tile_fit);
-  hipLaunchKernelGGL(k_plan_items, dim3(nb), dim3(kPlanNT), 0, s, tile_cnt, hdr, claims,
-                     chunk_leaves, plan_tmp, leaf_off, partial_off, chunk_off, tile_fit);
+  hipLaunchKernelGGL(k_plan_modes, dim3(nb), dim3(kPlanNT), 0, s, tile_cnt, hdr, plan_tmp,
+                     leaf_off, partial_off, chunk_off, tile_fit);
+  hipLaunchKernelGGL(k_plan_items, dim3(nb), dim3(kPlanNT), 0, s, hdr, claims, plan_tmp,
+                     leaf_off, partial_off, chunk_off);
   return hipGetLastError();
 }
 
@@ -2113,8 +2113,8 @@ template <int X, int Y, int Z>
 static hipError_t launch_eval_shape(int kk, int pp, bool cnt, int grid, int n_cu, int max_blocks,
                                     hipStream_t s,
                                     TreeView tv, const RoiDev* rois, const double* coords,
-                                    int chunk_leaves, const int64_t* leaf_off,
-                                    const int64_t* chunk_off, const int64_t* partial_off,
+                                    const int64_t* leaf_off, const int64_t* chunk_off,
+                                    const int64_t* partial_off,
                                     const int32_t* tile_cnt, const int32_t* tile_fit,
                                     const int32_t* leaves, const int32_t* item_tile,
                                     double* partials, int32_t* tile_done, BatchHdr* hdr,
@@ -2131,7 +2131,7 @@ static hipError_t launch_eval_shape(int kk, int pp, bool cnt, int grid, int n_cu
     }                                                                                          \
     const int g_ = grid > 0 ? grid : std::max(1, std::min(n_cu * occ_, max_blocks));          \
     hipLaunchKernelGGL((k_eval<X, Y, Z, KK, PP, C>), dim3(g_), dim3(256), 0, s, tv, rois,      \
-                       coords, chunk_leaves, leaf_off, chunk_off, partial_off, tile_cnt,       \
+                       coords, leaf_off, chunk_off, partial_off, tile_cnt,                     \
                        tile_fit, leaves, item_tile, partials, tile_done, hdr, claims);         \
   } while (0)
   if (cnt) {
@@ -2153,7 +2153,7 @@ static hipError_t launch_eval_shape(int kk, int pp, bool cnt, int grid, int n_cu
 
 hipError_t launch_eval(TreeView tv, const BatchHdr* hdr_c, const RoiDev* rois,
                        const double* coords, TileShape ts, int kk, int pp, bool cnt,
-                       int chunk_leaves, const int64_t* leaf_off, const int64_t* chunk_off,
+                       const int64_t* leaf_off, const int64_t* chunk_off,
                        const int64_t* partial_off, const int32_t* tile_cnt,
                        const int32_t* tile_fit, const int32_t* leaves, const int32_t* item_tile,
                        double* partials, int32_t* tile_done, BatchHdr* hdr, int32_t* claims,
@@ -2174,7 +2174,7 @@ hipError_t launch_eval(TreeView tv, const BatchHdr* hdr_c, const RoiDev* rois,
     }                                                                                         \
     const int g_ = grid_blocks > 0 ? grid_blocks : std::max(1, std::min(n_cu * occ_, max_blocks)); \
     hipLaunchKernelGGL((k_splat<KK, C>), dim3(g_), dim3(256), 0, s, tv, rois, coords,         \
-                       chunk_leaves, leaf_off, chunk_off, partial_off, tile_cnt, tile_fit,    \
+                       leaf_off, chunk_off, partial_off, tile_cnt, tile_fit,                  \
                        leaves, item_tile, partials, tile_done, hdr, claims);                  \
   } while (0)
     if (cnt)
@@ -2189,7 +2189,7 @@ hipError_t launch_eval(TreeView tv, const BatchHdr* hdr_c, const RoiDev* rois,
 #define SFK_L(X, Y, Z)                                                                        \
   return launch_eval_shape<X, Y, Z>(kk, pp, cnt, grid_blocks, n_cu, max_blocks, s, tv, rois, \
                                     coords,                                                   \
-                                    chunk_leaves, leaf_off, chunk_off, partial_off, tile_cnt, \
+                                    leaf_off, chunk_off, partial_off, tile_cnt,               \
                                     tile_fit, leaves, item_tile, partials, tile_done, hdr,    \
                                     claims)
   if ((ts).tx == 4 && (ts).ty == 4 && (ts).tz == 4) {

@@ -55,7 +55,8 @@ struct alignas(16) RoiDev {
   int32_t coord_off;     // into the batch coordinate table: x, then y, then z
   float* out;
   int32_t pp_mode;       // PPMode of this evaluation
-  int32_t pad_[3];
+  int32_t chunk;         // leaves per work item
+  int32_t pad_[2];
 };
 
 // Device-side header of one batch, staged by the host together with the ROI
@@ -229,18 +230,20 @@ hipError_t launch_fill_f32(float* p, int64_t n, float v, hipStream_t s);
 hipError_t launch_roi_coords(TreeView tv, const BatchHdr* hdr, const RoiDev* rois, int grid_rois,
                              double* coords, int32_t* roi_leaves, int32_t* roi_nl,
                              hipStream_t s);
-// tile_slots: hdr->slot_cap int32 per tile
+// tile_slots: hdr->slot_cap int32 per tile; tile_fit: the tile's chunk, for the
+// plan
 hipError_t launch_tile_count(TreeView tv, const BatchHdr* hdr, const RoiDev* rois,
                              const double* coords, const int32_t* roi_leaves,
                              const int32_t* roi_nl, TileShape ts, int grid_blocks,
-                             int32_t* tile_cnt, int32_t* tile_done, int32_t* tile_slots,
-                             hipStream_t s);
+                             int32_t* tile_cnt, int32_t* tile_fit, int32_t* tile_done,
+                             int32_t* tile_slots, hipStream_t s);
 // plan_tmp: 3 int64 per block of plan_blocks(max_tiles); max_tiles bounds
 // the header's tile count (the grid of a captured graph uses the capacity)
 int plan_blocks(int64_t max_tiles);
-hipError_t launch_plan(const int32_t* tile_cnt, BatchHdr* hdr, int32_t* claims, int chunk_leaves,
-                       int64_t* leaf_off, int64_t* partial_off, int64_t* chunk_off,
-                       int32_t* tile_fit, int64_t* plan_tmp, int64_t max_tiles, hipStream_t s);
+// tile_fit: the tiles' chunks in, their modes out
+hipError_t launch_plan(const int32_t* tile_cnt, BatchHdr* hdr, int32_t* claims, int64_t* leaf_off,
+                       int64_t* partial_off, int64_t* chunk_off, int32_t* tile_fit,
+                       int64_t* plan_tmp, int64_t max_tiles, hipStream_t s);
 // claims: the work-claim counters, whose error word the slot copy may set
 // partials/partial_off: bricks (hdr->splat) zero the node sums of their
 // partial slot here when they are split into several work items
@@ -253,7 +256,7 @@ hipError_t launch_tile_fill(TreeView tv, const BatchHdr* hdr, const RoiDev* rois
                             const int64_t* partial_off, hipStream_t s);
 hipError_t launch_eval(TreeView tv, const BatchHdr* hdr_c, const RoiDev* rois,
                        const double* coords, TileShape ts, int kk, int pp, bool cnt,
-                       int chunk_leaves, const int64_t* leaf_off, const int64_t* chunk_off,
+                       const int64_t* leaf_off, const int64_t* chunk_off,
                        const int64_t* partial_off, const int32_t* tile_cnt,
                        const int32_t* tile_fit, const int32_t* leaves, const int32_t* item_tile,
                        double* partials, int32_t* tile_done, BatchHdr* hdr, int32_t* claims,

@@ -115,7 +115,7 @@ struct Staging {
 struct GraphCache {
   bool valid = false;
   TileShape ts{0, 0, 0};
-  int kk = 0, pp = 0, ch = 0, nm = 0;
+  int kk = 0, pp = 0, nm = 0;
   bool cnt = false;
   bool interleave = false;  // captured with one-wave-per-tile evaluation grids
   sfk_tree tree = nullptr;
@@ -670,16 +670,10 @@ int brick_batch_chunk(sfk_ctx c, int64_t tiles, int64_t tree_leaves) {
   if (c->opts.chunk_leaves > 0) return c->opts.chunk_leaves;
   return tiles < 64 && tree_leaves < 2048 ? 8 : kBrickChunkLeaves;
 }
-int chunk_leaves_of(sfk_ctx c, TileShape ts, const sfk_roi* r) {
-  const int32_t t[3] = {ts.tx, ts.ty, ts.tz};
-  int64_t tiles = 1;
-  for (int k = 0; k < 3; ++k) tiles *= (r->res[k] + t[k] - 1) / t[k];
-  return chunk_leaves_of(c, ts, tiles);
-}
 
 // Fill RoiDev descriptors for rois[0..n) and the per-group tile total.
-void make_roidev(const GroupRoi* g, size_t n, TileShape ts, RoiDev* out, int64_t* n_tiles,
-                 int64_t* n_coords) {
+void make_roidev(sfk_ctx c, const GroupRoi* g, size_t n, TileShape ts, RoiDev* out,
+                 int64_t* n_tiles, int64_t* n_coords) {
   int64_t tb = 0, co = 0;
   for (size_t i = 0; i < n; ++i) {
     const sfk_roi* r = g[i].roi;
@@ -701,17 +695,26 @@ void make_roidev(const GroupRoi* g, size_t n, TileShape ts, RoiDev* out, int64_t
     d.coord_off = (int32_t)co;
     d.out = r->d_out;
     d.pp_mode = g[i].pp;
+    const int64_t tiles = (int64_t)d.ntile[0] * d.ntile[1] * d.ntile[2];
+    d.chunk = chunk_leaves_of(c, ts, tiles);
     out[i] = d;
-    tb += (int64_t)d.ntile[0] * d.ntile[1] * d.ntile[2];
+    tb += tiles;
     co += r->res[0] + r->res[1] + r->res[2];
   }
   *n_tiles = tb;
   *n_coords = co;
 }
 
-void make_roidev(const std::vector<GroupRoi>& g, TileShape ts, RoiDev* out, int64_t* n_tiles,
-                 int64_t* n_coords) {
-  make_roidev(g.data(), g.size(), ts, out, n_tiles, n_coords);
+void make_roidev(sfk_ctx c, const std::vector<GroupRoi>& g, TileShape ts, RoiDev* out,
+                 int64_t* n_tiles, int64_t* n_coords) {
+  make_roidev(c, g.data(), g.size(), ts, out, n_tiles, n_coords);
+}
+
+// the shortest chunk of a group's ROIs
+int least_chunk(const RoiDev* rd, size_t n) {
+  int ch = rd[0].chunk;
+  for (size_t i = 1; i < n; ++i) ch = std::min(ch, rd[i].chunk);
+  return ch;
 }
 
 struct Caps {
@@ -858,7 +861,7 @@ BatchHdr make_hdr(sfk_ctx c, const Caps& k, int64_t n_rois, int64_t n_tiles) {
 // tile and plan grids (exact for direct launches, the capacities for a
 // captured graph).
 sfk_status launch_kernels(sfk_ctx c, const TreeView& tv, TileShape ts, int kk, int pp, bool cnt,
-                          Workspace& ws, int roi_grid, int64_t max_tiles, int CH, hipStream_t s,
+                          Workspace& ws, int roi_grid, int64_t max_tiles, hipStream_t s,
                           int nm = 0) {
   if (sfk::is_sweep(ts)) {
     BatchHdr* hdr = (BatchHdr*)ws.hdr_rois.p;
@@ -897,11 +900,12 @@ sfk_status launch_kernels(sfk_ctx c, const TreeView& tv, TileShape ts, int kk, i
   {
     ProfScope p(c, PK_TILE_COUNT, s);
     SFK_HIP(c, sfk::launch_tile_count(tv, hdr, rois, coords, roi_leaves, roi_nl, ts, tile_grid,
-                                      tile_cnt, tile_done, (int32_t*)ws.tile_slots.p, s));
+                                      tile_cnt, tile_fit, tile_done, (int32_t*)ws.tile_slots.p,
+                                      s));
   }
   {
     ProfScope p(c, PK_PLAN, s);
-    SFK_HIP(c, sfk::launch_plan(tile_cnt, hdr, (int32_t*)ws.claims.p, CH, leaf_off, partial_off,
+    SFK_HIP(c, sfk::launch_plan(tile_cnt, hdr, (int32_t*)ws.claims.p, leaf_off, partial_off,
                                 chunk_off, tile_fit, (int64_t*)ws.plan_tmp.p, max_tiles, s));
   }
   {
@@ -927,7 +931,7 @@ sfk_status launch_kernels(sfk_ctx c, const TreeView& tv, TileShape ts, int kk, i
                        : 0;
   {
     ProfScope p(c, PK_EVAL, s, hdr);
-    SFK_HIP(c, sfk::launch_eval(tv, hdr, rois, coords, ts, kk, pp, cnt, CH, leaf_off, chunk_off,
+    SFK_HIP(c, sfk::launch_eval(tv, hdr, rois, coords, ts, kk, pp, cnt, leaf_off, chunk_off,
                                  partial_off, tile_cnt, tile_fit, (int32_t*)ws.leaves.p,
                                  (int32_t*)ws.item_tile.p, (double*)ws.partials.p, tile_done,
                                  hdr, (int32_t*)ws.claims.p, grid, c->n_cu,
@@ -974,10 +978,9 @@ struct GroupKey {
   int kk, pp;
   TileShape ts;
   int nm;  // particle sweep: nodes per axis a support spans (0 otherwise)
-  int ch;  // leaves per work item
   bool operator==(const GroupKey& o) const {
     return kk == o.kk && pp == o.pp && ts.tx == o.ts.tx && ts.ty == o.ts.ty &&
-           ts.tz == o.ts.tz && nm == o.nm && ch == o.ch;
+           ts.tz == o.ts.tz && nm == o.nm;
   }
 };
 
@@ -989,8 +992,7 @@ void group_rois(sfk_ctx c, sfk_tree t, const std::vector<const sfk_roi*>& rois, 
   for (const sfk_roi* r : rois) {
     GroupRoi g = resolve_cloud_roi(t, r, count_mode);
     const TileShape ts = force_ts ? *force_ts : choose_shape(c, t, r);
-    const GroupKey key{count_mode ? 0 : g.kk, g.pp, ts, sfk::is_sweep(ts) ? sweep_nm(g) : 0,
-                       chunk_leaves_of(c, ts, r)};
+    const GroupKey key{count_mode ? 0 : g.kk, g.pp, ts, sfk::is_sweep(ts) ? sweep_nm(g) : 0};
     size_t gi = 0;
     while (gi < keys->size() && !((*keys)[gi] == key)) ++gi;
     if (gi == keys->size()) {
@@ -1035,11 +1037,12 @@ sfk_status enqueue_groups(sfk_ctx c, sfk_tree t, std::vector<std::vector<GroupRo
     const int64_t n = (int64_t)groups[gi].size();
     RoiDev* rd = (RoiDev*)(st.host + off + sizeof(BatchHdr));
     int64_t n_coords = 0;
-    make_roidev(groups[gi], keys[gi].ts, rd, &tiles[gi], &n_coords);
-    if (sfk::is_brick(keys[gi].ts)) keys[gi].ch = brick_batch_chunk(c, tiles[gi], t->n_leaves);
+    make_roidev(c, groups[gi], keys[gi].ts, rd, &tiles[gi], &n_coords);
+    if (sfk::is_brick(keys[gi].ts))
+      for (int64_t i = 0; i < n; ++i) rd[i].chunk = brick_batch_chunk(c, tiles[gi], t->n_leaves);
     Caps k;
     SFK_TRY(reserve_group(c, ws, keys[gi].ts, n, tiles[gi], n_coords, 1.0, t->n_leaves,
-                          keys[gi].ch, s, &k));
+                          least_chunk(rd, (size_t)n), s, &k));
     *(BatchHdr*)(st.host + off) = make_hdr(c, k, n, tiles[gi]);
     off += sizeof(BatchHdr) + sizeof(RoiDev) * (size_t)n;
   }
@@ -1049,7 +1052,7 @@ sfk_status enqueue_groups(sfk_ctx c, sfk_tree t, std::vector<std::vector<GroupRo
     const size_t gb = sizeof(BatchHdr) + sizeof(RoiDev) * (size_t)n;
     SFK_HIP(c, hipMemcpyAsync(ws.hdr_rois.p, st.host + off, gb, hipMemcpyHostToDevice, s));
     SFK_TRY(launch_kernels(c, tv, keys[gi].ts, keys[gi].kk, keys[gi].pp, count_mode, ws, (int)n,
-                           tiles[gi], keys[gi].ch, s, keys[gi].nm));
+                           tiles[gi], s, keys[gi].nm));
     off += gb;
   }
   SFK_HIP(c, hipMemcpyAsync(st.hdr_host, ws.hdr_rois.p, sizeof(BatchHdr), hipMemcpyDeviceToHost, s));
@@ -1077,14 +1080,15 @@ sfk_status enqueue_cloud_rois_graph(sfk_ctx c, sfk_tree t,
   if (groups.size() != 1) return enqueue_groups(c, t, groups, keys, false, sl.ws, sl.st, sl.stream);
   const int64_t n = (int64_t)groups[0].size();
   const TileShape ts = keys[0].ts;
-  const int kk = keys[0].kk, pp = keys[0].pp, ch = keys[0].ch, nm = keys[0].nm;
+  const int kk = keys[0].kk, pp = keys[0].pp, nm = keys[0].nm;
   std::vector<RoiDev> rd((size_t)n);
   int64_t n_tiles = 0, n_coords = 0;
-  make_roidev(groups[0], ts, rd.data(), &n_tiles, &n_coords);
+  make_roidev(c, groups[0], ts, rd.data(), &n_tiles, &n_coords);
+  const int ch = least_chunk(rd.data(), rd.size());
   GraphCache& gc = sl.gc;
   const bool fits = gc.valid && gc.gen == sl.ws.gen && gc.st_gen == sl.st.gen && gc.tree == t &&
                     gc.kk == kk && gc.nm == nm &&
-                    gc.pp == pp && gc.ch == ch && !gc.cnt && gc.interleave == c->serve_interleave &&
+                    gc.pp == pp && !gc.cnt && gc.interleave == c->serve_interleave &&
                     gc.ts.tx == ts.tx &&
                     gc.ts.ty == ts.ty && gc.ts.tz == ts.tz && n <= gc.rois_cap &&
                     n_tiles <= gc.tiles_cap && n_coords <= gc.coords_cap;
@@ -1116,7 +1120,7 @@ sfk_status enqueue_cloud_rois_graph(sfk_ctx c, sfk_tree t,
       st = SFK_E_DEVICE;
     if (st == SFK_OK)
       st = launch_kernels(c, view_of(t), ts, kk, pp, false, sl.ws, (int)k.rois_cap, k.tiles_cap,
-                          ch, s, nm);
+                          s, nm);
     if (st == SFK_OK && hipMemcpyAsync(sl.st.hdr_host, sl.ws.hdr_rois.p, sizeof(BatchHdr),
                                        hipMemcpyDeviceToHost, s) != hipSuccess)
       st = SFK_E_DEVICE;
@@ -1143,7 +1147,6 @@ sfk_status enqueue_cloud_rois_graph(sfk_ctx c, sfk_tree t,
     gc.kk = kk;
     gc.nm = nm;
     gc.pp = pp;
-    gc.ch = ch;
     gc.cnt = false;
     gc.interleave = c->serve_interleave;
     gc.tree = t;
@@ -1315,16 +1318,16 @@ sfk_status eval_subcloud(sfk_ctx c, sfk_tree t, const sfk_roi* r, bool count_mod
     SFK_TRY(staging_reserve(c, st, gb));
     if (st.ev_valid) SFK_HIP(c, hipEventSynchronize(st.ev));
     int64_t n_tiles = 0, n_coords = 0;
-    make_roidev(v, ts, (RoiDev*)(st.host + sizeof(BatchHdr)), &n_tiles, &n_coords);
+    RoiDev* rd = (RoiDev*)(st.host + sizeof(BatchHdr));
+    make_roidev(c, v, ts, rd, &n_tiles, &n_coords);
     Caps k;
-    const int ch = chunk_leaves_of(c, ts, n_tiles);
-    SFK_TRY(reserve_group(c, ws, ts, 1, n_tiles, n_coords, 1.0, tv.n_leaves, ch, s, &k));
+    SFK_TRY(reserve_group(c, ws, ts, 1, n_tiles, n_coords, 1.0, tv.n_leaves, rd->chunk, s, &k));
     *(BatchHdr*)st.host = make_hdr(c, k, 1, n_tiles);
     SFK_HIP(c, hipMemcpyAsync(ws.hdr_rois.p, st.host, gb, hipMemcpyHostToDevice, s));
     SFK_HIP(c, hipEventRecord(st.ev, s));
     st.ev_valid = true;
     return launch_kernels(c, tv, ts, g.count_mode ? 0 : g.kk, g.pp, g.count_mode, ws, 1,
-                          n_tiles, ch, s);
+                          n_tiles, s);
   };
   // Memory that is refused may be the sub-cloud's scratch, over all the cloud's
   // leaves: wait for its kernels, give it back and ask again.
@@ -2335,7 +2338,7 @@ sfk_status sfk_eval_roi_noalloc(sfk_ctx c, sfk_tree t, const sfk_roi* roi, void*
   auto rb = [](size_t b) { return round_bytes(std::max<size_t>(b, 256)); };
   RoiDev rd;
   int64_t n_tiles = 0, n_coords = 0;
-  make_roidev(&g, 1, ts, &rd, &n_tiles, &n_coords);
+  make_roidev(c, &g, 1, ts, &rd, &n_tiles, &n_coords);
   if (sfk::is_sweep(ts)) {
     // the particle sweep needs the node sums of all its tiles and one item
     // per box of the hierarchy's first interior level
@@ -2379,8 +2382,7 @@ sfk_status sfk_eval_roi_noalloc(sfk_ctx c, sfk_tree t, const sfk_roi* roi, void*
       const bool prof = c->prof_on;
       c->prof_on = false;
       const sfk_status st =
-          launch_kernels(c, view_of(t), ts, g.kk, g.pp, false, wv, 1, n_tiles,
-                         kDefaultChunkLeaves, s, sweep_nm(g));
+          launch_kernels(c, view_of(t), ts, g.kk, g.pp, false, wv, 1, n_tiles, s, sweep_nm(g));
       c->prof_on = prof;
       SFK_TRY(st);
       SFK_HIP(c, hipEventRecord(c->na_ev[si], s));
@@ -2392,7 +2394,7 @@ sfk_status sfk_eval_roi_noalloc(sfk_ctx c, sfk_tree t, const sfk_roi* roi, void*
     }
     // too large for the array: the shape the ROI would take without the sweep
     ts = shape_of(default_shape_no_sweep(t, roi));
-    make_roidev(&g, 1, ts, &rd, &n_tiles, &n_coords);
+    make_roidev(c, &g, 1, ts, &rd, &n_tiles, &n_coords);
   }
   const int T = ts.tx * ts.ty * ts.tz;
   const size_t nt = (size_t)n_tiles;
@@ -2417,7 +2419,7 @@ sfk_status sfk_eval_roi_noalloc(sfk_ctx c, sfk_tree t, const sfk_roi* roi, void*
   // rest to leaf-list entries (for bricks, with one work item per
   // chunk_leaves entries); 4 x 256 bytes of rounding and item slack
   const bool brick = sfk::is_brick(ts);
-  const int CH = chunk_leaves_of(c, ts, n_tiles);
+  const int CH = rd.chunk;
   const size_t rest = cap - fixed - rb(sizeof(int32_t) * (nt + 1)) - 4 * 256;
   const int64_t partial_cap =
       std::max<int64_t>(1, (int64_t)(rest / 4 / (sizeof(double) * T + sizeof(int32_t))));
@@ -2476,7 +2478,7 @@ sfk_status sfk_eval_roi_noalloc(sfk_ctx c, sfk_tree t, const sfk_roi* roi, void*
   // profiling events may be created on demand: none here
   const bool prof = c->prof_on;
   c->prof_on = false;
-  const sfk_status st = launch_kernels(c, view_of(t), ts, g.kk, g.pp, false, wv, 1, n_tiles, CH, s);
+  const sfk_status st = launch_kernels(c, view_of(t), ts, g.kk, g.pp, false, wv, 1, n_tiles, s);
   c->prof_on = prof;
   SFK_TRY(st);
   SFK_HIP(c, hipEventRecord(c->na_ev[si], s));
@@ -2846,7 +2848,7 @@ sfk_status sfk_debug_candidates(sfk_ctx c, sfk_tree t, const sfk_roi* roi, int64
   std::vector<GroupRoi> v{g};
   RoiDev rd;
   int64_t n_tiles, n_coords;
-  make_roidev(v, ts, &rd, &n_tiles, &n_coords);
+  make_roidev(c, v, ts, &rd, &n_tiles, &n_coords);
   TmpBuf hdev(c), coords(c), cnt(c), off(c), idx(c), rlist(c);
   SFK_TRY(hdev.get(sizeof(BatchHdr) + sizeof(RoiDev), "descriptor"));
   SFK_TRY(coords.get(sizeof(double) * (size_t)n_coords, "coordinates"));
