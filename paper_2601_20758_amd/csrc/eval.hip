@@ -228,21 +228,40 @@ __global__ __launch_bounds__(256) void k_tile_count(TreeView tv, const BatchHdr*
                 });
     if (lane == 0) {
       tile_cnt[t] = cnt;
-      tile_fit[t] = R.chunk;
+      tile_fit[t] = (R.chunk << kFitChunk) | (R.block_log2 << kFitBlock);
       tile_done[t] = 0;
     }
   }
 }
 
 // How a tile is evaluated. Lists: its leaf list and partial slots fit the
-// buffers, one work item per chunk of its list. Walk per chunk: only the
-// partial slots fit; one work item per chunk, each walking the hierarchy and
-// evaluating the leaves of its chunk. Walk whole tile: one work item walks
-// and evaluates every chunk in order. All three visit the same leaves in the
-// same order with the same chunk boundaries, so the sums are bitwise equal.
+// buffers, one work item per chunk (or block) of its list. Listed whole: only
+// the list fits, one work item for all of it. Walk per item: only the partial
+// slots fit; each work item walks the hierarchy and evaluates its leaves. Walk
+// whole tile: one work item walks and evaluates everything. All visit the same
+// leaves in the same order, add a chunk's terms in float (each wavefront lane
+// its own, then over the lanes), a block's chunks in double and the blocks in
+// double, so the sums are bitwise equal.
 static constexpr int kModeWalkTile = 0;
 static constexpr int kModeLists = 1;
-static constexpr int kModeWalkChunk = 2;
+static constexpr int kModeWalkItem = 2;
+static constexpr int kModeListTile = 3;
+__device__ __forceinline__ bool mode_listed(int mode) {
+  return mode == kModeLists || mode == kModeListTile;
+}
+__device__ __forceinline__ bool mode_whole(int mode) {
+  return mode == kModeWalkTile || mode == kModeListTile;
+}
+// of a tile_fit entry
+__device__ __forceinline__ int fit_mode(int fit) { return fit & 3; }
+__device__ __forceinline__ int fit_chunk(int fit) {
+  return (fit & ((1 << kFitBlock) - 1)) >> kFitChunk;
+}
+__device__ __forceinline__ int fit_block(int fit) { return fit >> kFitBlock; }
+// leaves of a work item
+__device__ __forceinline__ int fit_span(int fit, bool coarse) {
+  return coarse ? fit_chunk(fit) << fit_block(fit) : fit_chunk(fit);
+}
 
 template <int TX, int TY, int TZ>
 __global__ __launch_bounds__(256) void k_tile_fill(
@@ -279,13 +298,14 @@ __global__ __launch_bounds__(256) void k_tile_fill(
       }
       continue;
     }
-    if (hdr->splat && tile_fit[t] != kModeWalkTile && chunk_off[t + 1] - c0 > 1) {
+    const int mode = fit_mode(tile_fit[t]);
+    if (hdr->splat && !mode_whole(mode) && chunk_off[t + 1] - c0 > 1) {
       // a brick split over several work items: its integer node sums start at 0
       constexpr int64_t T = (int64_t)TX * TY * TZ;
       unsigned long long* sums = (unsigned long long*)(partials) + partial_off[t] * T;
       for (int64_t i = lane; i < T; i += 64) sums[i] = 0ull;
     }
-    if (tile_fit[t] != kModeLists) continue;
+    if (!mode_listed(mode)) continue;
     int32_t* out = leaves + leaf_off[t];
     if (tc <= slot_cap) {
       // the count pass kept the whole list, in walk order; an entry that is
@@ -316,29 +336,45 @@ __global__ __launch_bounds__(256) void k_tile_fill(
 // ---------------------------------------------------------------------------
 // work plan: per tile, leaf_off (prefix of candidate leaves), partial_off
 // (prefix of partial-sum slots of split tiles), tile_fit (the count pass left
-// the tile's chunk there: how the tile is evaluated, below) and chunk_off
-// (prefix of work items). Three launches over blocks of kPlanNT consecutive
-// tiles (coalesced; no block waits for another): per-block sums of leaves and
-// partial slots; then each block adds the sums of the blocks before it, scans
-// its tiles, decides each tile's mode from the prefixes and its number of work
-// items (kept in chunk_off) and sums those; then the same for the items.
+// the tile's chunk and block there: how the tile is evaluated, above) and
+// chunk_off (prefix of work items). Three launches over blocks of kPlanNT
+// consecutive tiles (coalesced; no block waits for another): per-block sums of
+// leaves and of the partial slots that chunks and that blocks would need; then
+// each block adds the sums of the blocks before it, scans its tiles, decides
+// each tile's mode from the prefixes and its number of work items (kept in
+// chunk_off) and sums those; then the same for the items.
+// The batch's items are chunks if its partial slots last for that and blocks
+// otherwise: short chunks need up to eight times the slots, and where these run
+// out (a bounded workspace, very many or very heavy tiles) the tiles past the
+// last slot would be one item each, the heaviest of them the last to end: a
+// 64^3 grid of 20M points in wide supports took 3.3 ms so, 1.1 in blocks.
 // Block 0 of the last launch writes the totals. A batch of at most kPlanNT
 // tiles takes one launch of one block instead.
 // ---------------------------------------------------------------------------
 
 static constexpr int kPlanNT = 1024;
 
-// Work items of a tile: one per chunk of its leaves. A tile with no
-// candidate leaf has none: the fill pass writes its (zero) nodes.
-__device__ __forceinline__ int64_t plan_chunks(int64_t cnt, int chunk_leaves) {
-  return cnt > 0 ? (cnt + chunk_leaves - 1) / chunk_leaves : 0;
+// Work items of a tile that is split where it can be. A tile with no candidate
+// leaf has none: the fill pass writes its (zero) nodes.
+__device__ __forceinline__ int64_t plan_items(int64_t cnt, int span) {
+  return cnt > 0 ? (cnt + span - 1) / span : 0;
 }
 
-// Partial slots a tile needs: one per chunk when it is split (its chunks'
-// sums are combined in chunk order), or one for a split brick (its chunks
-// add integer node sums into that one slot).
-__device__ __forceinline__ int64_t plan_partials(int64_t nch, int splat) {
-  return nch > 1 ? (splat ? 1 : nch) : 0;
+// Partial slots a tile of n items needs: one per item when it is split (its
+// items' sums are combined in order), or one for a split brick (its items add
+// integer node sums into that one slot).
+__device__ __forceinline__ int64_t plan_partials(int64_t n, int splat) {
+  return n > 1 ? (splat ? 1 : n) : 0;
+}
+
+// A tile's mode, and the number of its items.
+__device__ __forceinline__ int plan_mode(bool fit_list, bool fit_slots, int64_t n, int splat) {
+  if (fit_list) return fit_slots ? kModeLists : kModeListTile;
+  // bricks never walk per item: their items stay within the list capacity
+  return fit_slots && n > 1 && !splat ? kModeWalkItem : kModeWalkTile;
+}
+__device__ __forceinline__ int64_t plan_count(int64_t cnt, int64_t n, int mode) {
+  return cnt > 0 && mode_whole(mode) ? 1 : n;
 }
 
 // sum of v over the block (every thread gets it)
@@ -365,12 +401,14 @@ __global__ __launch_bounds__(kPlanNT) void k_plan_sums(const int32_t* __restrict
   const int64_t t = (int64_t)blockIdx.x * kPlanNT + threadIdx.x;
   if ((int64_t)blockIdx.x * kPlanNT >= n_tiles) return;  // whole block past the end
   const int64_t cnt = t < n_tiles ? tile_cnt[t] : 0;
-  const int64_t nch = plan_chunks(cnt, t < n_tiles ? tile_fit[t] : 1);
+  const int fit = t < n_tiles ? tile_fit[t] : 1 << kFitChunk;
   const int64_t sl = block_sum(cnt, lds);
-  const int64_t sp = block_sum(t < n_tiles ? plan_partials(nch, hdr->splat) : 0, lds);
+  const int64_t sf = block_sum(plan_partials(plan_items(cnt, fit_span(fit, false)), hdr->splat), lds);
+  const int64_t sc = block_sum(plan_partials(plan_items(cnt, fit_span(fit, true)), hdr->splat), lds);
   if (threadIdx.x == 0) {
-    bs[3 * blockIdx.x] = sl;
-    bs[3 * blockIdx.x + 1] = sp;
+    bs[kPlanSums * blockIdx.x] = sl;
+    bs[kPlanSums * blockIdx.x + 1] = sf;
+    bs[kPlanSums * blockIdx.x + 2] = sc;
   }
 }
 
@@ -386,30 +424,30 @@ __global__ __launch_bounds__(kPlanNT) void k_plan_modes(const int32_t* __restric
   const int64_t leaf_cap = hdr->leaf_cap;
   const int64_t partial_cap = hdr->partial_cap;
   if ((int64_t)blockIdx.x * kPlanNT >= n_tiles) return;
-  const int64_t base_l = sum_before(bs, 3, 0, blockIdx.x, lds);
-  const int64_t base_p = sum_before(bs, 3, 1, blockIdx.x, lds);
+  const int64_t nb = (n_tiles + kPlanNT - 1) / kPlanNT;
+  const bool coarse = sum_before(bs, kPlanSums, 1, nb, lds) > partial_cap;
+  const int64_t base_l = sum_before(bs, kPlanSums, 0, blockIdx.x, lds);
+  const int64_t base_p = sum_before(bs, kPlanSums, coarse ? 2 : 1, blockIdx.x, lds);
   const int64_t t = (int64_t)blockIdx.x * kPlanNT + threadIdx.x;
   const bool v = t < n_tiles;
   const int64_t cnt = v ? tile_cnt[t] : 0;
-  const int64_t nch = plan_chunks(cnt, v ? tile_fit[t] : 1);
-  const int64_t pneed = v ? plan_partials(nch, hdr->splat) : 0;
+  const int fit = v ? tile_fit[t] : 1 << kFitChunk;
+  const int64_t n = plan_items(cnt, fit_span(fit, coarse));
+  const int64_t pneed = plan_partials(n, hdr->splat);
   int64_t tot;
   const int64_t lo = base_l + block_excl_scan<kPlanNT>(cnt, &tot, lds);
   const int64_t po = base_p + block_excl_scan<kPlanNT>(pneed, &tot, lds);
-  const bool fit_p = pneed == 0 || po + pneed <= partial_cap;
-  // bricks never walk per chunk: their items stay within the list capacity
-  const int mode = (lo + cnt <= leaf_cap && fit_p)    ? kModeLists
-                   : (fit_p && nch > 1 && !hdr->splat) ? kModeWalkChunk
-                                                       : kModeWalkTile;
-  const int64_t nit = v && cnt > 0 ? (mode == kModeWalkTile ? 1 : nch) : 0;
+  const int mode = plan_mode(lo + cnt <= leaf_cap, pneed == 0 || po + pneed <= partial_cap, n,
+                             hdr->splat);
+  const int64_t nit = plan_count(cnt, n, mode);
   if (v) {
     leaf_off[t] = lo;
     partial_off[t] = po;
     chunk_off[t] = nit;
-    tile_fit[t] = mode;
+    tile_fit[t] = fit | mode;
   }
   const int64_t si = block_sum(nit, lds);
-  if (threadIdx.x == 0) bs[3 * blockIdx.x + 2] = si;
+  if (threadIdx.x == 0) bs[kPlanSums * blockIdx.x + 3] = si;
 }
 
 __global__ __launch_bounds__(kPlanNT) void k_plan_items(BatchHdr* __restrict__ hdr,
@@ -423,10 +461,12 @@ __global__ __launch_bounds__(kPlanNT) void k_plan_items(BatchHdr* __restrict__ h
   const int64_t nb = (n_tiles + kPlanNT - 1) / kPlanNT;
   if (blockIdx.x == 0) {
     // totals (block 0 runs even for an empty batch)
-    const int64_t tl = sum_before(bs, 3, 0, nb, lds);
-    const int64_t tp = sum_before(bs, 3, 1, nb, lds);
-    const int64_t tc = sum_before(bs, 3, 2, nb, lds);
-    const int64_t leaf_cap = hdr->leaf_cap, partial_cap = hdr->partial_cap;
+    const int64_t partial_cap = hdr->partial_cap;
+    const int64_t tl = sum_before(bs, kPlanSums, 0, nb, lds);
+    const int64_t tf = sum_before(bs, kPlanSums, 1, nb, lds);
+    const bool coarse = tf > partial_cap;
+    const int64_t tp = coarse ? sum_before(bs, kPlanSums, 2, nb, lds) : tf;
+    const int64_t tc = sum_before(bs, kPlanSums, 3, nb, lds);
     // every thread of this block has read the header before thread 0 writes it
     __syncthreads();
     if (threadIdx.x < kClaimSlices) claims[threadIdx.x * kClaimStride] = 0;
@@ -437,11 +477,11 @@ __global__ __launch_bounds__(kPlanNT) void k_plan_items(BatchHdr* __restrict__ h
       hdr->total_leaves = tl;
       hdr->n_items = tc;
       hdr->total_partials = tp;
-      hdr->overflow = (tl > leaf_cap || tp > partial_cap) ? 1 : 0;
+      hdr->coarse = coarse ? 1 : 0;
     }
   }
   if ((int64_t)blockIdx.x >= nb) return;
-  const int64_t base_c = sum_before(bs, 3, 2, blockIdx.x, lds);
+  const int64_t base_c = sum_before(bs, kPlanSums, 3, blockIdx.x, lds);
   const int64_t t = (int64_t)blockIdx.x * kPlanNT + threadIdx.x;
   const bool v = t < n_tiles;
   const int64_t nit = v ? chunk_off[t] : 0;
@@ -553,8 +593,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
   constexpr int T = TX * TY * TZ;
   constexpr int NPL = T >= 64 ? T / 64 : 1;
   // Per-lane node accumulators are float32: a lane adds one term per drained
-  // batch of 64 particles (at most chunk_leaves terms per work item), the 64
-  // lanes are combined by a 6-level tree and the chunks of a tile in double.
+  // batch of 64 particles (at most one per leaf of a chunk), the 64 lanes are
+  // combined by a 6-level tree and the chunks of a tile in double.
   // Epanechnikov tiles of at most 16 nodes accumulate in double (registers
   // allow it), which also saves the per-pair conversion.
   constexpr bool kDoubleAcc = T <= 16 && KK == KK_EPAN && !CNT;
@@ -569,7 +609,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
   __shared__ float4 lds_qprm[4][PP == PP_ANISO ? QCAP : 1];
   const int lane = lane_id(), wave = threadIdx.x >> 6;
   const int64_t n_items = min(hdr->n_items, hdr->item_cap);  // equal by construction
-  const int n_rois = hdr->n_rois;
+  const int n_rois = hdr->n_rois, coarse = hdr->coarse;
   // XCD-aware work stealing. Workgroups are dispatched round-robin over the
   // 8 XCDs, each with its own L2. The item list is cut into kClaimSlices
   // contiguous (hence spatially coherent) slices, 8 per XCD, each with its own
@@ -608,7 +648,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     const int t = wave_uniform(item_tile[item]);
     const TileGeo g = tile_geo<TX, TY, TZ>(rois, n_rois, coords, t);
     const RoiDev& R = rois[g.r];
-    const int chunk_leaves = wave_uniform(R.chunk);
     const double* cx = coords + R.coord_off;
     const double* cy = cx + R.res[0];
     const double* cz = cy + R.res[1];
@@ -637,7 +676,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     }
     const float cc = (float)(c2 * (kWide * kWide));
     const int cnt = tile_cnt[t];  // > 0: tiles with no candidate leaf have no work item
-    const int nch = (cnt + chunk_leaves - 1) / chunk_leaves;
+    const int fit = wave_uniform(tile_fit[t]), mode = fit_mode(fit);
+    const int chunk = fit_chunk(fit), span = fit_span(fit, coarse);
+    const int nit = (cnt + span - 1) / span;
 
     Acc acc[T];
 
@@ -831,40 +872,52 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     auto lane_node = [&](int m) { return T >= 64 ? lane * NPL + m : (lane & (T - 1)); };
     const bool lane_writes = T >= 64 || lane < T;
 
-    const int mode = tile_fit[t];
     const int c = (int)(item - chunk_off[t]);
-    // the chunk's per-node sums: the grid values when the tile has one
-    // chunk, else a partial slot, the last chunk to finish combining all
-    // of them in chunk order (in double)
-    auto finish_chunk = [&]() __attribute__((always_inline)) {
-      if (nch == 1) {
+    const bool whole = mode_whole(mode);
+    // A block's chunks are added in double, and the blocks; so an item's sums
+    // combine to the same bits whether it is a chunk, a block or the tile.
+    const int block_mask = (1 << fit_block(fit)) - 1;
+    double dacc[NPL], bacc[NPL];  // the item's sums, its open block's
+#pragma unroll
+    for (int m = 0; m < NPL; ++m) dacc[m] = bacc[m] = 0.0;
+    // the item's per-node sums: the grid values when it is all of the tile,
+    // else a partial slot, the last item to finish combining all of them in
+    // order
+    auto finish_item = [&]() __attribute__((always_inline)) {
+      if (whole || nit == 1) {
         if (lane_writes) {
 #pragma unroll
-          for (int m = 0; m < NPL; ++m) node_out(lane_node(m), (double)acc[m] * R.scale);
+          for (int m = 0; m < NPL; ++m) node_out(lane_node(m), dacc[m] * R.scale);
         }
       } else {
         const int64_t pbase = (partial_off[t] + c) * T;
         if (lane_writes) {
 #pragma unroll
           for (int m = 0; m < NPL; ++m)
-            __hip_atomic_store(&partials[pbase + lane_node(m)], (double)acc[m], __ATOMIC_RELAXED,
+            __hip_atomic_store(&partials[pbase + lane_node(m)], dacc[m], __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
         }
         agent_writes_done();
         int prev = 0;
         if (lane == 0) prev = atomicAdd(&tile_done[t], 1);
         prev = __shfl(prev, 0, 64);
-        if (prev == nch - 1) {
+        if (prev == nit - 1) {
           agent_writes_done();
           if (lane_writes) {
             const int64_t p0 = partial_off[t] * T;
+            const int ends = coarse ? 0 : block_mask;
 #pragma unroll
             for (int m = 0; m < NPL; ++m) {
               const int node = lane_node(m);
-              double s = 0.0;
-              for (int cc = 0; cc < nch; ++cc)
-                s += __hip_atomic_load(&partials[p0 + (int64_t)cc * T + node], __ATOMIC_RELAXED,
+              double s = 0.0, b = 0.0;
+              for (int q = 0; q < nit; ++q) {
+                b += __hip_atomic_load(&partials[p0 + (int64_t)q * T + node], __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
+                if (((q + 1) & ends) == 0 || q == nit - 1) {
+                  s += b;
+                  b = 0.0;
+                }
+              }
               node_out(node, s * R.scale);
             }
           }
@@ -877,7 +930,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     // the leaves among them into a ring; so both feed the same loop, and the
     // kernel holds one copy of the evaluation (three took more registers than
     // three wavefronts a SIMD leave).
-    const bool listed = mode == kModeLists;
+    const bool listed = mode_listed(mode);
     const int64_t list0 = listed ? leaf_off[t] : 0;
     int32_t* ring = lds_walk[wave];
     int walked = 0, sp = 0, level = tv.n_levels - 1, first = 0, width = tv.level_cnt[level];
@@ -914,14 +967,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
       first = (e & ((1 << 27) - 1)) * SFK_FANOUT;
       width = min(SFK_FANOUT, tv.level_cnt[level] - first);
     };
-    // The work item's chunks: one, or all of the tile's when neither the list
-    // nor the partial slots fit.
-    const bool whole = mode == kModeWalkTile;
-    double dacc[NPL];
-#pragma unroll
-    for (int m = 0; m < NPL; ++m) dacc[m] = 0.0;
-    for (int cc = whole ? 0 : c; cc < (whole ? nch : c + 1); ++cc) {
-      const int lb = cc * chunk_leaves, le = min(lb + chunk_leaves, cnt);
+    // The work item's leaves, a chunk at a time.
+    const int i0 = whole ? 0 : c * span, i1 = whole ? cnt : min(i0 + span, cnt);
+    int left = block_mask;  // chunks to the block's end
+    for (int lb = i0; lb < i1; lb += chunk, left = (left - 1) & block_mask) {
+      const int le = min(lb + chunk, cnt);
 #pragma unroll
       for (int q = 0; q < T; ++q) acc[q] = (Acc)0;
       // Ids of leaves [i, i + 64) of the tile, one a lane; past the chunk's
@@ -982,17 +1032,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
         }
       }
       reduce_nodes(acc);
-      if (whole && nch > 1) {
 #pragma unroll
-        for (int m = 0; m < NPL; ++m) dacc[m] += (double)acc[m];
+      for (int m = 0; m < NPL; ++m) {
+        bacc[m] += (double)acc[m];
+        if (left == 0 || le == i1) {
+          dacc[m] += bacc[m];
+          bacc[m] = 0.0;
+        }
       }
     }
-    if (!whole || nch == 1) {
-      finish_chunk();
-    } else if (lane_writes) {
-#pragma unroll
-      for (int m = 0; m < NPL; ++m) node_out(lane_node(m), dacc[m] * R.scale);
-    }
+    finish_item();
   }
 }
 
@@ -1278,15 +1327,16 @@ __global__ __launch_bounds__(256) void k_splat(
       splat(p);
     };
 
-    const int cnt = tile_cnt[t], chunk_leaves = R.chunk;
-    const int nch = (cnt + chunk_leaves - 1) / chunk_leaves;
-    const int mode = tile_fit[t];
+    const int cnt = tile_cnt[t];
+    const int fit = tile_fit[t], mode = fit_mode(fit), span = fit_span(fit, hdr->coarse);
+    const int nit = (cnt + span - 1) / span;
+    const bool whole = mode_whole(mode);
     const int c = (int)(item - chunk_off[t]);
-    if (mode == kModeLists) {
-      // the chunk's leaves, every fourth to each wave; ids outside the tree
+    if (mode_listed(mode)) {
+      // the item's leaves, every fourth to each wave; ids outside the tree
       // are an internal error (flagged, leaf 0 read instead)
-      const int64_t lb = leaf_off[t] + (int64_t)c * chunk_leaves;
-      const int64_t le = min(lb + chunk_leaves, leaf_off[t] + cnt);
+      const int64_t lb = leaf_off[t] + (whole ? 0 : (int64_t)c * span);
+      const int64_t le = whole ? lb + cnt : min(lb + span, leaf_off[t] + cnt);
       auto leaf_at = [&](int64_t q) {
         int lid = leaves[q];
         if ((unsigned)lid >= (unsigned)tv.n_leaves) {
@@ -1313,24 +1363,21 @@ __global__ __launch_bounds__(256) void k_splat(
       }
       drain_rest();
     } else {
-      // walking modes: every wave walks the hierarchy (same order) and takes
-      // every fourth leaf of the item's range
-      const int start = mode == kModeWalkChunk ? c * chunk_leaves : 0;
-      const int stop = mode == kModeWalkChunk ? min(start + chunk_leaves, cnt) : cnt;
+      // the whole tile without a list: every wave walks the hierarchy (same
+      // order) and takes every fourth leaf
       int done = 0;
-      traverse_until(
+      traverse(
           tv, lds_stack[wave],
           [&](const NodeBox& b, int gidx) { return tile_box_test(tv, R, g, b, gidx); },
           [&](int child, bool pass, uint64_t mask) {
             (void)pass;
             uint64_t mm = mask;
-            while (mm && done < stop) {
+            while (mm) {
               const int bl = __ffsll((unsigned long long)mm) - 1;
               mm &= mm - 1;
-              if (done >= start && ((done - start) & 3) == wave) do_leaf(__shfl(child, bl, 64));
+              if ((done & 3) == wave) do_leaf(__shfl(child, bl, 64));
               ++done;
             }
-            return done < stop;
           });
     }
     __syncthreads();
@@ -1345,7 +1392,7 @@ __global__ __launch_bounds__(256) void k_splat(
             (float)(((double)v * unit) * R.scale);
       }
     };
-    if (mode == kModeWalkTile || nch == 1) {
+    if (whole || nit == 1) {
       for (int n = threadIdx.x; n < T; n += 256) write_node(n, sums[n]);
     } else {
       unsigned long long* slot = gsum + partial_off[t] * (int64_t)T;
@@ -1353,7 +1400,7 @@ __global__ __launch_bounds__(256) void k_splat(
         if (sums[n]) atomicAdd(&slot[n], sums[n]);
       agent_writes_done();
       __syncthreads();
-      if (threadIdx.x == 0) lds_last = atomicAdd(&tile_done[t], 1) == nch - 1 ? 1 : 0;
+      if (threadIdx.x == 0) lds_last = atomicAdd(&tile_done[t], 1) == nit - 1 ? 1 : 0;
       __syncthreads();
       if (lds_last) {
         agent_writes_done();
@@ -2038,23 +2085,27 @@ __global__ __launch_bounds__(kPlanNT) void k_plan_one(const int32_t* __restrict_
   const int64_t t = threadIdx.x;
   const bool v = t < n_tiles;
   const int64_t cnt = v ? tile_cnt[t] : 0;
-  const int64_t nch = plan_chunks(cnt, v ? tile_fit[t] : 1);
-  const int64_t pneed = v ? plan_partials(nch, hdr->splat) : 0;
+  const int fit = v ? tile_fit[t] : 1 << kFitChunk;
+  int64_t n = plan_items(cnt, fit_span(fit, false));
+  int64_t pneed = plan_partials(n, hdr->splat);
   int64_t tl, tp, tc;
   const int64_t lo = block_excl_scan<kPlanNT>(cnt, &tl, lds);
-  const int64_t po = block_excl_scan<kPlanNT>(pneed, &tp, lds);
-  const bool fit_p = pneed == 0 || po + pneed <= partial_cap;
-  // bricks never walk per chunk: their items stay within the list capacity
-  const int mode = (lo + cnt <= leaf_cap && fit_p)    ? kModeLists
-                   : (fit_p && nch > 1 && !hdr->splat) ? kModeWalkChunk
-                                                       : kModeWalkTile;
-  const int64_t nit = v && cnt > 0 ? (mode == kModeWalkTile ? 1 : nch) : 0;
+  int64_t po = block_excl_scan<kPlanNT>(pneed, &tp, lds);
+  const bool coarse = tp > partial_cap;
+  if (coarse) {
+    n = plan_items(cnt, fit_span(fit, true));
+    pneed = plan_partials(n, hdr->splat);
+    po = block_excl_scan<kPlanNT>(pneed, &tp, lds);
+  }
+  const int mode = plan_mode(lo + cnt <= leaf_cap, pneed == 0 || po + pneed <= partial_cap, n,
+                             hdr->splat);
+  const int64_t nit = plan_count(cnt, n, mode);
   const int64_t co = block_excl_scan<kPlanNT>(nit, &tc, lds);
   if (v) {
     leaf_off[t] = lo;
     partial_off[t] = po;
     chunk_off[t] = co;
-    tile_fit[t] = mode;
+    tile_fit[t] = fit | mode;
   }
   // every thread has read the header above before thread 0 writes it
   __syncthreads();
@@ -2066,7 +2117,7 @@ __global__ __launch_bounds__(kPlanNT) void k_plan_one(const int32_t* __restrict_
     hdr->total_leaves = tl;
     hdr->n_items = tc;
     hdr->total_partials = tp;
-    hdr->overflow = (tl > leaf_cap || tp > partial_cap) ? 1 : 0;
+    hdr->coarse = coarse ? 1 : 0;
   }
 }
 

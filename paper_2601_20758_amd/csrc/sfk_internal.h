@@ -55,9 +55,14 @@ struct alignas(16) RoiDev {
   int32_t coord_off;     // into the batch coordinate table: x, then y, then z
   float* out;
   int32_t pp_mode;       // PPMode of this evaluation
-  int32_t chunk;         // leaves per work item
-  int32_t pad_[2];
+  int32_t chunk;         // leaves summed in one go, the smallest work item
+  int32_t block_log2;    // 2^this chunks are a block, the work item of a batch
+                         // whose partial slots do not last for its chunks
+  int32_t pad_;
 };
+// How a tile is evaluated (tile_fit): the plan's mode in bits 0-1, the chunk
+// (at most 2^20 leaves) from bit 2, block_log2 from bit 24.
+constexpr int kFitChunk = 2, kFitBlock = 24;
 
 // Device-side header of one batch, staged by the host together with the ROI
 // descriptors (so a captured graph can be replayed for any batch that fits
@@ -70,15 +75,15 @@ struct alignas(16) BatchHdr {
   int32_t n_rois;        // host: descriptors that follow the header
   int32_t slot_cap;      // host: leaves the count pass keeps per tile (<= kTileSlotCap)
   int64_t total_leaves;  // plan: candidate leaves over all tiles
-  int64_t n_items;       // plan: work items (tile chunks)
+  int64_t n_items;       // plan: work items
   int64_t total_partials;  // plan: partial-sum slots the split tiles need
-  int32_t overflow;      // plan: 1 if some tile's lists did not fit (it walks the tree)
+  int32_t coarse;        // plan: 1 = work items are blocks, 0 = chunks
   int32_t debug_poison;  // host, tests only: bit 0 = the count pass stores out-of-range
                          // ids in the slots past the 64th of a tile, bit 1 = the fill
                          // pass stores them in the lists past the 64th entry
   int32_t splat;         // host: 1 = the tiles are bricks evaluated by scattering into
                          // integer node sums; a split brick then needs one partial
-                         // slot (its node sums), not one per chunk
+                         // slot (its node sums), not one per item
   int32_t pad_;
 };
 
@@ -237,8 +242,9 @@ hipError_t launch_tile_count(TreeView tv, const BatchHdr* hdr, const RoiDev* roi
                              const int32_t* roi_nl, TileShape ts, int grid_blocks,
                              int32_t* tile_cnt, int32_t* tile_fit, int32_t* tile_done,
                              int32_t* tile_slots, hipStream_t s);
-// plan_tmp: 3 int64 per block of plan_blocks(max_tiles); max_tiles bounds
+// plan_tmp: kPlanSums int64 per block of plan_blocks(max_tiles); max_tiles bounds
 // the header's tile count (the grid of a captured graph uses the capacity)
+constexpr int kPlanSums = 4;
 int plan_blocks(int64_t max_tiles);
 // tile_fit: the tiles' chunks in, their modes out
 hipError_t launch_plan(const int32_t* tile_cnt, BatchHdr* hdr, int32_t* claims, int64_t* leaf_off,

@@ -671,6 +671,15 @@ int brick_batch_chunk(sfk_ctx c, int64_t tiles, int64_t tree_leaves) {
   return tiles < 64 && tree_leaves < 2048 ? 8 : kBrickChunkLeaves;
 }
 
+// A chunk and the block it is part of: a chosen chunk by itself, the default
+// ones in blocks of kDefaultChunkLeaves.
+void set_chunk(sfk_ctx c, RoiDev& d, int chunk) {
+  d.chunk = chunk;
+  d.block_log2 = 0;
+  if (c->opts.chunk_leaves == 0)
+    while (chunk << d.block_log2 < kDefaultChunkLeaves) ++d.block_log2;
+}
+
 // Fill RoiDev descriptors for rois[0..n) and the per-group tile total.
 void make_roidev(sfk_ctx c, const GroupRoi* g, size_t n, TileShape ts, RoiDev* out,
                  int64_t* n_tiles, int64_t* n_coords) {
@@ -696,7 +705,7 @@ void make_roidev(sfk_ctx c, const GroupRoi* g, size_t n, TileShape ts, RoiDev* o
     d.out = r->d_out;
     d.pp_mode = g[i].pp;
     const int64_t tiles = (int64_t)d.ntile[0] * d.ntile[1] * d.ntile[2];
-    d.chunk = chunk_leaves_of(c, ts, tiles);
+    set_chunk(c, d, chunk_leaves_of(c, ts, tiles));
     out[i] = d;
     tb += tiles;
     co += r->res[0] + r->res[1] + r->res[2];
@@ -805,10 +814,10 @@ sfk_status reserve_group(sfk_ctx c, Workspace& ws, TileShape ts, int64_t n_rois,
   SFK_TRY(ws_reserve(c, ws, ws.roi_leaves, sizeof(int32_t) * kRoiListCap * (size_t)nr,
                      "ROI leaf lists"));
   SFK_TRY(ws_reserve(c, ws, ws.roi_nl, sizeof(int32_t) * (size_t)nr, "ROI list lengths"));
-  SFK_TRY(ws_reserve(c, ws, ws.plan_tmp, 3 * sizeof(int64_t) * (size_t)sfk::plan_blocks(tiles),
+  SFK_TRY(ws_reserve(c, ws, ws.plan_tmp, sfk::kPlanSums * sizeof(int64_t) * (size_t)sfk::plan_blocks(tiles),
                      "plan block sums"));
   Caps k;
-  k.tiles_cap = std::min<int64_t>({(int64_t)(ws.plan_tmp.bytes / (3 * sizeof(int64_t))) * 1024,
+  k.tiles_cap = std::min<int64_t>({(int64_t)(ws.plan_tmp.bytes / (sfk::kPlanSums * sizeof(int64_t))) * 1024,
                                    (int64_t)(ws.tile_cnt.bytes / sizeof(int32_t)),
                                    (int64_t)(ws.tile_fit.bytes / sizeof(int32_t)),
                                    (int64_t)(ws.tile_done.bytes / sizeof(int32_t)),
@@ -1039,7 +1048,8 @@ sfk_status enqueue_groups(sfk_ctx c, sfk_tree t, std::vector<std::vector<GroupRo
     int64_t n_coords = 0;
     make_roidev(c, groups[gi], keys[gi].ts, rd, &tiles[gi], &n_coords);
     if (sfk::is_brick(keys[gi].ts))
-      for (int64_t i = 0; i < n; ++i) rd[i].chunk = brick_batch_chunk(c, tiles[gi], t->n_leaves);
+      for (int64_t i = 0; i < n; ++i)
+        set_chunk(c, rd[i], brick_batch_chunk(c, tiles[gi], t->n_leaves));
     Caps k;
     SFK_TRY(reserve_group(c, ws, keys[gi].ts, n, tiles[gi], n_coords, 1.0, t->n_leaves,
                           least_chunk(rd, (size_t)n), s, &k));
@@ -2401,7 +2411,7 @@ sfk_status sfk_eval_roi_noalloc(sfk_ctx c, sfk_tree t, const sfk_roi* roi, void*
   const size_t fixed0 = rb(sizeof(BatchHdr) + sizeof(RoiDev)) + rb(sizeof(double) * n_coords) +
                         rb(kClaimBytes) + rb(sizeof(int32_t) * kRoiListCap) +
                         rb(sizeof(int32_t)) +
-                        rb(3 * sizeof(int64_t) * (size_t)sfk::plan_blocks(n_tiles)) +
+                        rb(sfk::kPlanSums * sizeof(int64_t) * (size_t)sfk::plan_blocks(n_tiles)) +
                         3 * rb(sizeof(int32_t) * nt) + 3 * rb(sizeof(int64_t) * (nt + 1));
   // leaf slots: the tile shape's capacity, halved until the fixed part
   // leaves at least half of the array to the lists (0: the fill pass walks)
@@ -2440,7 +2450,7 @@ sfk_status sfk_eval_roi_noalloc(sfk_ctx c, sfk_tree t, const sfk_roi* roi, void*
   take(wv.claims, kClaimBytes);
   take(wv.roi_leaves, sizeof(int32_t) * kRoiListCap);
   take(wv.roi_nl, sizeof(int32_t));
-  take(wv.plan_tmp, 3 * sizeof(int64_t) * (size_t)sfk::plan_blocks(n_tiles));
+  take(wv.plan_tmp, sfk::kPlanSums * sizeof(int64_t) * (size_t)sfk::plan_blocks(n_tiles));
   take(wv.tile_cnt, sizeof(int32_t) * nt);
   take(wv.tile_fit, sizeof(int32_t) * nt);
   take(wv.tile_done, sizeof(int32_t) * nt);
@@ -3031,11 +3041,10 @@ sfk_status sfk_debug_tile_leaves(sfk_ctx c, sfk_tree t, const sfk_roi* roi, int3
     SFK_TRY(eval_direct(c, t, roi, s, false));
     SFK_HIP(c, hipStreamSynchronize(s));
     SFK_HIP(c, hipMemcpy(&hh, c->direct_ws.hdr_rois.p, sizeof hh, hipMemcpyDeviceToHost));
-    if (!hh.overflow) break;
+    if (hh.total_leaves <= hh.leaf_cap) break;
     c->direct_ws.want_leaf_cap = std::max(c->direct_ws.want_leaf_cap, hh.total_leaves);
-    c->direct_ws.want_partial_cap = std::max(c->direct_ws.want_partial_cap, hh.total_partials);
   }
-  if (hh.overflow) {
+  if (hh.total_leaves > hh.leaf_cap) {
     set_err(c, "leaf lists overflowed twice");
     return SFK_E_INTERNAL;
   }

@@ -31,3 +31,53 @@ def test_chunk_classes_are_one_group(ctx, torch):
             ctx.wait(ctx.submit(tree, [r], [o]))
             assert np.array_equal(a, o.cpu().numpy())
     tree.close()
+
+
+def _grids(ctx, tree, rois, shape, **opts):
+    ctx.set_eval_opts(tile_shape=shape, **opts)
+    out = [ctx.eval_roi(tree, r).cpu().numpy() for r in rois]
+    ctx.set_eval_opts()
+    return out
+
+
+# 1000 and 1728 tiles of 4^3, either side of the plan's 1024 in one launch
+@pytest.mark.parametrize("shape,res", [(1, 40), (1, 48), (2, 33), (3, 30), (4, 20), (5, 11),
+                                       (6, 40), (6, 170)])
+def test_scarce_slots_and_lists_bitwise(ctx, torch, shape, res):
+    pts = synth.clumpy_cloud(120_000, 7)
+    tree = ctx.build_tree(dev(torch, pts), knn_k=8)
+    # supports that reach most of a tile's neighbourhood: up to dozens of chunks
+    h = (0.11, 0.2, 0.15) if shape < 6 else (0.03, 0.02, 0.025)
+    rois = [Roi((0.05,) * 3, (0.95,) * 3, (res, res - 1, res), bw="fixed", h=h),
+            Roi((0.3,) * 3, (0.7,) * 3, (res,) * 3, bw="fixed", h=h, kernel="gauss_trunc3")]
+    if shape < 6:
+        rois.append(Roi((0.2,) * 3, (0.8,) * 3, (res,) * 3, bw="per_point"))
+    want = _grids(ctx, tree, rois, shape, partial_capacity=1 << (20 if shape < 6 else 11))
+    lists = dict(list_capacity=1 << 22)
+    for kw in [dict(partial_capacity=1, **lists), dict(partial_capacity=60, **lists),
+               dict(partial_capacity=3000, **lists), dict(partial_capacity=1, list_capacity=1),
+               dict(partial_capacity=60, list_capacity=3000),
+               dict(partial_capacity=3000, list_capacity=40_000), dict(list_capacity=3000)]:
+        for a, b, r in zip(want, _grids(ctx, tree, rois, shape, **kw), rois):
+            assert np.array_equal(a, b), (kw, r)
+    for a, r in zip(want, rois):
+        ctx.set_eval_opts(tile_shape=shape)
+        out = torch.full((r.n_nodes,), -1.0, device="cuda")
+        ctx.eval_roi_noalloc(tree, r, out)
+        assert np.array_equal(a, out.cpu().numpy())
+        ctx.set_eval_opts()
+    tree.close()
+
+
+@pytest.mark.parametrize("shape", [1, 6])
+def test_lists_are_exported_without_slots(ctx, torch, shape):
+    tree = ctx.build_tree(dev(torch, synth.clumpy_cloud(120_000, 7)))
+    roi = Roi((0.05,) * 3, (0.95,) * 3, (60,) * 3, bw="fixed", h=(0.05,) * 3)
+    ctx.set_eval_opts(tile_shape=shape)
+    _, cnt, leaves = ctx.debug_tile_leaves(tree, roi)
+    assert cnt.max() > 64  # more than a chunk of either shape: some tiles are split
+    ctx.set_eval_opts(tile_shape=shape, partial_capacity=1)
+    _, cnt1, leaves1 = ctx.debug_tile_leaves(tree, roi)
+    assert np.array_equal(cnt, cnt1) and np.array_equal(leaves, leaves1)
+    ctx.set_eval_opts()
+    tree.close()
