@@ -76,7 +76,7 @@ def test_lists_are_exported_without_slots(ctx, torch, shape):
     ctx.set_eval_opts(tile_shape=shape)
     _, cnt, leaves = ctx.debug_tile_leaves(tree, roi)
     assert cnt.max() > 64  # more than a chunk of either shape: some tiles are split
-    ctx.set_eval_opts(tile_shape=shape, partial_capacity=1)
+    ctx.set_eval_opts(tile_shape=shape, partial_capacity=1, list_capacity=1 << 22)
     _, cnt1, leaves1 = ctx.debug_tile_leaves(tree, roi)
     assert np.array_equal(cnt, cnt1) and np.array_equal(leaves, leaves1)
     ctx.set_eval_opts()
