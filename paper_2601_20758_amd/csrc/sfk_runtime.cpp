@@ -787,8 +787,10 @@ sfk_status reserve_group(sfk_ctx c, Workspace& ws, TileShape ts, int64_t n_rois,
     leaf_cap = std::max<int64_t>(leaf_cap, 2 * nr * std::max<int64_t>(1, sweep_boxes));
   }
   if (c->opts.list_capacity > 0 && !sweep) {
+    // one slot per default chunk of what the lists hold, however short the
+    // chunks are (a brick's slot has 32 KB)
     leaf_cap = c->opts.list_capacity;
-    partial_cap = std::max<int64_t>(1, c->opts.list_capacity / CH);
+    partial_cap = std::max<int64_t>(1, leaf_cap / (chosen ? CH : kDefaultChunkLeaves));
   }
   if (c->opts.partial_capacity > 0 && !sweep) partial_cap = c->opts.partial_capacity;
   SFK_TRY(ws_reserve(c, ws, ws.tile_cnt, sizeof(int32_t) * (size_t)tiles, "tile counts"));

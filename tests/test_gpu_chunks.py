@@ -81,3 +81,18 @@ def test_lists_are_exported_without_slots(ctx, torch, shape):
     assert np.array_equal(cnt, cnt1) and np.array_equal(leaves, leaves1)
     ctx.set_eval_opts()
     tree.close()
+
+
+@pytest.mark.parametrize("shape,res", [(6, 40), (6, 150), (1, 40)])
+def test_list_capacity_bounds_the_slots(sfk, torch, shape, res):
+    # 2^24 list entries: 65536 slots, 2 GiB of a brick's, whatever the chunks
+    pts = synth.clumpy_cloud(20_000, 3)
+    roi = Roi((0.1,) * 3, (0.9,) * 3, (res,) * 3, bw="fixed", h=(0.02,) * 3)
+    grids = []
+    for kw in [dict(budget_bytes=(2 << 30) + (256 << 20)), dict()]:
+        with sfk.Context(0, **kw) as c:
+            tree = c.build_tree(dev(torch, pts))
+            c.set_eval_opts(tile_shape=shape, list_capacity=1 << 24 if kw else 0)
+            grids.append(c.eval_roi(tree, roi).cpu().numpy())
+            tree.close()
+    assert np.array_equal(*grids)
