@@ -477,6 +477,7 @@ __global__ __launch_bounds__(kPlanNT) void k_plan_items(BatchHdr* __restrict__ h
       hdr->total_leaves = tl;
       hdr->n_items = tc;
       hdr->total_partials = tp;
+      hdr->fine_partials = tf;
       hdr->coarse = coarse ? 1 : 0;
     }
   }
@@ -2091,7 +2092,8 @@ __global__ __launch_bounds__(kPlanNT) void k_plan_one(const int32_t* __restrict_
   int64_t tl, tp, tc;
   const int64_t lo = block_excl_scan<kPlanNT>(cnt, &tl, lds);
   int64_t po = block_excl_scan<kPlanNT>(pneed, &tp, lds);
-  const bool coarse = tp > partial_cap;
+  const int64_t tf = tp;
+  const bool coarse = tf > partial_cap;
   if (coarse) {
     n = plan_items(cnt, fit_span(fit, true));
     pneed = plan_partials(n, hdr->splat);
@@ -2117,6 +2119,7 @@ __global__ __launch_bounds__(kPlanNT) void k_plan_one(const int32_t* __restrict_
     hdr->total_leaves = tl;
     hdr->n_items = tc;
     hdr->total_partials = tp;
+    hdr->fine_partials = tf;
     hdr->coarse = coarse ? 1 : 0;
   }
 }

@@ -77,6 +77,7 @@ struct alignas(16) BatchHdr {
   int64_t total_leaves;  // plan: candidate leaves over all tiles
   int64_t n_items;       // plan: work items
   int64_t total_partials;  // plan: partial-sum slots the split tiles need
+  int64_t fine_partials;   // plan: those they would need for chunks as items
   int32_t coarse;        // plan: 1 = work items are blocks, 0 = chunks
   int32_t debug_poison;  // host, tests only: bit 0 = the count pass stores out-of-range
                          // ids in the slots past the 64th of a tile, bit 1 = the fill

@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <chrono>
 #include <cmath>
 #include <cstdarg>
@@ -41,6 +42,9 @@ constexpr int kNumSlots = 4;
 constexpr int kStagingRing = 8;
 constexpr int kDefaultChunkLeaves = 256;
 constexpr int kBrickChunkLeaves = 64;
+// Partial slots (512 B each for 4x4x4 tiles) a workspace may take so that short
+// chunks can be work items. Regions that need more have work items enough.
+constexpr int64_t kFineSlots = 1 << 19;
 
 double now_s() {
   using namespace std::chrono;
@@ -93,6 +97,7 @@ struct Workspace {
   void* claims_cleared = nullptr;  // the claims buffer whose error word is zeroed
   int64_t want_leaf_cap = 0;
   int64_t want_partial_cap = 0;
+  int64_t want_fine_cap = 0;  // slots for short chunks as work items
   // last enqueued use of the buffers: a buffer that must grow waits for it
   hipEvent_t last_use = nullptr;
   bool last_use_valid = false;
@@ -757,26 +762,21 @@ sfk_status reserve_group(sfk_ctx c, Workspace& ws, TileShape ts, int64_t n_rois,
   const int64_t tiles = (int64_t)std::ceil((double)n_tiles * headroom);
   const int64_t nr = std::max<int64_t>(64, (int64_t)std::ceil((double)n_rois * headroom));
   const int64_t nc = std::max<int64_t>(1024, (int64_t)std::ceil((double)n_coords * headroom));
-  int64_t leaf_cap = std::max<int64_t>({ws.want_leaf_cap, (int64_t)1 << 20, 64 * tiles,
-                                        4 * tree_leaves});
-  // partial slots are small (T doubles per chunk): room for twice the
-  // chunks the leaf lists hold, so a batch whose lists overflow still splits
-  // its heavy tiles over work items (walking per chunk)
   const bool brick = sfk::is_brick(ts);
   const bool sweep = sfk::is_sweep(ts);
   const bool chosen = c->opts.chunk_leaves > 0;
-  // a brick's partial slot holds its kBrick^3 node sums (32 KB): one per
-  // split brick, up to 8192 of them; bricks beyond walk their whole tile in
-  // one work item (which needs no slot)
-  int64_t partial_cap =
-      brick ? std::max<int64_t>(64, std::min<int64_t>(tiles, 8192))
-            : std::max<int64_t>({ws.want_partial_cap, (int64_t)1 << 14, tiles / 4,
-                                 2 * leaf_cap / (chosen ? CH : kDefaultChunkLeaves)});
-  // the shorter default chunks need more slots: up to eight a tile, unless the
-  // caller budgets the memory (tiles without slots walk their chunks in one
-  // item, to the same sums)
-  if (!brick && !chosen && !c->budget)
-    partial_cap = std::max(partial_cap, std::min<int64_t>(8 * tiles, 2 * leaf_cap / CH));
+  int64_t leaf_cap = std::max<int64_t>({(int64_t)1 << 20, 64 * tiles, 4 * tree_leaves});
+  // partial slots are small (T doubles per item): room for twice the default
+  // chunks the leaf lists hold, so a batch whose lists overflow still splits
+  // its heavy tiles over work items (walking per item). A brick's slot holds its
+  // kBrick^3 node sums (32 KB): one per split brick, up to 8192 of them; bricks
+  // beyond are one work item each (which needs no slot).
+  auto slots_for = [&](int64_t leaves) {
+    return brick ? std::max<int64_t>(64, std::min<int64_t>(tiles, 8192))
+                 : std::max<int64_t>({(int64_t)1 << 14, tiles / 4,
+                                      2 * leaves / (chosen ? CH : kDefaultChunkLeaves)});
+  };
+  int64_t partial_cap = slots_for(leaf_cap);
   // the sweep: the node sums of every tile, and the (ROI, box) items of
   // every descriptor the header may hold (two int32 per item)
   const int64_t sweep_boxes = tree_leaves > SFK_FANOUT
@@ -793,31 +793,63 @@ sfk_status reserve_group(sfk_ctx c, Workspace& ws, TileShape ts, int64_t n_rois,
     partial_cap = std::max<int64_t>(1, leaf_cap / (chosen ? CH : kDefaultChunkLeaves));
   }
   if (c->opts.partial_capacity > 0 && !sweep) partial_cap = c->opts.partial_capacity;
-  SFK_TRY(ws_reserve(c, ws, ws.tile_cnt, sizeof(int32_t) * (size_t)tiles, "tile counts"));
-  SFK_TRY(ws_reserve(c, ws, ws.tile_fit, sizeof(int32_t) * (size_t)tiles, "tile flags"));
-  SFK_TRY(ws_reserve(c, ws, ws.tile_done, sizeof(int32_t) * (size_t)tiles, "tile counters"));
   const int32_t slot_cap = slot_cap_of(ts);
-  SFK_TRY(ws_reserve(c, ws, ws.tile_slots, sizeof(int32_t) * slot_cap * (size_t)tiles,
-                     "tile leaf slots"));
-  SFK_TRY(ws_reserve(c, ws, ws.leaf_off, sizeof(int64_t) * (size_t)(tiles + 1), "leaf offsets"));
-  SFK_TRY(ws_reserve(c, ws, ws.partial_off, sizeof(int64_t) * (size_t)(tiles + 1), "partial offsets"));
-  SFK_TRY(ws_reserve(c, ws, ws.chunk_off, sizeof(int64_t) * (size_t)(tiles + 1), "item offsets"));
-  SFK_TRY(ws_reserve(c, ws, ws.leaves, sizeof(int32_t) * (size_t)leaf_cap, "leaf lists"));
-  SFK_TRY(ws_reserve(c, ws, ws.partials, sizeof(double) * (size_t)partial_cap * T, "partial sums"));
-  SFK_TRY(ws_reserve(c, ws, ws.hdr_rois, sizeof(BatchHdr) + sizeof(RoiDev) * (size_t)nr,
-                     "ROI descriptors"));
-  SFK_TRY(ws_reserve(c, ws, ws.coords, sizeof(double) * (size_t)nc, "node coordinates"));
-  SFK_TRY(ws_reserve(c, ws, ws.claims, kClaimBytes, "work-claim counters"));
+  struct Need {
+    DevBuf* b;
+    size_t bytes;
+    const char* what;
+  };
+  auto needs = [&](int64_t leaves, int64_t slots) {
+    return std::array<Need, 15>{{
+        {&ws.tile_cnt, sizeof(int32_t) * (size_t)tiles, "tile counts"},
+        {&ws.tile_fit, sizeof(int32_t) * (size_t)tiles, "tile flags"},
+        {&ws.tile_done, sizeof(int32_t) * (size_t)tiles, "tile counters"},
+        {&ws.tile_slots, sizeof(int32_t) * slot_cap * (size_t)tiles, "tile leaf slots"},
+        {&ws.leaf_off, sizeof(int64_t) * (size_t)(tiles + 1), "leaf offsets"},
+        {&ws.partial_off, sizeof(int64_t) * (size_t)(tiles + 1), "partial offsets"},
+        {&ws.chunk_off, sizeof(int64_t) * (size_t)(tiles + 1), "item offsets"},
+        {&ws.leaves, sizeof(int32_t) * (size_t)leaves, "leaf lists"},
+        {&ws.partials, sizeof(double) * (size_t)slots * T, "partial sums"},
+        {&ws.hdr_rois, sizeof(BatchHdr) + sizeof(RoiDev) * (size_t)nr, "ROI descriptors"},
+        {&ws.coords, sizeof(double) * (size_t)nc, "node coordinates"},
+        {&ws.claims, kClaimBytes, "work-claim counters"},
+        {&ws.roi_leaves, sizeof(int32_t) * kRoiListCap * (size_t)nr, "ROI leaf lists"},
+        {&ws.roi_nl, sizeof(int32_t) * (size_t)nr, "ROI list lengths"},
+        {&ws.plan_tmp, sfk::kPlanSums * sizeof(int64_t) * (size_t)sfk::plan_blocks(tiles),
+         "plan block sums"},
+    }};
+  };
+  // More list entries and slots make a batch faster and change no result: what
+  // earlier batches lacked, and slots for short chunks, up to eight a tile of the
+  // largest region that takes them (16384 tiles), where there is no budget.
+  const int64_t base_leaves = leaf_cap, base_slots = partial_cap;
+  if (c->opts.list_capacity == 0 || sweep) {
+    const bool tile_slots = !brick && !sweep && c->opts.partial_capacity == 0;
+    const int64_t wl = std::max(leaf_cap, ws.want_leaf_cap);
+    const int64_t wp = tile_slots ? std::max(slots_for(wl), ws.want_partial_cap) : partial_cap;
+    leaf_cap = wl;
+    partial_cap = wp;
+    if (tile_slots && !chosen && !c->budget && CH < kDefaultChunkLeaves)
+      partial_cap = std::max({partial_cap, ws.want_fine_cap,
+                              std::min(8 * std::min<int64_t>(tiles, 16384), 2 * leaf_cap / CH)});
+  }
+  for (const Need& n : needs(leaf_cap, partial_cap)) {
+    const size_t had = n.b->bytes;
+    sfk_status st = ws_reserve(c, ws, *n.b, n.bytes, n.what);
+    if (st == SFK_E_NOMEM && (n.b == &ws.leaves || n.b == &ws.partials)) {
+      // no more than is needed, then, but never less than there was: another
+      // group of the batch may count on it
+      for (const Need& m : needs(base_leaves, base_slots))
+        if (m.b == n.b && m.bytes < n.bytes)
+          st = ws_reserve(c, ws, *n.b, std::max(m.bytes, had), n.what);
+    }
+    SFK_TRY(st);
+  }
   if (ws.claims_cleared != ws.claims.p) {
     // a new buffer: its error word starts at zero (no kernel clears it)
     SFK_HIP(c, sfk::launch_fill_f32((float*)ws.claims.p, (int64_t)(ws.claims.bytes / 4), 0.0f, s));
     ws.claims_cleared = ws.claims.p;
   }
-  SFK_TRY(ws_reserve(c, ws, ws.roi_leaves, sizeof(int32_t) * kRoiListCap * (size_t)nr,
-                     "ROI leaf lists"));
-  SFK_TRY(ws_reserve(c, ws, ws.roi_nl, sizeof(int32_t) * (size_t)nr, "ROI list lengths"));
-  SFK_TRY(ws_reserve(c, ws, ws.plan_tmp, sfk::kPlanSums * sizeof(int64_t) * (size_t)sfk::plan_blocks(tiles),
-                     "plan block sums"));
   Caps k;
   k.tiles_cap = std::min<int64_t>({(int64_t)(ws.plan_tmp.bytes / (sfk::kPlanSums * sizeof(int64_t))) * 1024,
                                    (int64_t)(ws.tile_cnt.bytes / sizeof(int32_t)),
@@ -1199,6 +1231,9 @@ bool absorb_stats(Workspace& ws, const Staging& st) {
   if (h.total_leaves > h.leaf_cap) ws.want_leaf_cap = h.total_leaves + h.total_leaves / 4;
   if (h.total_partials > h.partial_cap)
     ws.want_partial_cap = h.total_partials + h.total_partials / 4;
+  if (h.coarse && !h.splat && h.fine_partials <= kFineSlots)
+    ws.want_fine_cap =
+        std::max(ws.want_fine_cap, std::min(kFineSlots, h.fine_partials + h.fine_partials / 4));
   int32_t* e = st.err_host();
   const bool err = *e != 0;
   *e = 0;

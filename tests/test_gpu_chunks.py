@@ -96,3 +96,27 @@ def test_list_capacity_bounds_the_slots(sfk, torch, shape, res):
             grids.append(c.eval_roi(tree, roi).cpu().numpy())
             tree.close()
     assert np.array_equal(*grids)
+
+
+def test_batch_memory_is_bounded(sfk, torch):
+    # 3.5M tiles of short chunks: slots for a bounded number of them
+    pts = synth.clumpy_cloud(50_000, 5)
+    free = lambda: torch.cuda.mem_get_info()[0]
+    used = []
+    for count in (4, 256):
+        rois = [Roi((0.1,) * 3, (0.3,) * 3, (96,) * 3, bw="per_point")] * count
+        out = torch.empty((count, rois[0].n_nodes), device="cuda")
+        torch.cuda.synchronize()
+        with sfk.Context(0, allocator="hip") as c:
+            tree = c.build_tree(dev(torch, pts), knn_k=8)
+            c.set_eval_opts(disable_graphs=True)
+            a = free()
+            c.wait(c.submit(tree, rois, list(out)))
+            used.append(a - free())
+            assert bool((out == out[0]).all())
+            tree.close()
+        del out
+    # per tile: lists of 64 leaves, a quarter of a slot of 512 B, counts and the
+    # count pass's 256 leaves; 131072 slots for short chunks beside that
+    tiles = 256 * 24 ** 3
+    assert used[1] - used[0] < tiles * (64 * 4 + 512 // 4 + 256 * 4 + 64 + 512 // 2) + (64 << 20)
