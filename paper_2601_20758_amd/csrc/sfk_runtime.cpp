@@ -820,15 +820,26 @@ sfk_status reserve_group(sfk_ctx c, Workspace& ws, TileShape ts, int64_t n_rois,
     }};
   };
   // More list entries and slots make a batch faster and change no result: what
-  // earlier batches lacked, and slots for short chunks, up to eight a tile of the
-  // largest region that takes them (16384 tiles), where there is no budget.
+  // earlier batches lacked, under a budget only where it fits, and slots for
+  // short chunks, up to eight a tile of the largest region that takes them
+  // (16384 tiles), without one.
   const int64_t base_leaves = leaf_cap, base_slots = partial_cap;
   if (c->opts.list_capacity == 0 || sweep) {
     const bool tile_slots = !brick && !sweep && c->opts.partial_capacity == 0;
     const int64_t wl = std::max(leaf_cap, ws.want_leaf_cap);
     const int64_t wp = tile_slots ? std::max(slots_for(wl), ws.want_partial_cap) : partial_cap;
-    leaf_cap = wl;
-    partial_cap = wp;
+    size_t grow = 0;
+    if (c->budget) {
+      auto add = [&](const DevBuf& b, size_t bytes) {
+        if (bytes > b.bytes) grow += round_bytes(std::max(bytes, b.bytes + b.bytes / 4)) - b.bytes;
+      };
+      for (const Need& n : needs(wl, wp)) add(*n.b, n.bytes);
+      add(ws.item_tile, 5 * (ws.tile_cnt.bytes / 4 + (size_t)(tiles + wp + (brick ? wl / CH : 0))));
+    }
+    if (!c->budget || c->ws_bytes + grow <= c->budget) {
+      leaf_cap = wl;
+      partial_cap = wp;
+    }
     if (tile_slots && !chosen && !c->budget && CH < kDefaultChunkLeaves)
       partial_cap = std::max({partial_cap, ws.want_fine_cap,
                               std::min(8 * std::min<int64_t>(tiles, 16384), 2 * leaf_cap / CH)});

@@ -98,6 +98,41 @@ def test_list_capacity_bounds_the_slots(sfk, torch, shape, res):
     assert np.array_equal(*grids)
 
 
+def test_budgeted_batch_is_accepted_again(sfk, torch):
+    # a chunk-heavy per-point batch in the budget its first call needs: what it
+    # lacked must not make the next calls ask for more than there is
+    pts = synth.clumpy_cloud(400_000, 5)
+    rois = [Roi((0.05,) * 3, (0.95,) * 3, (48,) * 3, bw="per_point"),
+            Roi((0.2,) * 3, (0.6,) * 3, (40,) * 3, bw="per_point"),
+            Roi((0.05,) * 3, (0.95,) * 3, (48,) * 3, bw="fixed", h=(0.2,) * 3)]
+    outs = [torch.empty(r.n_nodes, device="cuda") for r in rois]
+    want, low = None, None
+    for mb in (1 << 12, *range(16, 400, 4)):
+        with sfk.Context(0, budget_bytes=mb << 20) as c:
+            tree = c.build_tree(dev(torch, pts), knn_k=48)
+            c.set_eval_opts(tile_shape=1)
+            try:
+                c.wait(c.submit(tree, rois, outs))
+            except sfk.SfkError as e:
+                assert e.status == 3  # SFK_E_BUDGET: below what a first call needs
+                tree.close()
+                continue
+            got = [o.cpu().numpy() for o in outs]
+            if want is None:
+                want = got
+            for _ in range(4):
+                c.wait(c.submit(tree, rois, outs))
+                for a, o in zip(want, outs):
+                    assert np.array_equal(a, o.cpu().numpy()), mb
+                    o.fill_(-1.0)
+            tree.close()
+            if mb < 1 << 12:
+                low = low or mb
+                if mb > low + 60:
+                    break
+    assert low is not None
+
+
 def test_batch_memory_is_bounded(sfk, torch):
     # 3.5M tiles of short chunks: slots for a bounded number of them
     pts = synth.clumpy_cloud(50_000, 5)
