@@ -255,12 +255,13 @@ __device__ __forceinline__ bool mode_whole(int mode) {
 // of a tile_fit entry
 __device__ __forceinline__ int fit_mode(int fit) { return fit & 3; }
 __device__ __forceinline__ int fit_chunk(int fit) {
-  return (fit & ((1 << kFitBlock) - 1)) >> kFitChunk;
+  return (fit & ((1 << kFitCoarse) - 1)) >> kFitChunk;
 }
+__device__ __forceinline__ int fit_coarse(int fit) { return (fit >> kFitCoarse) & 1; }
 __device__ __forceinline__ int fit_block(int fit) { return fit >> kFitBlock; }
 // leaves of a work item
-__device__ __forceinline__ int fit_span(int fit, bool coarse) {
-  return coarse ? fit_chunk(fit) << fit_block(fit) : fit_chunk(fit);
+__device__ __forceinline__ int fit_span(int fit) {
+  return fit_chunk(fit) << (fit_coarse(fit) ? fit_block(fit) : 0);
 }
 
 template <int TX, int TY, int TZ>
@@ -384,11 +385,13 @@ __device__ __forceinline__ int64_t block_sum(int64_t v, int64_t* lds) {
   return tot;
 }
 
-// sum of bs[stride * i + k] over the blocks i < nb
-__device__ __forceinline__ int64_t sum_before(const int64_t* __restrict__ bs, int stride, int k,
-                                              int64_t nb, int64_t* lds) {
+// sum of bs[kPlanSums * i + k] over the blocks i < nb (each wavefront by itself
+// where its lanes hold them all)
+__device__ __forceinline__ int64_t sum_before(const int64_t* __restrict__ bs, int k, int64_t nb,
+                                              int64_t* lds) {
+  if (nb <= 64) return wave_sum(lane_id() < nb ? bs[kPlanSums * lane_id() + k] : (int64_t)0);
   int64_t v = 0;
-  for (int64_t i = threadIdx.x; i < nb; i += kPlanNT) v += bs[stride * i + k];
+  for (int64_t i = threadIdx.x; i < nb; i += kPlanNT) v += bs[kPlanSums * i + k];
   return block_sum(v, lds);
 }
 
@@ -403,8 +406,8 @@ __global__ __launch_bounds__(kPlanNT) void k_plan_sums(const int32_t* __restrict
   const int64_t cnt = t < n_tiles ? tile_cnt[t] : 0;
   const int fit = t < n_tiles ? tile_fit[t] : 1 << kFitChunk;
   const int64_t sl = block_sum(cnt, lds);
-  const int64_t sf = block_sum(plan_partials(plan_items(cnt, fit_span(fit, false)), hdr->splat), lds);
-  const int64_t sc = block_sum(plan_partials(plan_items(cnt, fit_span(fit, true)), hdr->splat), lds);
+  const int64_t sf = block_sum(plan_partials(plan_items(cnt, fit_span(fit)), hdr->splat), lds);
+  const int64_t sc = block_sum(plan_partials(plan_items(cnt, fit_span(fit | 1 << kFitCoarse)), hdr->splat), lds);
   if (threadIdx.x == 0) {
     bs[kPlanSums * blockIdx.x] = sl;
     bs[kPlanSums * blockIdx.x + 1] = sf;
@@ -425,14 +428,14 @@ __global__ __launch_bounds__(kPlanNT) void k_plan_modes(const int32_t* __restric
   const int64_t partial_cap = hdr->partial_cap;
   if ((int64_t)blockIdx.x * kPlanNT >= n_tiles) return;
   const int64_t nb = (n_tiles + kPlanNT - 1) / kPlanNT;
-  const bool coarse = sum_before(bs, kPlanSums, 1, nb, lds) > partial_cap;
-  const int64_t base_l = sum_before(bs, kPlanSums, 0, blockIdx.x, lds);
-  const int64_t base_p = sum_before(bs, kPlanSums, coarse ? 2 : 1, blockIdx.x, lds);
+  const bool coarse = sum_before(bs, 1, nb, lds) > partial_cap;
+  const int64_t base_l = sum_before(bs, 0, blockIdx.x, lds);
+  const int64_t base_p = sum_before(bs, coarse ? 2 : 1, blockIdx.x, lds);
   const int64_t t = (int64_t)blockIdx.x * kPlanNT + threadIdx.x;
   const bool v = t < n_tiles;
   const int64_t cnt = v ? tile_cnt[t] : 0;
-  const int fit = v ? tile_fit[t] : 1 << kFitChunk;
-  const int64_t n = plan_items(cnt, fit_span(fit, coarse));
+  const int fit = (v ? tile_fit[t] : 1 << kFitChunk) | (coarse ? 1 << kFitCoarse : 0);
+  const int64_t n = plan_items(cnt, fit_span(fit));
   const int64_t pneed = plan_partials(n, hdr->splat);
   int64_t tot;
   const int64_t lo = base_l + block_excl_scan<kPlanNT>(cnt, &tot, lds);
@@ -462,11 +465,11 @@ __global__ __launch_bounds__(kPlanNT) void k_plan_items(BatchHdr* __restrict__ h
   if (blockIdx.x == 0) {
     // totals (block 0 runs even for an empty batch)
     const int64_t partial_cap = hdr->partial_cap;
-    const int64_t tl = sum_before(bs, kPlanSums, 0, nb, lds);
-    const int64_t tf = sum_before(bs, kPlanSums, 1, nb, lds);
+    const int64_t tl = sum_before(bs, 0, nb, lds);
+    const int64_t tf = sum_before(bs, 1, nb, lds);
     const bool coarse = tf > partial_cap;
-    const int64_t tp = coarse ? sum_before(bs, kPlanSums, 2, nb, lds) : tf;
-    const int64_t tc = sum_before(bs, kPlanSums, 3, nb, lds);
+    const int64_t tp = coarse ? sum_before(bs, 2, nb, lds) : tf;
+    const int64_t tc = sum_before(bs, 3, nb, lds);
     // every thread of this block has read the header before thread 0 writes it
     __syncthreads();
     if (threadIdx.x < kClaimSlices) claims[threadIdx.x * kClaimStride] = 0;
@@ -482,7 +485,7 @@ __global__ __launch_bounds__(kPlanNT) void k_plan_items(BatchHdr* __restrict__ h
     }
   }
   if ((int64_t)blockIdx.x >= nb) return;
-  const int64_t base_c = sum_before(bs, kPlanSums, 3, blockIdx.x, lds);
+  const int64_t base_c = sum_before(bs, 3, blockIdx.x, lds);
   const int64_t t = (int64_t)blockIdx.x * kPlanNT + threadIdx.x;
   const bool v = t < n_tiles;
   const int64_t nit = v ? chunk_off[t] : 0;
@@ -583,14 +586,17 @@ __device__ __forceinline__ void agent_writes_done() {
 // four the sums spill. That grid takes 1.0 ms (1.37 with the cull in double,
 // a maximum per term, a queue moved to the front after each batch and ids read
 // from LDS), the 101x87x93 per-point grid of 1M points 0.18 ms (0.39).
+// (The order of the arguments keeps the compiler from loading and spilling them
+// eight registers at a time, with scratch memory for it.)
 template <int TX, int TY, int TZ, int KK, int PP, bool CNT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_eval(
     TreeView tv, const RoiDev* __restrict__ rois, const double* __restrict__ coords,
+    const BatchHdr* __restrict__ hdr, int32_t* __restrict__ claims,
     const int64_t* __restrict__ leaf_off, const int64_t* __restrict__ chunk_off,
     const int64_t* __restrict__ partial_off, const int32_t* __restrict__ tile_cnt,
     const int32_t* __restrict__ tile_fit, const int32_t* __restrict__ leaves,
     const int32_t* __restrict__ item_tile, double* __restrict__ partials,
-    int32_t* __restrict__ tile_done, BatchHdr* __restrict__ hdr, int32_t* __restrict__ claims) {
+    int32_t* __restrict__ tile_done) {
   constexpr int T = TX * TY * TZ;
   constexpr int NPL = T >= 64 ? T / 64 : 1;
   // Per-lane node accumulators are float32: a lane adds one term per drained
@@ -610,7 +616,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
   __shared__ float4 lds_qprm[4][PP == PP_ANISO ? QCAP : 1];
   const int lane = lane_id(), wave = threadIdx.x >> 6;
   const int64_t n_items = min(hdr->n_items, hdr->item_cap);  // equal by construction
-  const int n_rois = hdr->n_rois, coarse = hdr->coarse;
+  const int n_rois = hdr->n_rois;
   // XCD-aware work stealing. Workgroups are dispatched round-robin over the
   // 8 XCDs, each with its own L2. The item list is cut into kClaimSlices
   // contiguous (hence spatially coherent) slices, 8 per XCD, each with its own
@@ -678,7 +684,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     const float cc = (float)(c2 * (kWide * kWide));
     const int cnt = tile_cnt[t];  // > 0: tiles with no candidate leaf have no work item
     const int fit = wave_uniform(tile_fit[t]), mode = fit_mode(fit);
-    const int chunk = fit_chunk(fit), span = fit_span(fit, coarse);
+    const int chunk = fit_chunk(fit), span = fit_span(fit);
     const int nit = (cnt + span - 1) / span;
 
     Acc acc[T];
@@ -906,7 +912,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
           agent_writes_done();
           if (lane_writes) {
             const int64_t p0 = partial_off[t] * T;
-            const int ends = coarse ? 0 : block_mask;
+            const int ends = fit_coarse(fit) ? 0 : block_mask;
 #pragma unroll
             for (int m = 0; m < NPL; ++m) {
               const int node = lane_node(m);
@@ -1126,11 +1132,12 @@ __device__ __forceinline__ int64_t claim_item(int32_t* __restrict__ claims, int6
 template <int KK, bool CNT>
 __global__ __launch_bounds__(256) void k_splat(
     TreeView tv, const RoiDev* __restrict__ rois, const double* __restrict__ coords,
+    const BatchHdr* __restrict__ hdr, int32_t* __restrict__ claims,
     const int64_t* __restrict__ leaf_off, const int64_t* __restrict__ chunk_off,
     const int64_t* __restrict__ partial_off, const int32_t* __restrict__ tile_cnt,
     const int32_t* __restrict__ tile_fit, const int32_t* __restrict__ leaves,
     const int32_t* __restrict__ item_tile, double* __restrict__ partials,
-    int32_t* __restrict__ tile_done, BatchHdr* __restrict__ hdr, int32_t* __restrict__ claims) {
+    int32_t* __restrict__ tile_done) {
   constexpr int B = kBrick;
   constexpr int T = B * B * B;
   __shared__ unsigned long long sums[T];
@@ -1226,11 +1233,18 @@ __global__ __launch_bounds__(256) void k_splat(
               const double uy = (lds_c[1][jy] - pp[1]) * ih[1];
               const unsigned int yq = epan_sq_units(uy * uy);
               if (epan_units(xmax, yq) <= zq) continue;
-              const int row = B * (jy + B * kz), at = a[0] + 3 * jy + 5 * kz;
+              // byte offsets of the row and of its first node's swizzled slot,
+              // made here: the compiler made them again in each node's branch
+              // of one of the copies of this code, whose share of a 256^3 zoom
+              // was 142 us for 129
+              int row = 8 * B * (jy + B * kz), at = 8 * (a[0] + 3 * jy + 5 * kz);
+              asm volatile("" : "+v"(row), "+v"(at));
 #pragma unroll
               for (int m = 0; m < kSpan; ++m) {
                 const unsigned int q = epan_units(epan_units(xq[m], yq), zq);
-                if (q != 0u) atomicAdd(&sums[row + ((at + m) & (B - 1))], (unsigned long long)q);
+                if (q != 0u)
+                  atomicAdd((unsigned long long*)((char*)sums + (row + ((at + 8 * m) & (8 * (B - 1))))),
+                            (unsigned long long)q);
               }
             }
           }
@@ -1329,7 +1343,7 @@ __global__ __launch_bounds__(256) void k_splat(
     };
 
     const int cnt = tile_cnt[t];
-    const int fit = tile_fit[t], mode = fit_mode(fit), span = fit_span(fit, hdr->coarse);
+    const int fit = tile_fit[t], mode = fit_mode(fit), span = fit_span(fit);
     const int nit = (cnt + span - 1) / span;
     const bool whole = mode_whole(mode);
     const int c = (int)(item - chunk_off[t]);
@@ -2086,8 +2100,8 @@ __global__ __launch_bounds__(kPlanNT) void k_plan_one(const int32_t* __restrict_
   const int64_t t = threadIdx.x;
   const bool v = t < n_tiles;
   const int64_t cnt = v ? tile_cnt[t] : 0;
-  const int fit = v ? tile_fit[t] : 1 << kFitChunk;
-  int64_t n = plan_items(cnt, fit_span(fit, false));
+  int fit = v ? tile_fit[t] : 1 << kFitChunk;
+  int64_t n = plan_items(cnt, fit_span(fit));
   int64_t pneed = plan_partials(n, hdr->splat);
   int64_t tl, tp, tc;
   const int64_t lo = block_excl_scan<kPlanNT>(cnt, &tl, lds);
@@ -2095,7 +2109,8 @@ __global__ __launch_bounds__(kPlanNT) void k_plan_one(const int32_t* __restrict_
   const int64_t tf = tp;
   const bool coarse = tf > partial_cap;
   if (coarse) {
-    n = plan_items(cnt, fit_span(fit, true));
+    fit |= 1 << kFitCoarse;
+    n = plan_items(cnt, fit_span(fit));
     pneed = plan_partials(n, hdr->splat);
     po = block_excl_scan<kPlanNT>(pneed, &tp, lds);
   }
@@ -2185,8 +2200,8 @@ static hipError_t launch_eval_shape(int kk, int pp, bool cnt, int grid, int n_cu
     }                                                                                          \
     const int g_ = grid > 0 ? grid : std::max(1, std::min(n_cu * occ_, max_blocks));          \
     hipLaunchKernelGGL((k_eval<X, Y, Z, KK, PP, C>), dim3(g_), dim3(256), 0, s, tv, rois,      \
-                       coords, leaf_off, chunk_off, partial_off, tile_cnt,                     \
-                       tile_fit, leaves, item_tile, partials, tile_done, hdr, claims);         \
+                       coords, hdr, claims, leaf_off, chunk_off, partial_off, tile_cnt,        \
+                       tile_fit, leaves, item_tile, partials, tile_done);                      \
   } while (0)
   if (cnt) {
     if (pp == PP_UNIFORM) SFK_E(KK_EPAN, PP_UNIFORM, true);
@@ -2228,8 +2243,8 @@ hipError_t launch_eval(TreeView tv, const BatchHdr* hdr_c, const RoiDev* rois,
     }                                                                                         \
     const int g_ = grid_blocks > 0 ? grid_blocks : std::max(1, std::min(n_cu * occ_, max_blocks)); \
     hipLaunchKernelGGL((k_splat<KK, C>), dim3(g_), dim3(256), 0, s, tv, rois, coords,         \
-                       leaf_off, chunk_off, partial_off, tile_cnt, tile_fit,                  \
-                       leaves, item_tile, partials, tile_done, hdr, claims);                  \
+                       hdr, claims, leaf_off, chunk_off, partial_off, tile_cnt, tile_fit,     \
+                       leaves, item_tile, partials, tile_done);                               \
   } while (0)
     if (cnt)
       SFK_S(KK_EPAN, true);

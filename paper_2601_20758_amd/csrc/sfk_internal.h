@@ -61,8 +61,9 @@ struct alignas(16) RoiDev {
   int32_t pad_;
 };
 // How a tile is evaluated (tile_fit): the plan's mode in bits 0-1, the chunk
-// (at most 2^20 leaves) from bit 2, block_log2 from bit 24.
-constexpr int kFitChunk = 2, kFitBlock = 24;
+// (at most 2^20 leaves) from bit 2, in bit 23 whether its items are blocks,
+// block_log2 from bit 24.
+constexpr int kFitChunk = 2, kFitCoarse = 23, kFitBlock = 24;
 
 // Device-side header of one batch, staged by the host together with the ROI
 // descriptors (so a captured graph can be replayed for any batch that fits
