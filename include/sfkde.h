@@ -232,18 +232,20 @@ typedef struct {
                             whose support spans at most 8 nodes per axis, others take
                             the default of their key without the sweep) */
   int32_t chunk_leaves;  /* leaves per work item (heavy tiles are split), 0 =
-                            automatic: 256,
-                            wavefront tiles of ROIs below 16384 tiles 32, bricks 64
-                            or, few of them over a small cloud, 8 */
+                            automatic: 32 for wavefront tiles of ROIs below 16384
+                            tiles, 64 for bricks or, few of them over a small cloud,
+                            8, and 256 else and where the partial slots do not last
+                            for shorter ones (same results, bitwise) */
   int32_t persistent_waves_per_cu; /* 0 = automatic */
   int32_t list_capacity; /* leaf-list entries per batch, 0 = automatic; tiles whose
                             lists do not fit walk the tree inside the evaluation
-                            kernel instead (same results, bitwise): one work item
-                            per chunk while partial slots remain, else one per tile */
+                            kernel instead (same results, bitwise): several work items
+                            while partial slots remain, else one per tile */
   int32_t disable_graphs; /* 1: batches on context streams use direct launches
                              instead of each slot's captured hipGraph */
-  int32_t partial_capacity; /* partial-sum slots (chunks of split tiles) per batch,
-                               0 = automatic (list_capacity / chunk_leaves when
+  int32_t partial_capacity; /* partial-sum slots (items of split tiles, one for all
+                               of a brick's) per batch, 0 = automatic
+                               (list_capacity / chunk_leaves, 256 by default, when
                                list_capacity is set) */
 } sfk_eval_opts;
 sfk_status sfk_set_eval_opts(sfk_ctx ctx, const sfk_eval_opts* opts);

@@ -916,7 +916,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KM <= 32 ? 
     // column's end, which advances past the accepted ones only).
     //
     // Bound by VALU issue (10M clustered points, k = 32: 6.2 ms, 8.35 ms with
-    // the insertion below). A leaf evaluates 103 groups and sorts 32 runs in:
+    // an insertion per candidate). A leaf evaluates 103 groups and sorts 32 runs in:
     // appending costs three instructions a candidate, and a run is read, sorted
     // (63 compare-exchanges) and merged (16 minima, 80 compare-exchanges) for
     // every lane at once, some 320 instructions. Inserting each group's
@@ -1069,7 +1069,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KM <= 32 ? 
     // Phase 0 visits the leaf itself and its curve neighbours, which bound
     // every lane's answer from above; tau is then the wavefront's largest
     // bound. Each later phase visits one collected chunk of the walk. One
-    // visiting site keeps a single copy of the insertion code.
+    // visiting site keeps a single copy of the queue's and the networks' code.
     for (int phase = 0;; ++phase) {
       int no;
       if (phase == 0) {

@@ -557,13 +557,25 @@ __device__ __forceinline__ void reduce_nodes(A (&acc)[T]) {
 // leaf ids a walking work item holds (two blocks of 64 and a step's 64 more)
 constexpr int kWalkRing = 256;
 
-// Wait until this wavefront's agent-scope stores and atomics are performed.
-// Those go to the memory side of the eight XCDs' L2s themselves, and readers
-// load them at agent scope, so a chunk that publishes sums only has to wait
-// for its own before it counts itself done. A device-wide fence in its place
-// also writes back and invalidates the XCD's whole L2 on every chunk: the
-// 128^3 MBE estimate of 2.1M particles in chunks of 64 leaves (three a tile)
-// took 3.63 ms with it and 1.93 without, in chunks of 32 5.57 and 2.06.
+// The hand-over of a split tile's sums from the items that made them to the
+// last one, which combines them. Sums are stored and loaded as relaxed atomics
+// of agent scope, which go past the L2s of the eight XCDs to the memory they
+// share (the memory model of the gfx942 family in LLVM's user guide for the
+// AMDGPU backend), and an item waits for its own before it counts itself done.
+// An agent release would write back, and an acquire invalidate, the XCD's whole
+// L2 for the plain stores and loads that might go with them; there must be
+// none: whatever is handed over goes through these functions (or through
+// atomicAdd). With a device-wide fence per chunk the 128^3 MBE estimate of 2.1M
+// particles in chunks of 64 leaves (three a tile) took 3.63 ms, and 1.93
+// without, in chunks of 32 5.57 and 2.06.
+template <typename V>
+__device__ __forceinline__ void hand_over(V* p, V v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename V>
+__device__ __forceinline__ V handed_over(const V* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 __device__ __forceinline__ void agent_writes_done() {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
@@ -575,8 +587,8 @@ __device__ __forceinline__ void agent_writes_done() {
 // (Epanechnikov / truncated Gaussian), bandwidth source (uniform, per-particle
 // isotropic, per-particle anisotropic) and counting mode. Membership and the
 // Epanechnikov value 1 - u2 are double (same rate as unpacked float32 on
-// gfx950), each term then rounded once to float32; the Gaussian factors are
-// float32 exp2 of the double exponents.
+// gfx950), each term then rounded once to float32 where the sums are; the
+// Gaussian factors are float32 exp2 of the double exponents.
 //
 // Bound by VALU issue, two thirds busy, half of it culling (a 4x4x4 tile whose
 // supports span 11 nodes tests four particles for each that reaches it) and
@@ -690,11 +702,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     Acc acc[T];
 
     // Per-wave queue of particles whose support reaches the tile box. Each
-    // leaf is loaded one particle per lane and culled against the tile with
-    // the same monotone-rounding bound as the tree walk (a culled particle
-    // would only add exact zeros); survivors are appended in leaf-then-lane
-    // order and evaluated 64 at a time, so lanes stay busy with particles
-    // that can matter. The order is fixed, hence so are the sums.
+    // leaf is loaded one particle per lane and culled against the tile (in
+    // float32 with a margin, keep_of: a culled particle reaches no node);
+    // survivors are appended in leaf-then-lane order and evaluated 64 at a
+    // time, so lanes stay busy with particles that can matter. The order is
+    // fixed, hence so are the sums.
     float4* qp = lds_qpts[wave];
     float4* qa = lds_qprm[wave];
     int qn = 0, qh = 0;  // particles queued, place of the first
@@ -749,12 +761,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
             }
           }
       } else if constexpr (KK == KK_EPAN) {
-        // 1 - u2 = ((1 - sx) - sy) - sz, clamped to [0, 1] (it never exceeds
-        // 1; the clamp is an output modifier of the subtraction, a maximum
-        // would be an instruction) and added, or multiplied and added, in
-        // double: two instructions a node. The rounding differs from
-        // 1 - ((sx + sy) + sz) by at most an ulp of double or two; a term at
-        // the support's edge is then +-1e-16, not 0.
+        // 1 - u2 = ((1 - sx) - sy) - sz in double, clamped to [0, 1] (it never
+        // exceeds 1; the clamp is an output modifier of the subtraction, a
+        // maximum would be an instruction), then added, or multiplied and
+        // added: in double for tiles of at most 16 nodes, two instructions a
+        // node, after a conversion to float32 for larger ones. The rounding
+        // differs from 1 - ((sx + sy) + sz) by at most an ulp of double or
+        // two; a term at the support's edge is then up to 1e-16, not 0.
         double ox[TX];
 #pragma unroll
         for (int i = 0; i < TX; ++i) ox[i] = 1.0 - sx[i];
@@ -838,7 +851,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     // d is the distance from the box's centre (as a float), rounded once, the
     // half width is taken 2^-20 larger and the support 2^-20 wider, while all
     // roundings together stay below 2^-22. A particle that reaches a node is
-    // always kept; one kept in vain adds exact zeros (+-1e-16 at the edge).
+    // always kept; one kept in vain adds zeros (up to 1e-16 at the edge).
     // 10 to 16 instructions; in double, with its conversions and maxima, the
     // test took about 30.
     auto keep_of = [&](const float4 p, const float4 prm) __attribute__((always_inline)) {
@@ -900,9 +913,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
         const int64_t pbase = (partial_off[t] + c) * T;
         if (lane_writes) {
 #pragma unroll
-          for (int m = 0; m < NPL; ++m)
-            __hip_atomic_store(&partials[pbase + lane_node(m)], dacc[m], __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
+          for (int m = 0; m < NPL; ++m) hand_over(&partials[pbase + lane_node(m)], dacc[m]);
         }
         agent_writes_done();
         int prev = 0;
@@ -918,8 +929,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
               const int node = lane_node(m);
               double s = 0.0, b = 0.0;
               for (int q = 0; q < nit; ++q) {
-                b += __hip_atomic_load(&partials[p0 + (int64_t)q * T + node], __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
+                b += handed_over(&partials[p0 + (int64_t)q * T + node]);
                 if (((q + 1) & ends) == 0 || q == nit - 1) {
                   s += b;
                   b = 0.0;
@@ -1190,8 +1200,14 @@ __global__ __launch_bounds__(256) void k_splat(
     // registers: a row then takes a subtraction, a test and an add per node,
     // where each node of the general loop reads and converts its coordinate
     // again. 4096 bricks of a 256^3 zoom into 100M points, 6 nodes an axis:
-    // whole call 199 us, 298 without; with 8 nodes kept 212, with the y nodes
-    // kept as well 200 and three wavefronts a SIMD, at which batches lost 1%.
+    // whole call 171 us, 298 without (with the y nodes kept as well 200 for the
+    // 199 it had then, at three wavefronts a SIMD, at which batches lost 1%).
+    // Registers for n nodes are worked through by supports of fewer nodes too:
+    // 8M uniform points at 200^3 take, with 1 to 8 nodes an axis, 286 417 737
+    // 1359 2452 4023 6280 9193 us in the general loop, 304 420 609 891 1313
+    // 1897 6285 9181 with 6 kept, 298 386 548 1368 2467 4036 with 3 and 308 446
+    // 670 1007 1508 2142 2926 3990 with 8. By default a brick's supports have 4
+    // nodes at most, but for regions of under 1/8 particle a node.
     constexpr int kSpan = 6;
     const bool short_span = floor(2.0 * half[0]) + 1.0 <= (double)kSpan;
 
@@ -1420,7 +1436,7 @@ __global__ __launch_bounds__(256) void k_splat(
       if (lds_last) {
         agent_writes_done();
         for (int n = threadIdx.x; n < T; n += 256)
-          write_node(n, __hip_atomic_load(&slot[n], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+          write_node(n, handed_over(&slot[n]));
       }
     }
     __syncthreads();
@@ -1685,9 +1701,9 @@ void k_sweep(TreeView tv, const BatchHdr* __restrict__ hdr, const RoiDev* __rest
             } else if constexpr (kRowTest && NM <= 3) {
               // The first node of the range on each axis, one exit, and the
               // nodes from there to the block's end. The range's own end
-              // needs no test: past it a square is at least 1 (c^2 in the
-              // other modes) and the terms are 0 (15 instructions of 250;
-              // 3-node supports 5.45 -> 5.20 ms of a batch of 256 zooms).
+              // needs no test: past it a square is at least 1 and the terms
+              // are 0 (15 instructions of 250; 3-node supports 5.45 -> 5.20 ms
+              // of a batch of 256 zooms).
 #pragma unroll
               for (int k = 0; k < 3; ++k) {
                 const double ic = (pp[k] - lo[k]) * inv_s[k];

@@ -651,16 +651,18 @@ int sweep_nm(const GroupRoi& g) {
   return nm;
 }
 
-// Leaves per work item of a ROI of `tiles` tiles. Bricks add integer sums, so
-// their chunks are a matter of speed alone. The other shapes add a chunk's
-// terms in float and the chunks in double, so the chunk may only depend on
-// the ROI, not on its batch. Below 16384 tiles there are few work items per
-// resident wavefront (3072 on 256 CUs) and the densest tile's chunk is the
-// last to end: 442k points at 64^3 (4096 tiles) take 465 us with 32 leaves,
-// 510 with 64, 590 with 128 and 640 with 256 (MBE, both grids), 1M per-point
-// at 101x87x93 242, 252, 293 and 381. From there on each chunk's partial sums
-// and hand-over weigh as much: 128^3 takes 2.06 ms with 32 leaves, 1.93 with
-// 64, 1.91 with 128 and 1.99 with 256, which needs the fewest slots.
+// Chunk of a ROI of `tiles` tiles. Bricks add integer sums, so their chunks are
+// a matter of speed alone. The other shapes add a chunk's terms in float and
+// the chunks in double, so the chunk may only depend on the ROI, not on its
+// batch. Below 16384 tiles there are few work items per resident wavefront
+// (3072 on 256 CUs) and the densest tile's item is the last to end. Whole calls
+// with 32, 64, 128 and 256 leaves: 1M points per-point at 64^3 (4096 tiles) 183,
+// 193, 233 and 255 us, at 100^3 (15625) 289, 290, 310 and 336; adaptive 511,
+// 557, 639, 690 and 735, 767, 824, 837. Above the line 32 still gains, but less
+// as items become many (104^3 310 for 367 us, 128^3 407 for 441; 400k points at
+// 128^3 390 for 388), and each chunk's sums and hand-over weigh the more the
+// longer the lists are (adaptive, 2.1M particles at 128^3: 2.06 ms with 32,
+// 1.93, 1.91 and 1.99). The line keeps the slots, up to eight a tile, at 64 MB.
 int chunk_leaves_of(sfk_ctx c, TileShape ts, int64_t tiles) {
   if (c->opts.chunk_leaves > 0) return c->opts.chunk_leaves;
   if (sfk::is_brick(ts)) return kBrickChunkLeaves;
@@ -668,9 +670,15 @@ int chunk_leaves_of(sfk_ctx c, TileShape ts, int64_t tiles) {
   return tiles < 16384 ? 32 : kDefaultChunkLeaves;
 }
 // A batch on the caller's stream of a few bricks over a small cloud: 8 leaves,
-// or 8 workgroups would do all of it (20k points at 32^3 in 8 bricks, whole
-// call: 55 us, 67 with 64 or 256). Where there are bricks enough, 64: 256
-// zooms into 100M points 11.80 ms, 11.90 with 16, 12.01 with 256.
+// or a workgroup per brick would do all of it (20k points at 32^3 in 8 bricks,
+// whole call: 55 us, 67 with 64 or 256). The lines, in us with 8 and with 64
+// leaves (h = 0.02): 8 bricks of 313 leaves 72 and 95, of 938 75 and 103, of
+// 1875 94 and 112, of 4063 117 and 128, of 8125 154 and 149; 64 bricks of 313
+// leaves 75 and 77, of 1875 107 and 136, of 8125 185 and 167; 343 bricks of 313
+// leaves 106 and 100, of 1875 162 and 172. Clouds under 80 leaves lose up to 4
+// of 70 us with few terms (h = 0.02) and gain up to 17 with many (0.06). Where
+// there are bricks enough, 64: 256 zooms into 100M points 11.80 ms, 11.90 with
+// 16, 12.01 with 256.
 int brick_batch_chunk(sfk_ctx c, int64_t tiles, int64_t tree_leaves) {
   if (c->opts.chunk_leaves > 0) return c->opts.chunk_leaves;
   return tiles < 64 && tree_leaves < 2048 ? 8 : kBrickChunkLeaves;
